@@ -79,14 +79,16 @@ __device__ __forceinline__ void llg_site(double kf, const double *H0, double ms,
     for (int w = 0; w < 3; w++) Mn[w] = ms * X[w] / nx;
 }
 
+// tid: the thread's index in its block of 256 (film blocks also run in
+// launches whose blocks are 64 x 4)
 template <typename T>
-__device__ __forceinline__ void film_body(const KParams<T> &p, int phase, int inc_step, int blk) {
+__device__ __forceinline__ void film_body(const KParams<T> &p, int phase, int inc_step, int blk, int tid) {
     __shared__ double red[256];
-    if (inc_step && blk == 0 && threadIdx.x == 0) p.step[0] = p.step[0] + 1;
+    if (inc_step && blk == 0 && tid == 0) p.step[0] = p.step[0] + 1;
     const int4 bt = block_entry(p.blocktab, blk); // film, family, first local index
     const int f = bt.x, c = bt.y;
     const FilmDev F = film_desc(p.films, f);
-    const long long l = (long long)bt.z + threadIdx.x;
+    const long long l = (long long)bt.z + tid;
     double own = 0.0;
     if (l < F.ns) {
         int idx[3];
@@ -155,13 +157,31 @@ __device__ __forceinline__ void film_body(const KParams<T> &p, int phase, int in
     // block partial of the own component (mean-M probes, which read it
     // between the two half steps: the second half step's would go unread)
     if (phase != 1) return;
-    red[threadIdx.x] = own;
+    red[tid] = own;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        if (tid < s) red[tid] += red[tid + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) p.partial[blk] = red[0];
+    if (tid == 0) p.partial[blk] = red[0];
+}
+
+// copy the scratch of a single (bracket) half step into the state: the block
+// of magnetic faces blk
+template <typename T>
+__device__ __forceinline__ void film_commit_body(const KParams<T> &p, int blk, int tid) {
+    const int4 bt = block_entry(p.blocktab, blk);
+    const int f = bt.x, c = bt.y;
+    const FilmDev F = film_desc(p.films, f);
+    const long long l = (long long)bt.z + tid;
+    if (l >= F.ns) return;
+    int idx[3];
+    idx[0] = F.b0[0] + (int)(l % F.bn[0]);
+    idx[1] = F.b0[1] + (int)((l / F.bn[0]) % F.bn[1]);
+    idx[2] = F.b0[2] + (int)(l / ((long long)F.bn[0] * F.bn[1]));
+    if (!(F.prm[(c * 3) * F.ns + l] > 0.0)) return;
+    for (int w = 0; w < 3; w++) F.M[(c * 3 + w) * F.ns + l] = F.M1[(c * 3 + w) * F.ns + l];
+    p.Hw[c][p.slot(idx[0], idx[1], idx[2])] = (T)F.H1[c * F.ns + l];
 }
 
 } // namespace mpx

@@ -466,12 +466,11 @@ mpx_status upload_profiles(mpx_sim *s) {
     return MPX_OK;
 }
 
-// the number of probes that ride in the merged H/M launch: all of them when
-// every one reads only E or a film's mean-M partials and the launch has film
-// blocks on 256 x 1 tiles, else none (the probe launch takes them)
-int folded_probes(const mpx_sim *s, bool wide) {
+// the number of probes that ride in the H/M launch: all of them when every one
+// reads only E or a film's mean-M partials (which that launch does not write),
+// else none (the probe launch takes them)
+int folded_probes(const mpx_sim *s) {
     const int np = (int)s->probes.size();
-    if (np == 0 || s->nblk == 0 || !wide) return 0;
     for (const ProbeHost &pr : s->probes)
         if (!probe_reads_e_or_m(pr.dev.kind, pr.dev.field)) return 0;
     return np;
@@ -531,7 +530,7 @@ mpx_status run_body(mpx_sim *s, int &par, bool timed) {
     // of them read only E or mean M: the H/M launch writes neither)
     KParams<T> p;
     fill_params<T>(s, p, MODE_INPLACE, par);
-    const int npf = folded_probes(s, p.wide != 0);
+    const int npf = folded_probes(s);
     if ((r = rec(0, 0)) != MPX_OK) return r;
     CK(launch_epass<T>(p, st));
     if ((r = rec(0, 1)) != MPX_OK) return r;
@@ -540,7 +539,7 @@ mpx_status run_body(mpx_sim *s, int &par, bool timed) {
     if (npf == 0) CK(launch_probes<T>(p, np, s->probe_maxpart, st));
     if ((r = rec(2, 1)) != MPX_OK) return r;
     if ((r = rec(1, 0)) != MPX_OK) return r;
-    CK(launch_hbulk_film<T>(p, nblk, 1, st, npf));
+    CK(launch_hbulk_film<T>(p, 2, nblk, 1, st, npf));
     if ((r = rec(1, 1)) != MPX_OK) return r;
     return MPX_OK;
 }
@@ -553,9 +552,9 @@ mpx_status run_last(mpx_sim *s, int par, hipStream_t st = nullptr) {
     if (!st) st = s->stream;
     CK(launch_epass<T>(p, st));
     CK(launch_film<T>(p, s->nblk, 1, 0, st));
-    CK(launch_probes<T>(p, (int)s->probes.size(), s->probe_maxpart, st));
-    CK(launch_commit<T>(p, s->nblk, st));
-    CK(launch_hbulk<T>(p, 1, 1, st));
+    const int npf = folded_probes(s);
+    if (npf == 0) CK(launch_probes<T>(p, (int)s->probes.size(), s->probe_maxpart, st));
+    CK(launch_hbulk_film<T>(p, 1, s->nblk, 1, st, npf));
     return MPX_OK;
 }
 
@@ -568,8 +567,7 @@ mpx_status enqueue_steps(mpx_sim *s, long long nsteps) {
         KParams<T> p;
         fill_params<T>(s, p, MODE_INPLACE, s->parity);
         CK(launch_film<T>(p, nblk, 1, 0, st));
-        CK(launch_commit<T>(p, nblk, st));
-        CK(launch_hbulk<T>(p, 1, 0, st));
+        CK(launch_hbulk_film<T>(p, 1, nblk, 0, st));
     }
     long long body = nsteps - 1;
     mpx_status r;
@@ -747,6 +745,9 @@ struct mpx_batch {
     int nwork = 0;
     int4 *d_work2 = nullptr; // separate passes: (instance, x tile, y tile, plane)
     int nwork2 = 0;
+    int4 *d_workh = nullptr; // the H/M pass: the film and probe blocks of every instance, then d_work2's tiles
+    int nworkh = 0;
+    std::vector<int> nfold; // per instance: the probes that ride in its H/M pass (decided with the tables)
     int2 *d_wmixed = nullptr; // mixed-slot blocks: (instance, first entry)
     int nwmixed = 0;
     bool any_xcls = false; // a member has extended-table slots
@@ -789,8 +790,9 @@ void batch_drop_graph(mpx_batch *b) {
 template <typename T>
 mpx_status batch_tables(mpx_batch *b) {
     b->any_xcls = false;
+    b->nfold.clear();
     // tiles instance by instance, in the single-instance order
-    std::vector<int4> work, work2;
+    std::vector<int4> work, work2, workh;
     std::vector<int2> wmixed, wfilm, wext, wprobe;
     std::vector<int> tick;
     for (int q = 0; q < (int)b->sims.size(); q++) {
@@ -810,13 +812,23 @@ mpx_status batch_tables(mpx_batch *b) {
         }
         for (int k = 0; k < s->nblk; k++) wfilm.push_back(make_int2(q, k));
         for (int k = 0; k < s->nblk_ext; k++) wext.push_back(make_int2(q, k));
-        for (int k = 0; k < (int)s->probes.size(); k++) wprobe.push_back(make_int2(q, k));
+        b->nfold.push_back(b->variant == 0 ? folded_probes(s) : 0);
+        const bool folded = b->nfold.back() > 0;
+        if (!folded)
+            for (int k = 0; k < (int)s->probes.size(); k++) wprobe.push_back(make_int2(q, k));
         if (s->nblk == 0) tick.push_back(q);
+        if (b->variant == 0) {
+            for (int k = 0; k < s->nblk; k++) workh.push_back(make_int4(q, -1 - k, 0, 0));
+            if (folded) workh.push_back(make_int4(q, kBatchProbes, 0, 0));
+        }
     }
+    workh.insert(workh.end(), work2.begin(), work2.end());
     b->probe_maxpart = 0;
-    for (const mpx_sim *s : b->sims) b->probe_maxpart = std::max(b->probe_maxpart, s->probe_maxpart);
+    for (size_t q = 0; q < b->sims.size(); q++)
+        if (b->nfold[q] == 0) b->probe_maxpart = std::max(b->probe_maxpart, b->sims[q]->probe_maxpart);
     (void)hipFree(b->d_work);
     (void)hipFree(b->d_work2);
+    (void)hipFree(b->d_workh);
     (void)hipFree(b->d_wmixed);
     (void)hipFree(b->d_wfilm);
     (void)hipFree(b->d_wext);
@@ -824,11 +836,13 @@ mpx_status batch_tables(mpx_batch *b) {
     (void)hipFree(b->d_tick);
     b->d_work = nullptr;
     b->d_work2 = nullptr;
+    b->d_workh = nullptr;
     b->d_wmixed = nullptr;
     b->d_wfilm = b->d_wext = b->d_wprobe = nullptr;
     b->d_tick = nullptr;
     b->nwork = (int)work.size();
     b->nwork2 = (int)work2.size();
+    b->nworkh = (int)workh.size();
     b->nwmixed = (int)wmixed.size();
     b->nwfilm = (int)wfilm.size();
     b->nwext = (int)wext.size();
@@ -839,6 +853,9 @@ mpx_status batch_tables(mpx_batch *b) {
     BCK(hipMalloc(&b->d_work2, std::max<size_t>(1, work2.size()) * sizeof(int4)));
     if (!work2.empty())
         BCK(hipMemcpy(b->d_work2, work2.data(), work2.size() * sizeof(int4), hipMemcpyHostToDevice));
+    BCK(hipMalloc(&b->d_workh, std::max<size_t>(1, workh.size()) * sizeof(int4)));
+    if (!workh.empty())
+        BCK(hipMemcpy(b->d_workh, workh.data(), workh.size() * sizeof(int4), hipMemcpyHostToDevice));
     auto up2 = [&](int2 **d, std::vector<int2> &v) -> mpx_status {
         BCK(hipMalloc(d, std::max<size_t>(1, v.size()) * sizeof(int2)));
         if (!v.empty()) BCK(hipMemcpy(*d, v.data(), v.size() * sizeof(int2), hipMemcpyHostToDevice));
@@ -865,6 +882,7 @@ mpx_status batch_params(mpx_batch *b) {
             const mpx_sim *s = b->sims[q];
             if (b->variant == 0) {
                 fill_params<T>(s, pa[q], MODE_INPLACE, s->parity);
+                pa[q].nfold = b->nfold[q];
                 pb[q] = pa[q];
             } else {
                 fill_params<T>(s, pa[q], MODE_FUSED, s->parity ^ f);
@@ -885,13 +903,13 @@ mpx_status batch_body(mpx_batch *b, int f) {
     const KParams<T> *pb = (const KParams<T> *)b->d_pb[f];
     hipStream_t st = b->stream;
     if (b->variant == 0) {
-        // E pass, film half steps and probes, then the bulk H pass (which
-        // moves every instance's step counter)
+        // E pass, the films' first half step and the probes that read H, then
+        // the H/M pass with the films' second half step and the other probes
+        // (it moves every instance's step counter)
         BCK(launch_epass_batch<T>(pa, b->d_work2, b->nwork2, b->d_wmixed, b->nwmixed, b->any_xcls, st));
         BCK(launch_film_batch<T>(pa, b->d_wext, b->nwext, b->d_wfilm, b->nwfilm, 1, 0, st));
         BCK(launch_probes_batch<T>(pa, b->d_wprobe, b->nwprobe, b->probe_maxpart, st));
-        BCK(launch_film_batch<T>(pa, b->d_wext, b->nwext, b->d_wfilm, b->nwfilm, 2, 0, st));
-        BCK(launch_hbulk_batch<T>(pa, b->d_work2, b->nwork2, 2, 1, st));
+        BCK(launch_hbulk_batch<T>(pa, b->d_workh, b->nworkh, 2, 1, st));
         return MPX_OK;
     }
     if (b->variant == 1)
@@ -915,8 +933,7 @@ mpx_status batch_steps(mpx_batch *b, long long nsteps) {
         KParams<T> p;
         fill_params<T>(s, p, MODE_INPLACE, s->parity);
         BCK(launch_film<T>(p, s->nblk, 1, 0, st));
-        BCK(launch_commit<T>(p, s->nblk, st));
-        BCK(launch_hbulk<T>(p, 1, 0, st));
+        BCK(launch_hbulk_film<T>(p, 1, s->nblk, 0, st));
     }
     long long body = nsteps - 1;
     int f = 0;
@@ -1178,8 +1195,7 @@ mpx_status half_step_inplace(mpx_sim *s) {
     KParams<T> p;
     fill_params<T>(s, p, MODE_INPLACE, s->parity);
     CK(launch_film<T>(p, s->nblk, 1, 0, s->stream));
-    CK(launch_commit<T>(p, s->nblk, s->stream));
-    CK(launch_hbulk<T>(p, 1, 0, s->stream));
+    CK(launch_hbulk_film<T>(p, 1, s->nblk, 0, s->stream));
     return MPX_OK;
 }
 
@@ -1774,8 +1790,7 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
             p.films = tvar(tp, 0, V_BR);
             CK(launch_film<T>(p, nblk, 1, 0, st));
             p.films = tvar(tp, 0, V_BRC);
-            CK(launch_commit<T>(p, nblk, st));
-            CK(launch_hbulk<T>(p, 1, 0, st));
+            CK(launch_hbulk_film<T>(p, 1, nblk, 0, st));
             for (int m = 0; m < len; m++) {
                 if (neps > 0) CK(launch_tape_box<T>(p, eps_box, tp.boxp(m), st));
                 CK(launch_epass<T>(p, st));
@@ -1787,11 +1802,10 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
                     // the film's second half step with the merged H/M pass
                     // (one launch on wide grids, as in stepping)
                     p.films = tvar(tp, m, V_P2);
-                    CK(launch_hbulk_film<T>(p, nblk, 1, st));
+                    CK(launch_hbulk_film<T>(p, 2, nblk, 1, st));
                 } else {
                     p.films = tvar(tp, m, V_C);
-                    CK(launch_commit<T>(p, nblk, st));
-                    CK(launch_hbulk<T>(p, 1, 1, st));
+                    CK(launch_hbulk_film<T>(p, 1, nblk, 1, st));
                 }
             }
             return MPX_OK;
@@ -3320,6 +3334,7 @@ mpx_status mpx_batch_destroy(mpx_batch *b) {
     }
     (void)hipFree(b->d_work);
     (void)hipFree(b->d_work2);
+    (void)hipFree(b->d_workh);
     (void)hipFree(b->d_wmixed);
     (void)hipFree(b->d_wfilm);
     (void)hipFree(b->d_wext);

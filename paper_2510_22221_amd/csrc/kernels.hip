@@ -218,30 +218,13 @@ __global__ void __launch_bounds__(256) k_bhat_batch(const KParams<T> *__restrict
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_film(KParams<T> p, int phase, int inc_step) {
-    film_body(p, phase, inc_step, blockIdx.x);
+    film_body(p, phase, inc_step, blockIdx.x, threadIdx.x);
 }
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_film_batch(const KParams<T> *__restrict__ plist, const int2 *__restrict__ work, int phase, int inc_step) {
     const int2 wk = work[blockIdx.x];
-    film_body(plist[wk.x], phase, inc_step, wk.y);
-}
-
-// copy the scratch of a single (bracket) half step into the state
-template <typename T>
-__global__ void __launch_bounds__(256) k_film_commit(KParams<T> p) {
-    const int4 bt = block_entry(p.blocktab, blockIdx.x);
-    const int f = bt.x, c = bt.y;
-    const FilmDev F = film_desc(p.films, f);
-    const long long l = (long long)bt.z + threadIdx.x;
-    if (l >= F.ns) return;
-    int idx[3];
-    idx[0] = F.b0[0] + (int)(l % F.bn[0]);
-    idx[1] = F.b0[1] + (int)((l / F.bn[0]) % F.bn[1]);
-    idx[2] = F.b0[2] + (int)(l / ((long long)F.bn[0] * F.bn[1]));
-    if (!(F.prm[(c * 3) * F.ns + l] > 0.0)) return;
-    for (int w = 0; w < 3; w++) F.M[(c * 3 + w) * F.ns + l] = F.M1[(c * 3 + w) * F.ns + l];
-    p.Hw[c][p.slot(idx[0], idx[1], idx[2])] = (T)F.H1[c * F.ns + l];
+    film_body(plist[wk.x], phase, inc_step, wk.y, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -607,13 +590,6 @@ hipError_t launch_tick(long long *step, hipStream_t s) {
 }
 
 template <typename T>
-hipError_t launch_commit(const KParams<T> &p, int nblk, hipStream_t s) {
-    if (nblk == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_film_commit<T>, dim3(nblk), dim3(256), 0, s, p);
-    return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_probes(const KParams<T> &p, int nprobe, int maxpart, hipStream_t s) {
     if (nprobe == 0) return hipSuccess;
     if (maxpart > 0) hipLaunchKernelGGL(k_probe_parts<T>, dim3(maxpart, nprobe), dim3(256), 0, s, p);
@@ -661,7 +637,6 @@ hipError_t launch_tick_batch(const KParams<T> *plist, const int *inst, int n, hi
 #define MPX_INSTANTIATE(T)                                                                  \
     template hipError_t launch_bhat<T>(const KParams<T> &, int, hipStream_t);               \
     template hipError_t launch_film<T>(const KParams<T> &, int, int, int, hipStream_t);     \
-    template hipError_t launch_commit<T>(const KParams<T> &, int, hipStream_t);             \
     template hipError_t launch_film_batch<T>(const KParams<T> *, const int2 *, int, const int2 *, int, int, int, \
                                              hipStream_t);                                  \
     template hipError_t launch_probes_batch<T>(const KParams<T> *, const int2 *, int, int, hipStream_t); \

@@ -147,6 +147,7 @@ struct KParams {
     SrcDev src[kMaxSources];
     const SrcDev *srcs; // the same sources in device memory
     const ProbeDev *probes;
+    int nfold; // batches: the probes that ride in this instance's H/M pass (all of them, or 0)
     long long *step;
     int *flag;
 
@@ -284,10 +285,11 @@ constexpr int kPassTX = 64, kPassTY = 4; // separate-pass tile: 64 x 4 slots of 
 constexpr int kWideTX = 256, kWideTY = 1; // the wide tile of the single-instance passes
 constexpr int kWideMinNx = 512;           // grids this wide use it
 
-// the bulk H/M pass with the film's second half step (and, nprobe > 0, the
-// probes, all of kinds probe_reads_e_or_m accepts; 256 x 1 tiles and films only)
+// the bulk H/M pass with the film's part of it (nhalf 2: the second half step
+// of a merged pair; 1: the commit of a half step) and, nprobe > 0, the probes
+// (all of kinds probe_reads_e_or_m accepts)
 template <typename T>
-hipError_t launch_hbulk_film(const KParams<T> &p, int nblk, int inc, hipStream_t s, int nprobe = 0);
+hipError_t launch_hbulk_film(const KParams<T> &p, int nhalf, int nblk, int inc, hipStream_t s, int nprobe = 0);
 template <typename T> hipError_t launch_film(const KParams<T> &p, int nblk, int phase, int inc, hipStream_t s);
 template <typename T> hipError_t launch_fused(const KParams<T> &p, int kchunk, int variant, hipStream_t s);
 template <typename T> hipError_t launch_sweep(const KParams<T> &p, int kchunk, hipStream_t s);
@@ -304,7 +306,7 @@ hipError_t launch_film_batch(const KParams<T> *plist, const int2 *work_ext, int 
 template <typename T>
 hipError_t launch_probes_batch(const KParams<T> *plist, const int2 *work, int n, int maxpart, hipStream_t s);
 template <typename T> hipError_t launch_tick_batch(const KParams<T> *plist, const int *inst, int n, hipStream_t s);
-template <typename T> hipError_t launch_commit(const KParams<T> &p, int nblk, hipStream_t s);
+constexpr int kBatchProbes = -0x7fffffff; // x tile of a batch work entry that is a probe block
 template <typename T> hipError_t launch_probes(const KParams<T> &p, int nprobe, int maxpart, hipStream_t s);
 template <typename T>
 hipError_t launch_energy(const KParams<T> &p, int nblk, double *part, double *out, hipStream_t s);

@@ -361,20 +361,26 @@ __global__ void __launch_bounds__(TX *TY) k_hbulk(KParams<T> p, int inc_step) {
     hpass_block<T, NHALF, TX, TY>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// the merged H/M pass and the film kernel's second half step in one launch
-// (256 x 1 tiles): the first zf planes of the grid are the film blocks,
-// dispatched first so that the latency-bound LLG solves overlap the bulk
-// planes.  The two touch disjoint data: the film blocks read the prepass the
+// the H/M pass and the film's part of it in one launch: the first zf planes
+// of the grid are the film blocks (256 threads, one block of magnetic faces
+// each), dispatched first so that their latency-bound work overlaps the bulk
+// planes.  NHALF 2: the merged pair, with the film's second half step; NHALF
+// 1: a bracket half step, with the commit of the film's half step.  The two
+// touch disjoint data: the film blocks read the prepass (or the scratch) the
 // first half step wrote and write M and H of magnetic faces, which the bulk
 // blocks load but never store or use.
-// the probes of an integer time when every one of them reads only E or the
-// film's mean-M partials (which this launch does not write), in the block
+// The probes of an integer time when every one of them reads only E or the
+// film's mean-M partials (which this launch does not write) ride in the block
 // right after the film blocks: its first wavefront reads the step counter,
 // samples each probe due and then advances the counter (no other block of
-// the launch reads it)
+// the launch reads it).
+// Every tile shape uses it: on a grid of 10^4..10^6 cells a launch of its own
+// costs the film blocks or the probes 4-7 us (their chain of dependent loads)
+// against no measurable time beside the bulk blocks.
+// tid: the thread's index in its block of 256
 template <typename T>
-__device__ __forceinline__ void probe_block(const KParams<T> &p, int nprobe, int inc_step) {
-    if (threadIdx.x >= 64) return; // one wavefront does it all
+__device__ __forceinline__ void probe_block(const KParams<T> &p, int nprobe, int inc_step, int tid) {
+    if (tid >= 64) return; // one wavefront does it all
     const long long step = p.step[0];
     for (int pb = 0; pb < nprobe; pb++) {
         const ProbeDev &P = p.probes[pb];
@@ -386,23 +392,34 @@ __device__ __forceinline__ void probe_block(const KParams<T> &p, int nprobe, int
     }
     // lane 0 advances the counter after every lane has read it (one
     // wavefront: its reads above precede this store)
-    if (inc_step && threadIdx.x == 0) p.step[0] = step + 1;
+    if (inc_step && tid == 0) p.step[0] = step + 1;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kWideTX) k_hbulk_film(KParams<T> p, int inc_step, int zf, int nfb, int nprobe) {
+template <typename T, int NHALF>
+__device__ __forceinline__ void film_part(const KParams<T> &p, int blk, int tid) {
+    if constexpr (NHALF == 2)
+        film_body(p, 2, 0, blk, tid);
+    else
+        film_commit_body(p, blk, tid);
+}
+
+template <typename T, int NHALF, int TX, int TY>
+__global__ void __launch_bounds__(TX *TY) k_hbulk_film(KParams<T> p, int inc_step, int zf, int nfb, int nprobe) {
+    static_assert(TX * TY == 256, "film blocks are 256 threads");
     if ((int)blockIdx.z < zf) {
         const int fb = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
+        const int tid = (int)threadIdx.x + TX * (int)threadIdx.y;
         if (fb < nfb)
-            film_body(p, 2, 0, fb);
+            film_part<T, NHALF>(p, fb, tid);
         else if (fb == nfb && nprobe > 0)
-            probe_block(p, nprobe, inc_step);
+            probe_block(p, nprobe, inc_step, tid);
         return;
     }
     const int k = (int)blockIdx.z - zf;
-    if (inc_step && nprobe == 0 && blockIdx.x == 0 && blockIdx.y == 0 && k == 0 && threadIdx.x == 0)
+    if (inc_step && nprobe == 0 && blockIdx.x == 0 && blockIdx.y == 0 && k == 0 && threadIdx.x == 0 &&
+        threadIdx.y == 0)
         p.step[0] = p.step[0] + 1;
-    hpass_block<T, 2, kWideTX, kWideTY>(p, blockIdx.x, blockIdx.y, k);
+    hpass_block<T, NHALF, TX, TY>(p, blockIdx.x, blockIdx.y, k);
 }
 
 template <typename T>
@@ -433,7 +450,10 @@ __global__ void __launch_bounds__(256)
     if (m < p.nmixed) emixed_slot<T>(p, m);
 }
 
-// the step counter of each instance moves with its first block (inc_step)
+// work[w] = (instance, x tile, y tile, plane), or (instance, -1 - film block,
+// 0, 0), or (instance, kBatchProbes, 0, 0): the film blocks and the probe
+// block of an instance ride in the launch as in k_hbulk_film.  The step
+// counter of an instance moves with its probe block, or else its first tile.
 template <typename T, int NHALF>
 __global__ void __launch_bounds__(PTX *PTY)
     k_hbulk_batch(const KParams<T> *__restrict__ plist, const int4 *__restrict__ work, int nwork, int inc_step) {
@@ -441,7 +461,15 @@ __global__ void __launch_bounds__(PTX *PTY)
     if (w >= nwork) return;
     const int4 wk = work[w];
     const KParams<T> &p = plist[wk.x];
-    if (inc_step && wk.y == 0 && wk.z == 0 && wk.w == 0 && threadIdx.x == 0 && threadIdx.y == 0)
+    if (wk.y < 0) {
+        const int tid = (int)threadIdx.x + PTX * (int)threadIdx.y;
+        if (wk.y == kBatchProbes)
+            probe_block(p, p.nfold, inc_step, tid);
+        else
+            film_part<T, NHALF>(p, -1 - wk.y, tid);
+        return;
+    }
+    if (inc_step && p.nfold == 0 && wk.y == 0 && wk.z == 0 && wk.w == 0 && threadIdx.x == 0 && threadIdx.y == 0)
         p.step[0] = p.step[0] + 1;
     hpass_block<T, NHALF>(p, wk.y, wk.z, wk.w);
 }
@@ -487,23 +515,31 @@ hipError_t launch_hbulk(const KParams<T> &p, int nhalf, int inc, hipStream_t s) 
     return hipGetLastError();
 }
 
-// the film's second half step (nblk blocks) and the merged H/M pass; on
-// 256 x 1 tiles one launch, else two
-template <typename T>
-hipError_t launch_hbulk_film(const KParams<T> &p, int nblk, int inc, hipStream_t s, int nprobe) {
-    // probes ride in the launch only beside film blocks on 256 x 1 tiles
-    if (nprobe > 0 && (nblk == 0 || !p.wide)) return hipErrorInvalidValue;
-    if (nblk == 0) return launch_hbulk<T>(p, 2, inc, s);
-    if (!p.wide) {
-        hipError_t e = launch_film<T>(p, nblk, 2, 0, s);
-        if (e != hipSuccess) return e;
-        return launch_hbulk<T>(p, 2, inc, s);
-    }
-    static_assert(kWideTX == 256 && kWideTY == 1, "film blocks are 256 threads along x");
-    const dim3 g = pass_grid<kWideTX, kWideTY>(p.n);
+template <typename T, int NHALF, int TX, int TY>
+static void launch_hm(const KParams<T> &p, int nblk, int inc, int nprobe, hipStream_t s) {
+    const dim3 g = pass_grid<TX, TY>(p.n);
     const int per_plane = (int)(g.x * g.y);
     const int zf = (nblk + (nprobe > 0 ? 1 : 0) + per_plane - 1) / per_plane;
-    k_hbulk_film<T><<<dim3(g.x, g.y, g.z + zf), dim3(kWideTX, kWideTY), 0, s>>>(p, inc, zf, nblk, nprobe);
+    k_hbulk_film<T, NHALF, TX, TY><<<dim3(g.x, g.y, g.z + zf), dim3(TX, TY), 0, s>>>(p, inc, zf, nblk, nprobe);
+}
+
+// the H/M pass with the film's part (nblk blocks: the second half step of a
+// merged pair, nhalf = 2, or the commit of a bracket half step, nhalf = 1)
+// and nprobe probes
+template <typename T>
+hipError_t launch_hbulk_film(const KParams<T> &p, int nhalf, int nblk, int inc, hipStream_t s, int nprobe) {
+    if (nblk == 0 && nprobe == 0) return launch_hbulk<T>(p, nhalf, inc, s);
+    if (p.wide) {
+        if (nhalf == 1)
+            launch_hm<T, 1, kWideTX, kWideTY>(p, nblk, inc, nprobe, s);
+        else
+            launch_hm<T, 2, kWideTX, kWideTY>(p, nblk, inc, nprobe, s);
+    } else {
+        if (nhalf == 1)
+            launch_hm<T, 1, PTX, PTY>(p, nblk, inc, nprobe, s);
+        else
+            launch_hm<T, 2, PTX, PTY>(p, nblk, inc, nprobe, s);
+    }
     return hipGetLastError();
 }
 
@@ -534,7 +570,7 @@ hipError_t launch_hbulk_batch(const KParams<T> *plist, const int4 *work, int nwo
 #define MPX_PASSES(T)                                                                                      \
     template hipError_t launch_epass<T>(const KParams<T> &, hipStream_t);                                 \
     template hipError_t launch_hbulk<T>(const KParams<T> &, int, int, hipStream_t);                       \
-    template hipError_t launch_hbulk_film<T>(const KParams<T> &, int, int, hipStream_t, int);                  \
+    template hipError_t launch_hbulk_film<T>(const KParams<T> &, int, int, int, hipStream_t, int);             \
     template hipError_t launch_epass_batch<T>(const KParams<T> *, const int4 *, int, const int2 *, int,   \
                                               bool, hipStream_t);                                         \
     template hipError_t launch_hbulk_batch<T>(const KParams<T> *, const int4 *, int, int, int, hipStream_t);
