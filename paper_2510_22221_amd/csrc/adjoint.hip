@@ -18,18 +18,9 @@
 //     of each face and the edge coefficients ca, cb collect gradients.
 // One thread per slot or per film face; every sum a thread forms is a gather
 // (no atomics), so results do not depend on scheduling.
-#include "device_common.h"
+#include "film.h"
 
 namespace mpx {
-
-__device__ __forceinline__ void cross3a(const double *a, const double *b, double *r) {
-    r[0] = a[1] * b[2] - a[2] * b[1];
-    r[1] = a[2] * b[0] - a[0] * b[2];
-    r[2] = a[0] * b[1] - a[1] * b[0];
-}
-__device__ __forceinline__ double dot3a(const double *a, const double *b) {
-    return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
-}
 
 // local index of face idx (folded) in the film's face box, -1 outside
 __device__ __forceinline__ long long film_local_idx(const FilmDev &F, const int *idx) {
@@ -60,86 +51,75 @@ __device__ __forceinline__ int mag_site(const KParams<T> &p, int c, const int *i
 // magnetic faces: lambda of (M', H'_c) -> lambda of M (direct), P, Q; the
 // prepass (B^n, B^* of the input state) must have run
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) k_adj_film(AdjParams<T> A) {
+// (latency-bound like the forward film kernel: all loads of a face go out
+// before the magnetic test; 8.9 to 5.5 us on a 64 x 12 x 4 film, 16.4 to 14.2
+// on 256 x 48 x 4)
+template <typename T, int c>
+__device__ __forceinline__ void adj_film_face(const AdjParams<T> &A, const FilmDev &F, const AdjFilmDev &G,
+                                              unsigned l) {
     const KParams<T> &p = A.p;
-    const int4 bt = block_entry(p.blocktab, blockIdx.x);
-    const int f = bt.x, c = bt.y;
-    const FilmDev F = film_desc(p.films, f);
-    const AdjFilmDev G = scalar_desc(A.af, f);
-    const long long l = (long long)bt.z + threadIdx.x;
-    if (l >= F.ns) return;
-    const double ms = F.prm[(c * 3 + 0) * F.ns + l];
+    int r[3];
+    box_split(l, F.bn, r);
+    double ms = F.prm[(c * 3 + 0) * F.ns + l];
     const double al = F.prm[(c * 3 + 1) * F.ns + l];
     const double ga = F.prm[(c * 3 + 2) * F.ns + l];
-    if (!(ms > 0.0)) return;
-    int idx[3];
-    idx[0] = F.b0[0] + (int)(l % F.bn[0]);
-    idx[1] = F.b0[1] + (int)((l / F.bn[0]) % F.bn[1]);
-    idx[2] = F.b0[2] + (int)(l / ((long long)F.bn[0] * F.bn[1]));
-    auto ext = [&](const int *q) -> long long {
-        const int r0 = q[0] - F.e0[0], r1 = q[1] - F.e0[1], r2 = q[2] - F.e0[2];
-        if (r0 < 0 || r0 >= F.en[0] || r1 < 0 || r1 >= F.en[1] || r2 < 0 || r2 >= F.en[2]) return -1;
-        return (long long)r0 + (long long)F.en[0] * ((long long)r1 + (long long)F.en[1] * r2);
-    };
-    // the forward quantities (as the film kernel computes them)
-    const long long le = ext(idx);
-    double P[3], Q[3], M[3];
-    P[c] = le >= 0 ? F.Bs[c * F.nse + le] : 0.0;
-    Q[c] = le >= 0 ? F.Bn[c * F.nse + le] : 0.0;
-    for (int cp = 0; cp < 3; cp++) {
-        if (cp == c) continue;
-        double vn[2][2], vs[2][2];
-        for (int u = 0; u < 2; u++)
-            for (int v = 0; v < 2; v++) {
-                int q[3] = {idx[0], idx[1], idx[2]};
-                q[c] += u - 1;
-                q[cp] += v;
-                for (int a = 0; a < 3; a++) q[a] = fold(q[a], p.n[a], p.per[a]);
-                const long long lq = ext(q);
-                vn[u][v] = lq >= 0 ? F.Bn[cp * F.nse + lq] : 0.0;
-                vs[u][v] = lq >= 0 ? F.Bs[cp * F.nse + lq] : 0.0;
-            }
-        Q[cp] = ((vn[0][0] + vn[1][0]) + (vn[0][1] + vn[1][1])) * 0.25;
-        P[cp] = ((vs[0][0] + vs[1][0]) + (vs[0][1] + vs[1][1])) * 0.25;
+    // the forward quantities (as the film kernel computes them), lambda M' and
+    // lambda H' of the face, the accumulators
+    double P[3], Q[3], M[3], lMt[3], gh[3];
+    int le;
+    film_gather(p.n, p.per, F, c, r, F.Bn, F.Bs, P, Q, le);
+    const long long sl = p.slot(F.b0[0] + r[0], F.b0[1] + r[1], F.b0[2] + r[2]);
+    double lh = (double)A.lH[c][sl], g0 = G.gMs[c * F.ns + l];
+#pragma unroll
+    for (int w = 0; w < 3; w++) {
+        M[w] = F.M[(c * 3 + w) * F.ns + l];
+        lMt[w] = G.lM[(c * 3 + w) * F.ns + l];
+        gh[w] = G.gH0[(c * 3 + w) * F.ns + l];
     }
+#pragma unroll
+    for (int w = 0; w < 3; w++) {
+        hold(P[w]);
+        hold(Q[w]);
+        hold(M[w]);
+        hold(lMt[w]);
+        hold(gh[w]);
+    }
+    hold(lh);
+    hold(g0);
+    if (!(ms > 0.0)) return;
     for (int w = 0; w < 3; w++) {
         P[w] += p.H0[w];
         Q[w] += p.H0[w];
-        M[w] = F.M[(c * 3 + w) * F.ns + l];
     }
     const double kk = p.kf * ga;
     double MxQ[3], b[3], a[3];
-    cross3a(M, Q, MxQ);
+    cross3(M, Q, MxQ);
     for (int w = 0; w < 3; w++) b[w] = M[w] - kk * MxQ[w];
     for (int w = 0; w < 3; w++) a[w] = -(kk * P[w] + (al / ms) * M[w]);
     double axb[3], X[3];
-    cross3a(a, b, axb);
-    const double ab = dot3a(a, b), aa = dot3a(a, a);
+    cross3(a, b, axb);
+    const double ab = dot3(a, b), aa = dot3(a, a);
     const double D = 1.0 + aa;
     for (int w = 0; w < 3; w++) X[w] = (b[w] + ab * a[w] - axb[w]) / D;
-    const double nx = sqrt(dot3a(X, X));
+    const double nx = sqrt(dot3(X, X));
     double u[3];
     for (int w = 0; w < 3; w++) u[w] = X[w] / nx;
 
     // lambda of M' (the face's H' = B^*_c - M'_c contributes -lambda H'_c)
-    const long long sl = p.slot(idx[0], idx[1], idx[2]);
-    double lMt[3];
-    for (int w = 0; w < 3; w++) lMt[w] = G.lM[(c * 3 + w) * F.ns + l];
-    lMt[c] -= (double)A.lH[c][sl];
+    lMt[c] -= lh;
     // M' = Ms u, u = X/|X|
-    const double ul = dot3a(u, lMt);
+    const double ul = dot3(u, lMt);
     double gms = ul;
     double lX[3];
     for (int w = 0; w < 3; w++) lX[w] = ms * (lMt[w] - u[w] * ul) / nx;
     // X = N / D, N = b + (a.b) a - a x b, D = 1 + a.a
     double lN[3];
     for (int w = 0; w < 3; w++) lN[w] = lX[w] / D;
-    const double lD = -dot3a(lX, X) / D;
-    const double alN = dot3a(a, lN);
+    const double lD = -dot3(lX, X) / D;
+    const double alN = dot3(a, lN);
     double lNxb[3], lNxa[3];
-    cross3a(lN, b, lNxb);
-    cross3a(lN, a, lNxa);
+    cross3(lN, b, lNxb);
+    cross3(lN, a, lNxa);
     double la[3], lb[3];
     for (int w = 0; w < 3; w++) {
         la[w] = 2.0 * a[w] * lD + b[w] * alN + ab * lN[w] + lNxb[w];
@@ -147,21 +127,37 @@ __global__ void __launch_bounds__(256) k_adj_film(AdjParams<T> A) {
     }
     // a = -(k P + (alpha/Ms) M);  b = M - k M x Q
     double lP[3], lQ[3], lMd[3], Qxlb[3], lbxM[3];
-    cross3a(Q, lb, Qxlb);
-    cross3a(lb, M, lbxM);
+    cross3(Q, lb, Qxlb);
+    cross3(lb, M, lbxM);
     for (int w = 0; w < 3; w++) {
         lP[w] = -kk * la[w];
         lQ[w] = -kk * lbxM[w];
         lMd[w] = -(al / ms) * la[w] + lb[w] - kk * Qxlb[w];
     }
-    gms += (al / (ms * ms)) * dot3a(M, la);
+    gms += (al / (ms * ms)) * dot3(M, la);
     for (int w = 0; w < 3; w++) {
         G.lp[(c * 3 + w) * F.ns + l] = lP[w];
         G.lq[(c * 3 + w) * F.ns + l] = lQ[w];
         G.lMout[(c * 3 + w) * F.ns + l] = lMd[w];
-        G.gH0[(c * 3 + w) * F.ns + l] += lP[w] + lQ[w];
+        G.gH0[(c * 3 + w) * F.ns + l] = gh[w] + (lP[w] + lQ[w]);
     }
-    G.gMs[c * F.ns + l] += gms;
+    G.gMs[c * F.ns + l] = g0 + gms;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_adj_film(AdjParams<T> A) {
+    const KParams<T> &p = A.p;
+    const int4 bt = block_entry(p.blocktab, blockIdx.x);
+    const FilmDev F = block_desc(p.films, p.nfilm, bt.x);
+    const AdjFilmDev G = block_desc(A.af, p.nfilm, bt.x);
+    const unsigned l = (unsigned)bt.z + threadIdx.x;
+    if (l >= (unsigned)F.ns) return;
+    if (bt.y == 0)
+        adj_film_face<T, 0>(A, F, G, l);
+    else if (bt.y == 1)
+        adj_film_face<T, 1>(A, F, G, l);
+    else
+        adj_film_face<T, 2>(A, F, G, l);
 }
 
 // can the face at idx be magnetic or be read by a magnetic face's solve (a
@@ -655,9 +651,10 @@ __global__ void k_accum(const double *part, int n, double *acc, double scale) {
 // slot of region index t after folding; a slot that the fold maps onto an
 // index the region already holds (a box spanning a periodic axis) belongs to
 // that index.  Returns false for no slot or a slot owned elsewhere.
-__device__ __forceinline__ bool region_slot(const int *n, const int *per, const int *b0, const int *r, long long t,
+__device__ __forceinline__ bool region_slot(const int *n, const int *per, const int *b0, const int *r, unsigned t,
                                             int *q) {
-    const int loc[3] = {(int)(t % r[0]), (int)((t / r[0]) % r[1]), (int)(t / ((long long)r[0] * r[1]))};
+    int loc[3];
+    box_split(t, r, loc);
     for (int a = 0; a < 3; a++) {
         int v = b0[a] + loc[a];
         if (v >= n[a]) {
@@ -690,13 +687,15 @@ __device__ __forceinline__ long long region_index(const int *n, const int *per, 
 // the film's E and H at an integer time over its cell box grown by one slot:
 // [6][region] (Ex, Ey, Ez, Hx, Hy, Hz).  merged = 1: between the two film half
 // steps of a merged pair (magnetic faces' H in the film's staging, bulk faces'
-// H one bulk half step ahead of the stored H); 0: a state at an integer time
+// H one bulk half step ahead of the stored H); 0: a state at an integer time.
+// No other film's faces lie in the region (films are at least two cells
+// apart); every load goes out at once, what a face does not use is dropped.
 template <typename T>
 __global__ void __launch_bounds__(256) k_tape_loss(KParams<T> p, int film, int merged, double *dst) {
-    const FilmDev &F = p.films[film];
+    const FilmDev F = film_desc(p.films, film);
     const int b0[3] = {F.cb[0], F.cb[1], F.cb[2]}, r[3] = {F.cb[3] + 1, F.cb[4] + 1, F.cb[5] + 1};
     const long long tb = (long long)r[0] * r[1] * r[2];
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
     if (t >= tb) return;
     int q[3];
     if (!region_slot(p.n, p.per, b0, r, t, q)) {
@@ -704,25 +703,47 @@ __global__ void __launch_bounds__(256) k_tape_loss(KParams<T> p, int film, int m
         return;
     }
     const long long sl = p.slot(q[0], q[1], q[2]);
+    // the +1 neighbours along each axis (zero past a wall)
+    long long su[3];
+    bool ok[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        int u[3] = {q[0], q[1], q[2]};
+        u[a] = fold(q[a] + 1, p.n[a], p.per[a]);
+        ok[a] = u[a] >= 0;
+        su[a] = ok[a] ? p.slot(u[0], u[1], u[2]) : sl;
+    }
+    T e[3], h[3], eu[3][3];
+    double h1[3] = {0.0, 0.0, 0.0}, ms[3] = {0.0, 0.0, 0.0};
+    bool inside = false;
+    long long l = 0;
+    if (merged && p.nfilm) l = film_local<T>(F, q, inside);
+#pragma unroll
     for (int C = 0; C < 3; C++) {
-        dst[C * tb + t] = (double)p.E[C][sl];
-        double h;
-        long long l;
-        const int f = merged && p.nfilm ? mag_site(p, C, q, l) : -1;
-        if (!merged) {
-            h = (double)p.H[C][sl];
-        } else if (f >= 0) {
-            h = p.films[f].H1[C * p.films[f].ns + l];
-        } else {
-            const int C1 = (C + 1) % 3, C2 = (C + 2) % 3;
-            int u1[3] = {q[0], q[1], q[2]}, u2[3] = {q[0], q[1], q[2]};
-            u1[C1] += 1;
-            u2[C2] += 1;
-            const T d1 = dif(ldz(p, p.E[C2], u1[0], u1[1], u1[2]), p.E[C2][sl], p.dT[C1], p.invd[C1]);
-            const T d2 = dif(ldz(p, p.E[C1], u2[0], u2[1], u2[2]), p.E[C1][sl], p.dT[C2], p.invd[C2]);
-            h = (double)(p.H[C][sl] - p.hc * (d1 - d2));
+        e[C] = p.E[C][sl];
+        h[C] = p.H[C][sl];
+        if (merged) {
+            // E_C at +1 along the other two axes
+            eu[C][(C + 1) % 3] = p.E[C][su[(C + 1) % 3]];
+            eu[C][(C + 2) % 3] = p.E[C][su[(C + 2) % 3]];
+            if (p.nfilm) {
+                h1[C] = F.H1[C * F.ns + l];
+                ms[C] = F.prm[(C * 3) * F.ns + l];
+            }
         }
-        dst[(3 + C) * tb + t] = h;
+    }
+#pragma unroll
+    for (int C = 0; C < 3; C++) {
+        dst[C * tb + t] = (double)e[C];
+        double hv = (double)h[C];
+        if (merged) {
+            const int C1 = (C + 1) % 3, C2 = (C + 2) % 3;
+            const T d1 = dif(ok[C1] ? eu[C2][C1] : T(0), e[C2], p.dT[C1], p.invd[C1]);
+            const T d2 = dif(ok[C2] ? eu[C1][C2] : T(0), e[C1], p.dT[C2], p.invd[C2]);
+            hv = (double)(h[C] - p.hc * (d1 - d2));
+            if (inside && ms[C] > 0.0) hv = h1[C];
+        }
+        dst[(3 + C) * tb + t] = hv;
     }
 }
 
@@ -737,7 +758,7 @@ __global__ void __launch_bounds__(256) k_adj_loss_tape(AdjParams<T> A, int film,
     const FilmDev &F = p.films[film];
     const int b0[3] = {F.cb[0], F.cb[1], F.cb[2]}, r[3] = {F.cb[3] + 1, F.cb[4] + 1, F.cb[5] + 1};
     const long long tb = (long long)r[0] * r[1] * r[2];
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
     int q[3];
     if (t >= tb || !region_slot(p.n, p.per, b0, r, t, q)) return;
     const long long sl = p.slot(q[0], q[1], q[2]);
@@ -837,7 +858,7 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_tape_box(KParams<T> p, int4 bb, int4 bs, double *dst) {
     const int b0[3] = {bb.x, bb.y, bb.z}, r[3] = {bs.x + 1, bs.y + 1, bs.z + 1};
     const long long tb = (long long)r[0] * r[1] * r[2];
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
     if (t >= tb) return;
     int q[3];
     if (!region_slot(p.n, p.per, b0, r, t, q)) {
@@ -846,13 +867,25 @@ __global__ void __launch_bounds__(256) k_tape_box(KParams<T> p, int4 bb, int4 bs
     }
     const long long sl = p.slot(q[0], q[1], q[2]);
     const long long step = p.step[0];
+    // H at the slot and at its -1 neighbours (zero past a wall), all at once
+    T h0[3], hm[3][3], e0[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        int u[3] = {q[0], q[1], q[2]};
+        u[a] = fold(q[a] - 1, p.n[a], p.per[a]);
+        const bool ok = u[a] >= 0;
+        const long long su = ok ? p.slot(u[0], u[1], u[2]) : sl;
+        const T x1 = p.H[(a + 1) % 3][su], x2 = p.H[(a + 2) % 3][su];
+        hm[(a + 1) % 3][a] = ok ? x1 : T(0);
+        hm[(a + 2) % 3][a] = ok ? x2 : T(0);
+        h0[a] = p.H[a][sl];
+        e0[a] = p.E[a][sl];
+    }
+#pragma unroll
     for (int C = 0; C < 3; C++) {
         const int C1 = (C + 1) % 3, C2 = (C + 2) % 3;
-        int d1i[3] = {q[0], q[1], q[2]}, d2i[3] = {q[0], q[1], q[2]};
-        d1i[C1] -= 1;
-        d2i[C2] -= 1;
-        T d1 = dif(p.H[C2][sl], ldz(p, p.H[C2], d1i[0], d1i[1], d1i[2]), p.dT[C1], p.invd[C1]);
-        T d2 = dif(p.H[C1][sl], ldz(p, p.H[C1], d2i[0], d2i[1], d2i[2]), p.dT[C2], p.invd[C2]);
+        T d1 = dif(h0[C2], hm[C2][C1], p.dT[C1], p.invd[C1]);
+        T d2 = dif(h0[C1], hm[C1][C2], p.dT[C2], p.invd[C2]);
         const int a1 = q[C1], a2 = q[C2];
         if (p.psiE[C][C1] && (a1 < p.nlo[C1] || a1 >= p.n[C1] - p.nhi[C1]))
             d1 += p.bE[C1][a1] * p.psiE[C][C1][p.psi_index(C1, q)] + p.cE[C1][a1] * d1;
@@ -867,7 +900,7 @@ __global__ void __launch_bounds__(256) k_tape_box(KParams<T> p, int4 bb, int4 bs
                 continue;
             if (step < S.n) J += S.table[step];
         }
-        dst[C * tb + t] = (double)p.E[C][sl];
+        dst[C * tb + t] = (double)e0[C];
         dst[(3 + C) * tb + t] = (double)(d1 - d2) - J;
     }
 }
@@ -1036,21 +1069,116 @@ __device__ __forceinline__ bool nb_or_self(const int *n, const int *per, const i
     return ok;
 }
 
+// adj_face_core for a face of family C at slot idx inside the reach of film F
+// that no other film's reach meets (G.alone), off the CPML slabs: only this
+// film's faces matter, and every load goes out at once (a face outside the
+// face box reads its element 0, and what it does not use is dropped)
+template <typename T, int C>
+__device__ __forceinline__ void adj_face_alone(const AdjParams<T> &A, const FilmDev &F, const AdjFilmDev &G,
+                                               const int *idx, T &ad0, T &ad1) {
+    const KParams<T> &p = A.p;
+    const long long q = p.slot(idx[0], idx[1], idx[2]);
+    double lHp = (double)A.lH[C][q];
+    bool in0;
+    const long long lm = film_local<T>(F, idx, in0);
+    double own = F.prm[(C * 3) * F.ns + lm], olp = G.lp[(C * 3 + C) * F.ns + lm], olq = G.lq[(C * 3 + C) * F.ns + lm],
+           omo = G.lMout[(C * 3 + C) * F.ns + lm];
+    // the magnetic faces s = t + a e_cs - b e_C of each other family cs with
+    // this face in their four-face mean
+    double tms[2][2][2], tlp[2][2][2], tlq[2][2][2];
+    bool tin[2][2][2];
+#pragma unroll
+    for (int v = 0; v < 2; v++) {
+        // families in the order of adj_face_core: the lower of the two first
+        const int cs = v == 0 ? (C == 0 ? 1 : 0) : (C == 2 ? 1 : 2);
+#pragma unroll
+        for (int aa = 0; aa < 2; aa++)
+#pragma unroll
+            for (int bb = 0; bb < 2; bb++) {
+                int s[3] = {idx[0], idx[1], idx[2]};
+                s[cs] = fold(s[cs] + aa, p.n[cs], p.per[cs]);
+                s[C] = fold(s[C] - bb, p.n[C], p.per[C]);
+                bool in;
+                const long long ls = film_local<T>(F, s, in); // false for a folded -1 too
+                tin[v][aa][bb] = in;
+                tms[v][aa][bb] = F.prm[(cs * 3) * F.ns + ls];
+                tlp[v][aa][bb] = G.lp[(cs * 3 + C) * F.ns + ls];
+                tlq[v][aa][bb] = G.lq[(cs * 3 + C) * F.ns + ls];
+            }
+    }
+    hold(lHp);
+    hold(own);
+    hold(olp);
+    hold(olq);
+    hold(omo);
+#pragma unroll
+    for (int v = 0; v < 8; v++) {
+        hold((&tms[0][0][0])[v]);
+        hold((&tlp[0][0][0])[v]);
+        hold((&tlq[0][0][0])[v]);
+    }
+    const bool mag = in0 && own > 0.0;
+    double lbs_f = 0.0, lbn = 0.0;
+    if (mag) {
+        lbs_f += olp;
+        lbn += olq;
+    }
+#pragma unroll
+    for (int v = 0; v < 2; v++)
+#pragma unroll
+        for (int aa = 0; aa < 2; aa++)
+#pragma unroll
+            for (int bb = 0; bb < 2; bb++)
+                if (tin[v][aa][bb] && tms[v][aa][bb] > 0.0) {
+                    lbs_f += 0.25 * tlp[v][aa][bb];
+                    lbn += 0.25 * tlq[v][aa][bb];
+                }
+    if (mag) {
+        const double lbs = lHp + lbs_f;
+        const double lbt = lbn + lbs;
+        A.lH[C][q] = (T)lbt;
+        G.lMout[(C * 3 + C) * F.ns + lm] = omo + lbt;
+        ad0 = (T)(-p.hcd * lbs);
+        ad1 = (T)(p.hcd * lbs);
+    } else {
+        A.lH[C][q] = (T)(lHp + lbn + lbs_f);
+        ad0 = (T)(-(double)p.hc * lHp - p.hcd * lbs_f);
+        ad1 = (T)((double)p.hc * lHp + p.hcd * lbs_f);
+    }
+}
+
 // the film region's faces: the general face adjoint (magnetic faces, faces
 // the solves read), lambda H and lambda M updated in place, the curl-part
-// adjoints stored for the field pass
+// adjoints stored for the field pass.  A film apart from the others and off
+// the slabs (G.alone, decided once by the host) takes the straight-line form:
+// the general one's film loop and tests put up to eleven round trips in a row
+// (12.4 us on the reach of a 64 x 12 x 4 film, 19.6 us of 256 x 48 x 4; 4.9
+// and 9.8 us without them)
 template <typename T>
 __global__ void __launch_bounds__(256) k_adj_film_faces(AdjParams<T> A, int f) {
     const AdjFilmDev G = scalar_desc(A.af, f);
-    const long long lr = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (lr >= G.nr) return;
-    const int idx[3] = {G.r0[0] + (int)(lr % G.rn[0]), G.r0[1] + (int)((lr / G.rn[0]) % G.rn[1]),
-                        G.r0[2] + (int)(lr / ((long long)G.rn[0] * G.rn[1]))};
-    long long l2;
-    if (first_region(A, idx, l2) != f) return;
+    const FilmDev FD = film_desc(A.p.films, f);
+    const unsigned lr = blockIdx.x * 256u + threadIdx.x;
+    if (lr >= (unsigned)G.nr) return;
+    int idx[3];
+    box_split(lr, G.rn, idx);
+    for (int a = 0; a < 3; a++) idx[a] += G.r0[a];
     // one face family per grid row
     T a0, a1;
     const int F = blockIdx.y;
+    if (G.alone) {
+        if (F == 0)
+            adj_face_alone<T, 0>(A, FD, G, idx, a0, a1);
+        else if (F == 1)
+            adj_face_alone<T, 1>(A, FD, G, idx, a0, a1);
+        else
+            adj_face_alone<T, 2>(A, FD, G, idx, a0, a1);
+        G.aDr[(2 * F) * G.nr + lr] = (double)a0;
+        G.aDr[(2 * F + 1) * G.nr + lr] = (double)a1;
+        return;
+    }
+    long long l2;
+    if (first_region(A, idx, l2) != f) return;
     if (F == 0)
         adj_face_core<T, 0>(A, idx, A.lpsiH[0][1], A.lpsiH[0][2], A.lpsiHo[0][1], A.lpsiHo[0][2], a0, a1);
     else if (F == 1)

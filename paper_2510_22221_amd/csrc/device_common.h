@@ -17,6 +17,17 @@ __device__ __forceinline__ int fold(int i, int n, int per) {
     return (i < 0 || i >= n) ? -1 : i;
 }
 
+// position r of element l (x fastest) in a box of extents n.  Film boxes, film
+// reaches and loss regions hold fewer than 2^31 sites (their block tables and
+// launch grids are 32-bit), and a 64-bit division here costs some 150
+// instructions on the way to a thread's first load.
+__device__ __forceinline__ void box_split(unsigned l, const int *n, int *r) {
+    const unsigned q = l / (unsigned)n[0], z = q / (unsigned)n[1];
+    r[0] = (int)(l - q * (unsigned)n[0]);
+    r[1] = (int)(q - z * (unsigned)n[1]);
+    r[2] = (int)z;
+}
+
 // central difference over a spacing: a true division in float64 (the plain
 // definition), a multiply by the reciprocal in float32
 template <typename T>
@@ -56,6 +67,13 @@ __device__ __forceinline__ D scalar_desc(const D *tab, int f) {
 }
 
 __device__ __forceinline__ FilmDev film_desc(const FilmDev *films, int f) { return scalar_desc(films, f); }
+
+// the descriptor of a block's film (index f from its block-table entry): with
+// one film it does not wait for that entry
+template <typename D>
+__device__ __forceinline__ D block_desc(const D *tab, int nfilm, int f) {
+    return nfilm == 1 ? scalar_desc(tab, 0) : scalar_desc(tab, f);
+}
 
 __device__ __forceinline__ int4 block_entry(const int4 *tab, int b) {
     const cword_t *src = (const cword_t *)(tab + b);

@@ -79,91 +79,135 @@ __device__ __forceinline__ void llg_site(double kf, const double *H0, double ms,
     for (int w = 0; w < 3; w++) Mn[w] = ms * X[w] / nx;
 }
 
+// B^ (Q) and B^* (P) of family-c face r (position in film F's face box): the
+// face's own in component c, the mean of the four nearest faces of family c'
+// in each other (indices {-1, 0} along c and {0, 1} along c'), from the
+// prepass arrays over the grown face box.  Every load is issued, a neighbour
+// outside the grown box at its element 0 with the value dropped (only
+// non-magnetic faces have any): a magnetic face waits for one round trip.
+__device__ __forceinline__ void film_gather(const int *n, const int *per, const FilmDev &F, int c, const int *r,
+                                            const double *Bn, const double *Bs, double *P, double *Q, int &le) {
+    // position in the grown box of the site and of its -1 and +1 neighbours
+    int o[3], lo[3], hi[3];
+    const int st[3] = {1, F.en[0], F.en[0] * F.en[1]};
+    bool okl[3], okh[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        const int i = F.b0[a] + r[a];
+        o[a] = (i - F.e0[a]) * st[a];
+        const int m = fold(i - 1, n[a], per[a]) - F.e0[a], q = fold(i + 1, n[a], per[a]) - F.e0[a];
+        okl[a] = m >= 0 && m < F.en[a];
+        okh[a] = q >= 0 && q < F.en[a];
+        lo[a] = m * st[a];
+        hi[a] = q * st[a];
+    }
+    le = o[0] + o[1] + o[2];
+    P[c] = Bs[c * F.nse + le];
+    Q[c] = Bn[c * F.nse + le];
+#pragma unroll
+    for (int w = 1; w < 3; w++) {
+        const int cp = c + w < 3 ? c + w : c + w - 3, ct = 3 - c - cp;
+        double vn[2][2], vs[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int v = 0; v < 2; v++) {
+                const bool ok = (u || okl[c]) && (!v || okh[cp]);
+                const int q = (u ? o[c] : lo[c]) + (v ? hi[cp] : o[cp]) + o[ct];
+                const double xn = Bn[cp * F.nse + (ok ? q : 0)], xs = Bs[cp * F.nse + (ok ? q : 0)];
+                vn[u][v] = ok ? xn : 0.0;
+                vs[u][v] = ok ? xs : 0.0;
+            }
+        Q[cp] = ((vn[0][0] + vn[1][0]) + (vn[0][1] + vn[1][1])) * 0.25;
+        P[cp] = ((vs[0][0] + vs[1][0]) + (vs[0][1] + vs[1][1])) * 0.25;
+    }
+}
+
+// keeps a value from being computed only behind the branch that uses it (the
+// compiler moves loads there, one round trip later)
+__device__ __forceinline__ void hold(double &v) { asm volatile("" : "+v"(v)); }
+
+// one half step of a block of 256 magnetic faces.  Latency-bound (a film of
+// 10^3..10^5 faces is a few waves per CU): the chain is table entry and
+// descriptor, one round trip for all of a face's loads, the float64 solve, the
+// stores.  32-bit indices, the loads ahead of the magnetic test and the block
+// sum in one barrier took the 64 x 12 x 4 film of a 128 x 64 x 64 grid from
+// 7.0 to 4.2 us, a 400 x 60 x 4 film from 11.3 to 9.0 us; eight 200 x 40 x 4
+// films stay at 30.5 us (bandwidth: 24 float64 loads a face, from cache)
 // tid: the thread's index in its block of 256 (film blocks also run in
 // launches whose blocks are 64 x 4)
+template <typename T, int C>
+__device__ __forceinline__ double film_face(const KParams<T> &p, const FilmDev &F, int phase, unsigned l) {
+    int r[3];
+    box_split(l, F.bn, r);
+    const double ms = F.prm[(C * 3 + 0) * F.ns + l];
+    const double al = F.prm[(C * 3 + 1) * F.ns + l];
+    const double ga = F.prm[(C * 3 + 2) * F.ns + l];
+    const double *Msrc = (phase == 1) ? F.M : F.M1;
+    double P[3], Q[3], M[3];
+#pragma unroll
+    for (int w = 0; w < 3; w++) M[w] = Msrc[(C * 3 + w) * F.ns + l];
+    int le;
+    film_gather(p.n, p.per, F, C, r, phase == 1 ? F.Bn : F.Bn2, phase == 1 ? F.Bs : F.Bs2, P, Q, le);
+    // the curl term the prepass left for the face's phase-2 values
+    double cu = 0.0;
+    if (phase == 1 && F.Bn2) cu = F.Bs2[C * F.nse + le];
+#pragma unroll
+    for (int w = 0; w < 3; w++) {
+        hold(M[w]);
+        hold(P[w]);
+        hold(Q[w]);
+    }
+    hold(cu);
+    if (!(ms > 0.0)) return 0.0;
+    const double bs = P[C];
+    double Mn[3];
+    llg_site(p.kf, p.H0, ms, al, ga, P, Q, M, Mn);
+    const double hnew = bs - Mn[C];
+    if (phase == 1) {
+#pragma unroll
+        for (int w = 0; w < 3; w++) F.M1[(C * 3 + w) * F.ns + l] = Mn[w];
+        F.H1[C * F.ns + l] = hnew;
+        if (F.Bn2) {
+            // the phase-2 prepass of this face: B^ = H1 + M1_c, B^* =
+            // B^ - dt/(2 mu0) curl E with the same E
+            const double b2 = hnew + Mn[C];
+            F.Bn2[C * F.nse + le] = b2;
+            F.Bs2[C * F.nse + le] = b2 - cu;
+        }
+    } else {
+#pragma unroll
+        for (int w = 0; w < 3; w++) F.M[(C * 3 + w) * F.ns + l] = Mn[w];
+        p.Hw[C][p.slot(F.b0[0] + r[0], F.b0[1] + r[1], F.b0[2] + r[2])] = (T)hnew;
+    }
+    return Mn[C];
+}
+
 template <typename T>
 __device__ __forceinline__ void film_body(const KParams<T> &p, int phase, int inc_step, int blk, int tid) {
     __shared__ double red[256];
     if (inc_step && blk == 0 && tid == 0) p.step[0] = p.step[0] + 1;
     const int4 bt = block_entry(p.blocktab, blk); // film, family, first local index
-    const int f = bt.x, c = bt.y;
-    const FilmDev F = film_desc(p.films, f);
-    const long long l = (long long)bt.z + tid;
+    const FilmDev F = block_desc(p.films, p.nfilm, bt.x);
+    const unsigned l = (unsigned)bt.z + (unsigned)tid;
     double own = 0.0;
-    if (l < F.ns) {
-        int idx[3];
-        idx[0] = F.b0[0] + (int)(l % F.bn[0]);
-        idx[1] = F.b0[1] + (int)((l / F.bn[0]) % F.bn[1]);
-        idx[2] = F.b0[2] + (int)(l / ((long long)F.bn[0] * F.bn[1]));
-        const double ms = F.prm[(c * 3 + 0) * F.ns + l];
-        const double al = F.prm[(c * 3 + 1) * F.ns + l];
-        const double ga = F.prm[(c * 3 + 2) * F.ns + l];
-        if (ms > 0.0) {
-            // index in the grown face box (every face the solve reads lies in it)
-            // (-1 outside it: cannot happen for accepted film placements)
-            auto ext = [&](const int *q) -> long long {
-                const int r0 = q[0] - F.e0[0], r1 = q[1] - F.e0[1], r2 = q[2] - F.e0[2];
-                if (r0 < 0 || r0 >= F.en[0] || r1 < 0 || r1 >= F.en[1] || r2 < 0 || r2 >= F.en[2]) return -1;
-                return (long long)r0 + (long long)F.en[0] * ((long long)r1 + (long long)F.en[1] * r2);
-            };
-            const long long le = ext(idx);
-            const double *Bn = phase == 1 ? F.Bn : F.Bn2, *Bs = phase == 1 ? F.Bs : F.Bs2;
-            const double bn = le >= 0 ? Bn[c * F.nse + le] : 0.0, bs = le >= 0 ? Bs[c * F.nse + le] : 0.0;
-            double P[3], Q[3], M[3];
-            P[c] = bs;
-            Q[c] = bn;
-            for (int cp = 0; cp < 3; cp++) {
-                if (cp == c) continue;
-                // I_{c'}: mean of the four nearest family-c' faces, indices
-                // {idx_c - 1, idx_c} along c and {idx_c', idx_c' + 1} along c'
-                double vn[2][2], vs[2][2];
-                for (int u = 0; u < 2; u++)
-                    for (int v = 0; v < 2; v++) {
-                        int q[3] = {idx[0], idx[1], idx[2]};
-                        q[c] += u - 1;
-                        q[cp] += v;
-                        for (int a = 0; a < 3; a++) q[a] = fold(q[a], p.n[a], p.per[a]);
-                        const long long lq = ext(q);
-                        vn[u][v] = lq >= 0 ? Bn[cp * F.nse + lq] : 0.0;
-                        vs[u][v] = lq >= 0 ? Bs[cp * F.nse + lq] : 0.0;
-                    }
-                Q[cp] = ((vn[0][0] + vn[1][0]) + (vn[0][1] + vn[1][1])) * 0.25;
-                P[cp] = ((vs[0][0] + vs[1][0]) + (vs[0][1] + vs[1][1])) * 0.25;
-            }
-            const double *Msrc = (phase == 1) ? F.M : F.M1;
-            for (int w = 0; w < 3; w++) M[w] = Msrc[(c * 3 + w) * F.ns + l];
-            double Mn[3];
-            llg_site(p.kf, p.H0, ms, al, ga, P, Q, M, Mn);
-            const double hnew = bs - Mn[c];
-            if (phase == 1) {
-                for (int w = 0; w < 3; w++) F.M1[(c * 3 + w) * F.ns + l] = Mn[w];
-                F.H1[c * F.ns + l] = hnew;
-                if (F.Bn2 && le >= 0) {
-                    // the phase-2 prepass of this face: B^ = H1 + M1_c, B^* =
-                    // B^ - dt/(2 mu0) curl E with the same E (the prepass
-                    // left that term in this face's B^* slot)
-                    const double cu = F.Bs2[c * F.nse + le];
-                    const double b2 = hnew + Mn[c];
-                    F.Bn2[c * F.nse + le] = b2;
-                    F.Bs2[c * F.nse + le] = b2 - cu;
-                }
-            } else {
-                for (int w = 0; w < 3; w++) F.M[(c * 3 + w) * F.ns + l] = Mn[w];
-                p.Hw[c][p.slot(idx[0], idx[1], idx[2])] = (T)hnew;
-            }
-            own = Mn[c];
-        }
-    }
+    if (l < (unsigned)F.ns)
+        own = bt.y == 0   ? film_face<T, 0>(p, F, phase, l)
+              : bt.y == 1 ? film_face<T, 1>(p, F, phase, l)
+                          : film_face<T, 2>(p, F, phase, l);
     // block partial of the own component (mean-M probes, which read it
-    // between the two half steps: the second half step's would go unread)
+    // between the two half steps: the second half step's would go unread): a
+    // halving tree, its first two levels over LDS, the rest in one wavefront
     if (phase != 1) return;
     red[tid] = own;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
-        __syncthreads();
+    if (tid >= 64) return;
+    double s = (red[tid] + red[tid + 128]) + (red[tid + 64] + red[tid + 192]);
+    for (int st = 32; st > 0; st >>= 1) {
+        const double o = __shfl_down(s, st, 64);
+        if (tid < st) s = s + o;
     }
-    if (tid == 0) p.partial[blk] = red[0];
+    if (tid == 0) p.partial[blk] = s;
 }
 
 // copy the scratch of a single (bracket) half step into the state: the block
@@ -171,17 +215,22 @@ __device__ __forceinline__ void film_body(const KParams<T> &p, int phase, int in
 template <typename T>
 __device__ __forceinline__ void film_commit_body(const KParams<T> &p, int blk, int tid) {
     const int4 bt = block_entry(p.blocktab, blk);
-    const int f = bt.x, c = bt.y;
-    const FilmDev F = film_desc(p.films, f);
-    const long long l = (long long)bt.z + tid;
-    if (l >= F.ns) return;
-    int idx[3];
-    idx[0] = F.b0[0] + (int)(l % F.bn[0]);
-    idx[1] = F.b0[1] + (int)((l / F.bn[0]) % F.bn[1]);
-    idx[2] = F.b0[2] + (int)(l / ((long long)F.bn[0] * F.bn[1]));
-    if (!(F.prm[(c * 3) * F.ns + l] > 0.0)) return;
-    for (int w = 0; w < 3; w++) F.M[(c * 3 + w) * F.ns + l] = F.M1[(c * 3 + w) * F.ns + l];
-    p.Hw[c][p.slot(idx[0], idx[1], idx[2])] = (T)F.H1[c * F.ns + l];
+    const int c = bt.y;
+    const FilmDev F = block_desc(p.films, p.nfilm, bt.x);
+    const unsigned l = (unsigned)bt.z + (unsigned)tid;
+    if (l >= (unsigned)F.ns) return;
+    int r[3];
+    box_split(l, F.bn, r);
+    const double ms = F.prm[(c * 3) * F.ns + l];
+    double m[3], h = F.H1[c * F.ns + l];
+    for (int w = 0; w < 3; w++) {
+        m[w] = F.M1[(c * 3 + w) * F.ns + l];
+        hold(m[w]);
+    }
+    hold(h);
+    if (!(ms > 0.0)) return;
+    for (int w = 0; w < 3; w++) F.M[(c * 3 + w) * F.ns + l] = m[w];
+    p.Hw[c][p.slot(F.b0[0] + r[0], F.b0[1] + r[1], F.b0[2] + r[2])] = (T)h;
 }
 
 } // namespace mpx

@@ -1723,6 +1723,24 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
                 if (s->nlo[a] > 0 && g.r0[a] < s->nlo[a]) merge = false;
                 if (s->nhi[a] > 0 && g.r0[a] + g.rn[a] > s->n[a] - s->nhi[a]) merge = false;
             }
+        // a film whose reach meets no slab and no other film's reach (as index
+        // ranges on every axis; a reach on a whole periodic axis meets every
+        // other there)
+        for (size_t f = 0; f < h.af.size(); f++) {
+            AdjFilmDev &g = h.af[f];
+            bool alone = true;
+            for (int a = 0; a < 3; a++)
+                if ((s->nlo[a] > 0 && g.r0[a] < s->nlo[a]) ||
+                    (s->nhi[a] > 0 && g.r0[a] + g.rn[a] > s->n[a] - s->nhi[a]))
+                    alone = false;
+            for (size_t o = 0; o < h.af.size(); o++) {
+                bool meet = o != f;
+                for (int a = 0; a < 3; a++)
+                    if (g.r0[a] >= h.af[o].r0[a] + h.af[o].rn[a] || h.af[o].r0[a] >= g.r0[a] + g.rn[a]) meet = false;
+                if (meet) alone = false;
+            }
+            g.alone = alone ? 1 : 0;
+        }
         if (!h.af.empty()) {
             CK(hipMemcpy(h.d_af, h.af.data(), h.af.size() * sizeof(AdjFilmDev), hipMemcpyHostToDevice));
             // lambda M ping-pong: the first map of a step reads lM and writes

@@ -187,6 +187,7 @@ struct AdjFilmDev {
     double *aDr;
     long long nr;
     int r0[3], rn[3];
+    int alone, pad; // no other film's reach and no CPML slab meets this one's
 };
 
 template <typename T>
