@@ -63,7 +63,7 @@ def kernel_source_hash():
     import re
 
     h = hashlib.sha256()
-    for f in ("passes.hip", "stencil.h", "film.h", "device_common.h", "mpx_internal.h"):
+    for f in ("passes.hip", "rows.h", "stencil.h", "film.h", "device_common.h", "mpx_internal.h"):
         with open(os.path.join(ROOT, "paper_2510_22221_amd", "csrc", f)) as fh:
             src = fh.read()
         src = re.sub(r"/\*.*?\*/", "", src, flags=re.S)

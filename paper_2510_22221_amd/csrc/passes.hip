@@ -7,36 +7,19 @@
 // follows eq. iterate_H, and eq. iterate_H with M = 0 for non-magnetic faces
 // (the magnetic ones are the film kernels' work).
 //
-// Memory access: in blocks that touch no boundary every load is a raw buffer
-// load (a scalar resource per array whose base is the block's lowest plane,
-// a 32-bit byte offset per lane, and the neighbour plane as a scalar offset),
-// so the address work per load is one or two integer operations; blocks at a
-// boundary use folded, zero-filled loads.  Per-tile CPML / source / film
-// flags come from a host table (one per tile shape); edge coefficients come
-// from the packed row of the slot's class (its six values in one or two
-// 16-byte loads; no per-block staging).
+// Memory access: a wavefront is 64 slots of one row (rows.h), so every array
+// is read at a uniform plane base and a 32-bit lane offset; rows, slabs and
+// their coefficients are scalar.  One path serves interior and boundary.
+// Per-tile source / film flags come from a host table (one per tile shape);
+// edge coefficients come from the packed row of the slot's class (its six
+// values in one or two 16-byte loads; no per-block staging).
 #include "film.h"
+#include "rows.h"
 #include "stencil.h"
 
 namespace mpx {
 
 constexpr int PTX = kPassTX, PTY = kPassTY;
-constexpr int kRsrcWord3 = 0x00020000; // raw buffer resource, gfx9 family
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, long long bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, kRsrcWord3);
-}
-
-// AUX: the load's cache-policy bits (2: non-temporal)
-template <typename T, int AUX = 0>
-__device__ __forceinline__ T bld(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-    if constexpr (sizeof(T) == 8)
-        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, AUX));
-    else
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, AUX));
-}
-
-constexpr int kOOB = 0x7ffffff0; // a byte offset past every resource: the load returns 0
 
 // ---------------------------------------------------------------------------
 // E pass: E_c <- ca E_c + cb ((curl H)_c - J_c) on the three edges of slot
@@ -51,16 +34,19 @@ constexpr int kOOB = 0x7ffffff0; // a byte offset past every resource: the load 
 // list (class byte 255, or 16-bit class 0xffff) is skipped and updated
 // afterwards by the mixed-slot kernel from the same old values.
 // ---------------------------------------------------------------------------
-// whether this wave takes the CPML path: a wide tile that reaches CPML slabs
-// only along x (flag 1 without 8) needs it only in the waves whose 64 slots,
-// with the one-slot halo, reach an x slab (the same test as the tile's, on
-// the wave's range; uniform over the wave, so the other waves skip it)
-template <typename T, int TX>
-__device__ __forceinline__ bool wave_pml(const KParams<T> &p, int bx, int f) {
-    if (!(f & 1)) return false;
-    if (TX != kWideTX || (f & 8)) return true;
-    const int w0 = bx * TX + (__builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63);
-    return (p.nlo[0] > 0 && w0 - 1 < p.nlo[0]) || (p.nhi[0] > 0 && w0 + 64 >= p.n[0] - p.nhi[0]);
+// the current of the sources on the edge of component C at (i, j, k)
+template <typename T>
+__device__ __forceinline__ T src_current(const KParams<T> &p, int C, int i, int j, int k, long long step) {
+    double J = 0.0;
+    for (int s = 0; s < p.nsrc; s++) {
+        const SrcDev &S = p.srcs[s]; // device copy: no dynamic index into the kernel argument
+        if (S.comp != C) continue;
+        if (i < S.box[0] || i >= S.box[0] + S.box[3] || j < S.box[1] || j >= S.box[1] + S.box[4] || k < S.box[2] ||
+            k >= S.box[2] + S.box[5])
+            continue;
+        if (step < S.n) J += S.table[step];
+    }
+    return T(J);
 }
 
 // CLS: the slot class read, 0 the class byte, 1 the 16-bit class (a grid
@@ -68,116 +54,94 @@ __device__ __forceinline__ bool wave_pml(const KParams<T> &p, int bx, int f) {
 // launch differ; the test is uniform over a member's lanes).  f: the tile's
 // flag byte, first used after every field load has been issued (so that the
 // loads do not wait for it).
-template <typename T, int CLS, int TX>
-__device__ __forceinline__ void epass_tile(const KParams<T> &p, int i0, int j0, int k, int f, int bxt) {
-    const int i = i0 + (int)threadIdx.x, j = j0 + (int)threadIdx.y;
-    const bool inside = i < p.n[0] && j < p.n[1];
-    const int ic = min(i, p.n[0] - 1), jc = min(j, p.n[1] - 1);
+template <typename T, int CLS>
+__device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, int f) {
+    if (r.j >= p.n[1]) return; // a partial tile's row (uniform)
+    const unsigned es = (unsigned)sizeof(T);
+    const int ic = min(r.i, p.n[0] - 1), j = r.j, k = r.k;
     const long long sz = (long long)p.px * p.n[1];
-    const long long pb = sz * (long long)sizeof(T);
-    const int es = (int)sizeof(T), rowb = p.px * es;
-    const int o = ic + p.px * jc, vo = o * es;
-    const int vxm = ic > 0 ? vo - es : (p.per[0] ? vo + (p.n[0] - 1) * es : vo);
-    const int vym = jc > 0 ? vo - rowb : (p.per[1] ? vo + (p.n[1] - 1) * rowb : vo);
+    const unsigned io = (unsigned)ic * es, rowb = (unsigned)p.px * es, vo = io + (unsigned)j * rowb;
+    // the -1 neighbours: wrapped on a periodic axis, any in-range value at a wall
+    const unsigned vxm = ic > 0 ? vo - es : (p.per[0] ? vo + (unsigned)(p.n[0] - 1) * es : vo);
+    const unsigned jm = (unsigned)(j > 0 ? j - 1 : (p.per[1] ? p.n[1] - 1 : j)), vym = io + jm * rowb;
     const int kb = k > 0 ? k - 1 : (p.per[2] ? p.n[2] - 1 : k);
-    const auto rx = make_rsrc(p.H[0] + k * sz, pb), ry = make_rsrc(p.H[1] + k * sz, pb),
-               rz = make_rsrc(p.H[2] + k * sz, pb);
-    const auto bx = make_rsrc(p.H[0] + kb * sz, pb), by = make_rsrc(p.H[1] + kb * sz, pb);
-    // the -z plane's H is read here for the last time (the tiles of its own
-    // plane and of the next row read it before): non-temporal
-    const T hx0 = bld<T>(rx, vo, 0), hx_km = bld<T, 2>(bx, vo, 0), hx_ym = bld<T>(rx, vym, 0);
-    const T hy0 = bld<T>(ry, vo, 0), hy_km = bld<T, 2>(by, vo, 0), hy_xm = bld<T>(ry, vxm, 0);
-    const T hz0 = bld<T>(rz, vo, 0), hz_xm = bld<T>(rz, vxm, 0), hz_ym = bld<T>(rz, vym, 0);
-    // E, the class and the new E are touched once per pass: non-temporal, so
-    // that they leave L2 first and the H rows and planes the neighbouring
-    // tiles read again, and the coefficient rows, stay
-    T *ex = p.E[0] + k * sz, *ey = p.E[1] + k * sz, *ez = p.E[2] + k * sz;
-    const T e0 = __builtin_nontemporal_load(ex + o), e1 = __builtin_nontemporal_load(ey + o),
-            e2 = __builtin_nontemporal_load(ez + o);
-    // the coefficient triple's row: the class byte (255: the slot is on the
-    // mixed list), or with extended triples the 16-bit class (0xffff: on the
-    // mixed list), whose rows past 255 are the extended table's
+    const long long zo = k * sz, zb = kb * sz;
+    // the class first: its coefficient row is the one load that waits for another
     bool c16 = CLS == 1;
     if constexpr (CLS == 2) c16 = p.cls16 != nullptr;
     int c0;
     if constexpr (CLS == 0)
-        c0 = __builtin_nontemporal_load(p.cls + k * sz + o);
+        c0 = row_ld<true>(p.cls + zo, (unsigned)ic + (unsigned)j * (unsigned)p.px);
     else if constexpr (CLS == 1)
-        c0 = __builtin_nontemporal_load(p.cls16 + k * sz + o);
+        c0 = row_ld<true>(p.cls16 + zo, 2u * ((unsigned)ic + (unsigned)j * (unsigned)p.px));
     else if (c16)
-        c0 = (p.cls16 + k * sz)[o];
+        c0 = row_ld(p.cls16 + zo, 2u * ((unsigned)ic + (unsigned)j * (unsigned)p.px));
     else
-        c0 = (p.cls + k * sz)[o];
+        c0 = row_ld(p.cls + zo, (unsigned)ic + (unsigned)j * (unsigned)p.px);
+    const T *Hx = p.H[0] + zo, *Hy = p.H[1] + zo, *Hz = p.H[2] + zo;
+    // the -z plane's H is read here for the last time (the tiles of its own
+    // plane and of the next row read it before): non-temporal
+    const T hx0 = row_ld(Hx, vo), hx_km = row_ld<true>(p.H[0] + zb, vo), hx_ym = row_ld(Hx, vym);
+    const T hy0 = row_ld(Hy, vo), hy_km = row_ld<true>(p.H[1] + zb, vo), hy_xm = row_ld(Hy, vxm);
+    const T hz0 = row_ld(Hz, vo), hz_xm = row_ld(Hz, vxm), hz_ym = row_ld(Hz, vym);
+    // E, the class and the new E are touched once per pass: non-temporal, so
+    // that they leave L2 first and the H rows and planes the neighbouring
+    // tiles read again, and the coefficient rows, stay
+    T *Ex = p.E[0] + zo, *Ey = p.E[1] + zo, *Ez = p.E[2] + zo;
+    const T e0 = row_ld<true>(Ex, vo), e1 = row_ld<true>(Ey, vo), e2 = row_ld<true>(Ez, vo);
+    RowPml<T> m = row_pml<T, true>(p, r, io);
+    // the slot's six coefficients in one or two wide loads (a slot on the
+    // mixed list, class byte 255 or 16-bit class 0xffff, reads row 0 and uses
+    // none)
     const int kSkip = c16 ? 0xffff : kMixed;
-    // the slot's six coefficients in one or two wide loads (a skipped slot
-    // reads row 0 and uses none)
     const CoefRow<T> L = coef_row<T>(p.coefv, c0 == kSkip ? 0 : c0);
-    const bool tpml = wave_pml<T, TX>(p, bxt, f), tsrc = (f & 2) != 0;
-    const long long step = tsrc ? p.step[0] : 0;
     const T dx = p.dT[0], dy = p.dT[1], dz = p.dT[2], ix = p.invd[0], iy = p.invd[1], iz = p.invd[2];
-    int q0[3], q1[3], q2[3];
-    const bool v0 = inside && e_site<T, 0, true>(p, i, j, k, q0), v1 = inside && e_site<T, 1, true>(p, i, j, k, q1),
-               v2 = inside && e_site<T, 2, true>(p, i, j, k, q2);
-    if constexpr (sizeof(T) == 8) {
-        // float64: the CPML state of one edge at a time (each thread alone
-        // reads and writes its edges' psi and E), which keeps the kernel's
-        // registers, and with them its occupancy, near the bulk path's
-        if (!inside || c0 == kSkip) return;
-        T n0 = T(0), n1 = T(0), n2 = T(0);
-        {
-            Psi2<T> r;
-            if (tpml && v0) r = psi_load<T, 0, true>(p, q0);
-            if (v0)
-                n0 = e_apply<T, 0, CoefRow<T>, false>(p, L, q0, c0, e0, dif(hz0, hz_ym, dy, iy), dif(hy0, hy_km, dz, iz),
-                                                     r, tsrc, step);
-            if (tpml) psi_store<T, 0>(p.psiE[0], r);
-        }
-        {
-            Psi2<T> r;
-            if (tpml && v1) r = psi_load<T, 1, true>(p, q1);
-            if (v1)
-                n1 = e_apply<T, 1, CoefRow<T>, false>(p, L, q1, c0, e1, dif(hx0, hx_km, dz, iz), dif(hz0, hz_xm, dx, ix),
-                                                     r, tsrc, step);
-            if (tpml) psi_store<T, 1>(p.psiE[1], r);
-        }
-        {
-            Psi2<T> r;
-            if (tpml && v2) r = psi_load<T, 2, true>(p, q2);
-            if (v2)
-                n2 = e_apply<T, 2, CoefRow<T>, false>(p, L, q2, c0, e2, dif(hy0, hy_xm, dx, ix), dif(hx0, hx_ym, dy, iy),
-                                                     r, tsrc, step);
-            if (tpml) psi_store<T, 2>(p.psiE[2], r);
-        }
-        __builtin_nontemporal_store(n0, ex + o);
-        __builtin_nontemporal_store(n1, ey + o);
-        __builtin_nontemporal_store(n2, ez + o);
-        return;
+    // E_x: along y then z; E_y: z, x; E_z: x, y
+    T ay = dif(hz0, hz_ym, dy, iy), az = dif(hy0, hy_km, dz, iz);
+    T bz = dif(hx0, hx_km, dz, iz), bx = dif(hz0, hz_xm, dx, ix);
+    T cx = dif(hy0, hy_xm, dx, ix), cy = dif(hx0, hx_ym, dy, iy);
+    // an edge on a lower wall (an axis other than its own) or on a conductor
+    // (cb = 0) stays zero and keeps its psi
+    const bool ox = r.i > 0 || p.per[0], oy = j > 0 || p.per[1], oz = k > 0 || p.per[2];
+    const bool u0 = oy && oz && L.cb[0] != T(0), u1 = ox && oz && L.cb[1] != T(0), u2 = ox && oy && L.cb[2] != T(0);
+    if (m.wx) {
+        pml_step_if(m.sx, m.xy, m.bx, m.cx, bx);
+        pml_step_if(m.sx, m.xz, m.bx, m.cx, cx);
     }
-    // float32: every load of the thread before any store (the CPML state of
-    // the three edges too)
-    Psi2<T> r0, r1, r2;
-    if (tpml) {
-        if (v0) r0 = psi_load<T, 0, true>(p, q0);
-        if (v1) r1 = psi_load<T, 1, true>(p, q1);
-        if (v2) r2 = psi_load<T, 2, true>(p, q2);
+    if (m.wy) {
+        pml_step(m.yx, m.by, m.cy, ay);
+        pml_step(m.yz, m.by, m.cy, cy);
     }
-    if (!inside || c0 == kSkip) return;
-    const T n0 = v0 ? e_apply<T, 0, CoefRow<T>, false>(p, L, q0, c0, e0, dif(hz0, hz_ym, dy, iy),
-                                                       dif(hy0, hy_km, dz, iz), r0, tsrc, step)
-                    : T(0);
-    const T n1 = v1 ? e_apply<T, 1, CoefRow<T>, false>(p, L, q1, c0, e1, dif(hx0, hx_km, dz, iz),
-                                                       dif(hz0, hz_xm, dx, ix), r1, tsrc, step)
-                    : T(0);
-    const T n2 = v2 ? e_apply<T, 2, CoefRow<T>, false>(p, L, q2, c0, e2, dif(hy0, hy_xm, dx, ix),
-                                                       dif(hx0, hx_ym, dy, iy), r2, tsrc, step)
-                    : T(0);
-    __builtin_nontemporal_store(n0, ex + o);
-    __builtin_nontemporal_store(n1, ey + o);
-    __builtin_nontemporal_store(n2, ez + o);
-    if (tpml) {
-        psi_store<T, 0>(p.psiE[0], r0);
-        psi_store<T, 1>(p.psiE[1], r1);
-        psi_store<T, 2>(p.psiE[2], r2);
+    if (m.wz) {
+        pml_step(m.zx, m.bz, m.cz, az);
+        pml_step(m.zy, m.bz, m.cz, bz);
+    }
+    T x0 = ay - az, x1 = bz - bx, x2 = cx - cy;
+    if (f & 2) {
+        const long long step = p.step[0];
+        // (x - 0) is x bitwise, so subtracting only here matches the plain form
+        x0 = x0 - src_current(p, 0, r.i, j, k, step);
+        x1 = x1 - src_current(p, 1, r.i, j, k, step);
+        x2 = x2 - src_current(p, 2, r.i, j, k, step);
+    }
+    if (!r.in || c0 == kSkip) return;
+    row_st<true>(Ex, vo, u0 ? L.ca[0] * e0 + L.cb[0] * x0 : T(0));
+    row_st<true>(Ey, vo, u1 ? L.ca[1] * e1 + L.cb[1] * x1 : T(0));
+    row_st<true>(Ez, vo, u2 ? L.ca[2] * e2 + L.cb[2] * x2 : T(0));
+    if (m.wx && m.sx) {
+        const long long q = row_psi(p, 0, j, k);
+        if (u1) row_st(p.psiE[1][0] + q, m.ox, m.xy);
+        if (u2) row_st(p.psiE[2][0] + q, m.ox, m.xz);
+    }
+    if (m.wy) {
+        const long long q = row_psi(p, 1, j, k);
+        if (u0) row_st<true>(p.psiE[0][1] + q, io, m.yx);
+        if (u2) row_st<true>(p.psiE[2][1] + q, io, m.yz);
+    }
+    if (m.wz) {
+        const long long q = row_psi(p, 2, j, k);
+        if (u0) row_st<true>(p.psiE[0][2] + q, io, m.zx);
+        if (u1) row_st<true>(p.psiE[1][2] + q, io, m.zy);
     }
 }
 
@@ -198,7 +162,7 @@ __device__ __forceinline__ int tile_flag(const KParams<T> &p, int bx, int by, in
 // that tile shape
 template <typename T, int CLS, int TX = PTX, int TY = PTY>
 __device__ __forceinline__ void epass_block(const KParams<T> &p, int bx, int by, int k) {
-    epass_tile<T, CLS, TX>(p, bx * TX, by * TY, k, tile_flag<T, TX, TY>(p, bx, by, k), bx);
+    epass_row<T, CLS>(p, row_pos<TX>(p.n, bx, by, TY, k), tile_flag<T, TX, TY>(p, bx, by, k));
 }
 
 // the mixed slots, one thread each: the general path (folded loads; edge
@@ -241,100 +205,99 @@ __device__ __forceinline__ void emixed_slot(const KParams<T> &p, int m) {
 // on a periodic axis and reads zero at a wall (the E there is tangential to
 // it); lanes past the domain store nothing.
 // ---------------------------------------------------------------------------
-template <typename T, int NHALF, int TX>
-__device__ __forceinline__ void hpass_tile(const KParams<T> &p, int i0, int j0, int k, int f, int bxt) {
-    const int i = i0 + (int)threadIdx.x, j = j0 + (int)threadIdx.y;
-    const bool inside = i < p.n[0] && j < p.n[1];
-    const int ic = min(i, p.n[0] - 1), jc = min(j, p.n[1] - 1);
+template <typename T, int NHALF>
+__device__ __forceinline__ void hpass_row(const KParams<T> &p, const RowPos &r, int f) {
+    if (r.j >= p.n[1]) return; // a partial tile's row (uniform)
+    const unsigned es = (unsigned)sizeof(T);
+    const int ic = min(r.i, p.n[0] - 1), j = r.j, k = r.k;
     const long long sz = (long long)p.px * p.n[1];
-    const long long pb = sz * (long long)sizeof(T);
-    const int es = (int)sizeof(T), rowb = p.px * es;
-    const int o = ic + p.px * jc, vo = o * es;
-    const int vxp = ic + 1 < p.n[0] ? vo + es : (p.per[0] ? vo - (p.n[0] - 1) * es : kOOB);
-    const int vyp = jc + 1 < p.n[1] ? vo + rowb : (p.per[1] ? vo - (p.n[1] - 1) * rowb : kOOB);
-    const int ka = k + 1 < p.n[2] ? k + 1 : (p.per[2] ? 0 : -1);
-    const auto rx = make_rsrc(p.E[0] + k * sz, pb), ry = make_rsrc(p.E[1] + k * sz, pb),
-               rz = make_rsrc(p.E[2] + k * sz, pb);
-    // the plane above; none (every load zero) above a wall
-    const auto ax = make_rsrc(p.E[0] + (ka < 0 ? 0 : ka) * sz, ka < 0 ? 0 : pb),
-               ay = make_rsrc(p.E[1] + (ka < 0 ? 0 : ka) * sz, ka < 0 ? 0 : pb);
-    const auto gx = make_rsrc(p.H[0] + k * sz, pb), gy = make_rsrc(p.H[1] + k * sz, pb),
-               gz = make_rsrc(p.H[2] + k * sz, pb);
-    const T ex0 = bld<T>(rx, vo, 0), ex_yp = bld<T>(rx, vyp, 0), ex_kp = bld<T>(ax, vo, 0);
-    const T ey0 = bld<T>(ry, vo, 0), ey_xp = bld<T>(ry, vxp, 0), ey_kp = bld<T>(ay, vo, 0);
-    const T ez0 = bld<T>(rz, vo, 0), ez_xp = bld<T>(rz, vxp, 0), ez_yp = bld<T>(rz, vyp, 0);
+    const unsigned io = (unsigned)ic * es, rowb = (unsigned)p.px * es, vo = io + (unsigned)j * rowb;
+    // the +1 neighbours: wrapped on a periodic axis; past a wall the own
+    // value is read and dropped
+    const bool wlx = !p.per[0] && ic + 1 >= p.n[0], wly = !p.per[1] && j + 1 >= p.n[1],
+               wlz = !p.per[2] && k + 1 >= p.n[2];
+    const unsigned vxp = ic + 1 < p.n[0] ? vo + es : (p.per[0] ? vo - (unsigned)(p.n[0] - 1) * es : vo);
+    const unsigned jp = (unsigned)(j + 1 < p.n[1] ? j + 1 : (p.per[1] ? 0 : j)), vyp = io + jp * rowb;
+    const int ka = k + 1 < p.n[2] ? k + 1 : (p.per[2] ? 0 : k);
+    const long long zo = k * sz, za = ka * sz;
+    const T *Ex = p.E[0] + zo, *Ey = p.E[1] + zo, *Ez = p.E[2] + zo;
+    T ex0 = row_ld(Ex, vo), ex_yp = row_ld(Ex, vyp), ex_kp = row_ld(p.E[0] + za, vo);
+    T ey0 = row_ld(Ey, vo), ey_xp = row_ld(Ey, vxp), ey_kp = row_ld(p.E[1] + za, vo);
+    T ez0 = row_ld(Ez, vo), ez_xp = row_ld(Ez, vxp), ez_yp = row_ld(Ez, vyp);
     // H and the new H are touched once per pass: non-temporal (the E halo
-    // stays in L2); the CPML state keeps the default policy (an x slab's rows
-    // share lines with the next row's block)
-    const T h0 = bld<T, 2>(gx, vo, 0), h1 = bld<T, 2>(gy, vo, 0), h2 = bld<T, 2>(gz, vo, 0);
+    // stays in L2)
+    T *Hx = p.H[0] + zo, *Hy = p.H[1] + zo, *Hz = p.H[2] + zo;
+    T h0 = row_ld<true>(Hx, vo), h1 = row_ld<true>(Hy, vo), h2 = row_ld<true>(Hz, vo);
+    RowPml<T> m = row_pml<T, false>(p, r, io);
     // the tile's flags, first used after every field load has been issued
-    const bool tpml = wave_pml<T, TX>(p, bxt, f), tfilm = (f & 4) != 0;
-    const T dx = p.dT[0], dy = p.dT[1], dz = p.dT[2], ix = p.invd[0], iy = p.invd[1], iz = p.invd[2];
-    const int idx[3] = {ic, jc, k};
-    Psi2<T> r0, r1, r2;
-    if constexpr (sizeof(T) == 4) {
-        if (tpml && inside) {
-            r0 = psi_load<T, 0, false>(p, idx);
-            r1 = psi_load<T, 1, false>(p, idx);
-            r2 = psi_load<T, 2, false>(p, idx);
-        }
-    }
     bool mag[3] = {false, false, false};
-    if (tfilm && inside) {
+    if ((f & 4) && r.in) {
+        const int idx[3] = {ic, j, k};
         mag[0] = face_is_magnetic(p, 0, idx);
         mag[1] = face_is_magnetic(p, 1, idx);
         mag[2] = face_is_magnetic(p, 2, idx);
     }
-    if (!inside) return;
-    if constexpr (sizeof(T) == 8) {
-        // float64: the CPML state of one face at a time (as in the E pass)
-        T *hx = p.H[0] + k * sz, *hy = p.H[1] + k * sz, *hz = p.H[2] + k * sz;
-        {
-            Psi2<T> r;
-            if (tpml) r = psi_load<T, 0, false>(p, idx);
-            const T n = h_apply<T, 0, NHALF>(p, h0, dif(ez_yp, ez0, dy, iy), dif(ey_kp, ey0, dz, iz), r);
-            if (!mag[0]) {
-                __builtin_nontemporal_store(n, hx + o);
-                if (tpml) psi_store<T, 0>(p.psiH[0], r);
+    ey_xp = wlx ? T(0) : ey_xp;
+    ez_xp = wlx ? T(0) : ez_xp;
+    if (wly) ex_yp = ez_yp = T(0);
+    if (wlz) ex_kp = ey_kp = T(0);
+    const T dx = p.dT[0], dy = p.dT[1], dz = p.dT[2], ix = p.invd[0], iy = p.invd[1], iz = p.invd[2];
+    const T ay = dif(ez_yp, ez0, dy, iy), az = dif(ey_kp, ey0, dz, iz);
+    const T bz = dif(ex_kp, ex0, dz, iz), bx = dif(ez_xp, ez0, dx, ix);
+    const T cx = dif(ey_xp, ey0, dx, ix), cy = dif(ex_yp, ex0, dy, iy);
+    if (m.wx || m.wy || m.wz) {
+#pragma unroll
+        for (int hs = 0; hs < NHALF; hs++) {
+            T a1 = ay, a2 = az, b1 = bz, b2 = bx, c1 = cx, c2 = cy;
+            if (m.wx) {
+                pml_step_if(m.sx, m.xy, m.bx, m.cx, b2);
+                pml_step_if(m.sx, m.xz, m.bx, m.cx, c1);
             }
-        }
-        {
-            Psi2<T> r;
-            if (tpml) r = psi_load<T, 1, false>(p, idx);
-            const T n = h_apply<T, 1, NHALF>(p, h1, dif(ex_kp, ex0, dz, iz), dif(ez_xp, ez0, dx, ix), r);
-            if (!mag[1]) {
-                __builtin_nontemporal_store(n, hy + o);
-                if (tpml) psi_store<T, 1>(p.psiH[1], r);
+            if (m.wy) {
+                pml_step(m.yx, m.by, m.cy, a1);
+                pml_step(m.yz, m.by, m.cy, c2);
             }
-        }
-        {
-            Psi2<T> r;
-            if (tpml) r = psi_load<T, 2, false>(p, idx);
-            const T n = h_apply<T, 2, NHALF>(p, h2, dif(ey_xp, ey0, dx, ix), dif(ex_yp, ex0, dy, iy), r);
-            if (!mag[2]) {
-                __builtin_nontemporal_store(n, hz + o);
-                if (tpml) psi_store<T, 2>(p.psiH[2], r);
+            if (m.wz) {
+                pml_step(m.zx, m.bz, m.cz, a2);
+                pml_step(m.zy, m.bz, m.cz, b1);
             }
+            h0 = h0 - p.hc * (a1 - a2);
+            h1 = h1 - p.hc * (b1 - b2);
+            h2 = h2 - p.hc * (c1 - c2);
         }
-        return;
+    } else {
+        const T g0 = p.hc * (ay - az), g1 = p.hc * (bz - bx), g2 = p.hc * (cx - cy);
+#pragma unroll
+        for (int hs = 0; hs < NHALF; hs++) {
+            h0 = h0 - g0;
+            h1 = h1 - g1;
+            h2 = h2 - g2;
+        }
     }
-    const T n0 = h_apply<T, 0, NHALF>(p, h0, dif(ez_yp, ez0, dy, iy), dif(ey_kp, ey0, dz, iz), r0);
-    const T n1 = h_apply<T, 1, NHALF>(p, h1, dif(ex_kp, ex0, dz, iz), dif(ez_xp, ez0, dx, ix), r1);
-    const T n2 = h_apply<T, 2, NHALF>(p, h2, dif(ey_xp, ey0, dx, ix), dif(ex_yp, ex0, dy, iy), r2);
-    T *hx = p.H[0] + k * sz, *hy = p.H[1] + k * sz, *hz = p.H[2] + k * sz;
-    if (!mag[0]) __builtin_nontemporal_store(n0, hx + o);
-    if (!mag[1]) __builtin_nontemporal_store(n1, hy + o);
-    if (!mag[2]) __builtin_nontemporal_store(n2, hz + o);
-    if (tpml) {
-        if (!mag[0]) psi_store<T, 0>(p.psiH[0], r0);
-        if (!mag[1]) psi_store<T, 1>(p.psiH[1], r1);
-        if (!mag[2]) psi_store<T, 2>(p.psiH[2], r2);
+    if (!r.in) return;
+    if (!mag[0]) row_st<true>(Hx, vo, h0);
+    if (!mag[1]) row_st<true>(Hy, vo, h1);
+    if (!mag[2]) row_st<true>(Hz, vo, h2);
+    if (m.wx && m.sx) {
+        const long long q = row_psi(p, 0, j, k);
+        if (!mag[1]) row_st(p.psiH[1][0] + q, m.ox, m.xy);
+        if (!mag[2]) row_st(p.psiH[2][0] + q, m.ox, m.xz);
+    }
+    if (m.wy) {
+        const long long q = row_psi(p, 1, j, k);
+        if (!mag[0]) row_st<true>(p.psiH[0][1] + q, io, m.yx);
+        if (!mag[2]) row_st<true>(p.psiH[2][1] + q, io, m.yz);
+    }
+    if (m.wz) {
+        const long long q = row_psi(p, 2, j, k);
+        if (!mag[0]) row_st<true>(p.psiH[0][2] + q, io, m.zx);
+        if (!mag[1]) row_st<true>(p.psiH[1][2] + q, io, m.zy);
     }
 }
 
 template <typename T, int NHALF, int TX = PTX, int TY = PTY>
 __device__ __forceinline__ void hpass_block(const KParams<T> &p, int bx, int by, int k) {
-    hpass_tile<T, NHALF, TX>(p, bx * TX, by * TY, k, tile_flag<T, TX, TY>(p, bx, by, k), bx);
+    hpass_row<T, NHALF>(p, row_pos<TX>(p.n, bx, by, TY, k), tile_flag<T, TX, TY>(p, bx, by, k));
 }
 
 // grid (x tiles, y tiles, planes) in natural order: the blocks resident at
@@ -343,14 +306,10 @@ __device__ __forceinline__ void hpass_block(const KParams<T> &p, int bx, int by,
 // slots, or on grids at least two wide tiles across, 256 x 1 (each block
 // then reads and writes 256 consecutive slots of every array: measured 5 %
 // (float32) and 9 % (float64) faster per step on a 512-wide grid, slower on
-// narrow ones).  In float32 the E pass is held to 72 VGPRs (7 waves per
-// SIMD): with the slot's packed coefficient row loaded at once it fits
-// without spilling, and it measured 4 % faster than the per-edge table loads
-// at 64 VGPRs (at 64 the row spills).  XC: the variant for grids with
-// extended-table slots (16-bit classes).
+// narrow ones).  XC: the variant for grids with extended-table slots (16-bit
+// classes).
 template <typename T, int TX, int TY, bool XC>
-__global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 7 : 1, 8)))
-k_epass(KParams<T> p) {
+__global__ void __launch_bounds__(TX *TY) k_epass(KParams<T> p) {
     epass_block<T, XC ? 1 : 0, TX, TY>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
