@@ -19,6 +19,7 @@
 // One thread per slot or per film face; every sum a thread forms is a gather
 // (no atomics), so results do not depend on scheduling.
 #include "film.h"
+#include "rows.h"
 
 namespace mpx {
 
@@ -971,7 +972,7 @@ struct EdgeCoef {
 };
 
 template <typename T>
-__device__ __noinline__ EdgeCoef<T> edge_coef_mixed(const uint8_t *id, const MatDev *mat, int n0, int n1, int n2,
+__device__ __forceinline__ EdgeCoef<T> edge_coef_mixed(const uint8_t *id, const MatDev *mat, int n0, int n1, int n2,
                                                      int per0, int per1, int per2, int px, double eps0, double dt,
                                                      int C, int i, int j, int k) {
     const int n[3] = {n0, n1, n2}, per[3] = {per0, per1, per2};
@@ -997,40 +998,52 @@ __device__ __noinline__ EdgeCoef<T> edge_coef_mixed(const uint8_t *id, const Mat
     return r;
 }
 
-// the E-step coefficients of the three edges of slot idx (q its slot): one
-// class read, then the three table entries together
+// the E-step coefficients of a slot's three edges: its class (the 16-bit one
+// on a grid with extended triples), then the class's packed row in one or two
+// wide loads (a PEC edge has ca = cb = 0, every other edge cb > 0)
+struct EdgeRow {
+    int c;
+    bool mixed; // on the mixed list: the general path from the cell ids
+};
+
 template <typename T>
-__device__ __forceinline__ void edge_coefs(const KParams<T> &p, const int *idx, long long q, T *ca, T *cb, bool *ok) {
-    const int cl = p.cls[q];
-    ca[0] = ca[1] = ca[2] = cb[0] = cb[1] = cb[2] = T(0);
-    ok[0] = ok[1] = ok[2] = false;
-    if (cl != kMixed) {
-        // the class's packed row (one or two wide loads; a PEC edge has
-        // ca = cb = 0, every other edge cb > 0)
-        const CoefRow<T> r = coef_row<T>(p.coefv, cl);
-#pragma unroll
-        for (int C = 0; C < 3; C++) {
-            ca[C] = r.ca[C];
-            cb[C] = r.cb[C];
-            ok[C] = r.cb[C] != T(0);
-        }
+__device__ __forceinline__ EdgeRow edge_class(const KParams<T> &p, int i, int j, int k, long long zo) {
+    const unsigned o = (unsigned)i + (unsigned)j * (unsigned)p.px;
+    EdgeRow e;
+    if (p.cls16) { // uniform
+        e.c = row_ld(p.cls16 + zo, 2u * o);
+        e.mixed = e.c == 0xffff;
+    } else {
+        e.c = row_ld(p.cls + zo, o);
+        e.mixed = e.c == kMixed;
     }
+    return e;
+}
+
+template <typename T>
+__device__ __forceinline__ void edge_row_coefs(const KParams<T> &p, const EdgeRow &e, int i, int j, int k, T *ca,
+                                               T *cb, bool *ok) {
+    const CoefRow<T> r = coef_row<T>(p.coefv, e.mixed ? 0 : e.c);
     // an edge on a lower wall (a non-periodic axis other than its own) is held
     // at zero; a mixed slot's edges read the four cells around them, which
     // exist off the walls only
+    const bool ox = i > 0 || p.per[0], oy = j > 0 || p.per[1], oz = k > 0 || p.per[2];
+    const bool off[3] = {oy && oz, ox && oz, ox && oy};
+#pragma unroll
     for (int C = 0; C < 3; C++) {
-        bool wall = false;
-        for (int a = 0; a < 3; a++)
-            if (a != C && !p.per[a] && idx[a] == 0) wall = true;
-        if (wall) {
-            ca[C] = cb[C] = T(0);
+        ca[C] = r.ca[C];
+        cb[C] = r.cb[C];
+        ok[C] = off[C] && r.cb[C] != T(0);
+    }
+    if (e.mixed) {
+        for (int C = 0; C < 3; C++) {
             ok[C] = false;
-        } else if (cl == kMixed) {
-            const EdgeCoef<T> r = edge_coef_mixed<T>(p.id, p.mat, p.n[0], p.n[1], p.n[2], p.per[0], p.per[1],
-                                                     p.per[2], p.px, p.eps0, p.dt, C, idx[0], idx[1], idx[2]);
-            ca[C] = r.ca;
-            cb[C] = r.cb;
-            ok[C] = r.ok;
+            if (!off[C]) continue;
+            const EdgeCoef<T> m = edge_coef_mixed<T>(p.id, p.mat, p.n[0], p.n[1], p.n[2], p.per[0], p.per[1],
+                                                     p.per[2], p.px, p.eps0, p.dt, C, i, j, k);
+            ca[C] = m.ca;
+            cb[C] = m.cb;
+            ok[C] = m.ok;
         }
     }
 }
@@ -1047,26 +1060,6 @@ __device__ __forceinline__ int first_region(const AdjParams<T> &A, const int *id
         }
     }
     return -1;
-}
-
-// a neighbour slot t - e_a (D = -1) or t + e_a (D = +1): folded, false when
-// outside the domain
-template <int D>
-__device__ __forceinline__ bool nb(const int *n, const int *per, const int *t, int a, int *q) {
-    q[0] = t[0];
-    q[1] = t[1];
-    q[2] = t[2];
-    q[a] = fold(t[a] + D, n[a], per[a]);
-    return q[a] >= 0;
-}
-
-// the neighbour t + D e_a as nb, or t itself where nb finds none (false):
-// the caller evaluates there and drops the value
-template <int D>
-__device__ __forceinline__ bool nb_or_self(const int *n, const int *per, const int *t, int a, int *q) {
-    const bool ok = nb<D>(n, per, t, a, q);
-    if (!ok) q[a] = t[a];
-    return ok;
 }
 
 // adj_face_core for a face of family C at slot idx inside the reach of film F
@@ -1204,90 +1197,42 @@ __device__ __forceinline__ long long region_index_folded(const int *n, const int
     return li;
 }
 
-// a new lambda psi value held for a store after the thread's last load
-// (q1 / q2 < 0: none)
+// the weights of the film-energy gradient over the loss film's region (its
+// cell box grown by one slot), once per adjoint run: [6][region], the sum of
+// eps_r over the film cells that share the E_C edge, the number of them that
+// share the H_C face
 template <typename T>
-struct PsiOut {
-    long long q1 = -1, q2 = -1;
-    T v1 = T(0), v2 = T(0);
-};
-
-// curl-part adjoints (aD0, aD1) of the face of family F at slot f (in the
-// domain), general case: from the film region's table, or from lambda H with
-// the CPML recursions (own: also store lambda psiH after the map).  In
-// float32 every load is unconditional (a lane outside a slab reads its
-// lambda H again in place of the slab state and drops it), so that the loads
-// of all of a thread's faces can be in flight at once.
-template <typename T, int F, int FILM>
-__device__ __forceinline__ void hface(const AdjParams<T> &A, const int *f, bool own, T &aD0, T &aD1) {
-    constexpr int F1 = (F + 1) % 3, F2 = (F + 2) % 3;
-    const KParams<T> &p = A.p;
-    if (FILM) {
-        long long lr;
-        const int fr = first_region(A, f, lr);
-        if (fr >= 0) {
-            const AdjFilmDev &G = A.af[fr];
-            aD0 = (T)G.aDr[(F * 2) * G.nr + lr];
-            aD1 = (T)G.aDr[(F * 2 + 1) * G.nr + lr];
-            return;
+__global__ void __launch_bounds__(256) k_adj_loss_weights(KParams<T> p, int film, double *dst) {
+    const FilmDev F = film_desc(p.films, film);
+    const int b0[3] = {F.cb[0], F.cb[1], F.cb[2]}, r[3] = {F.cb[3] + 1, F.cb[4] + 1, F.cb[5] + 1};
+    const long long tb = (long long)r[0] * r[1] * r[2];
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
+    if (t >= tb) return;
+    int q[3];
+    const bool slot = region_slot(p.n, p.per, b0, r, t, q);
+    for (int C = 0; C < 3; C++) {
+        const int C1 = (C + 1) % 3, C2 = (C + 2) % 3;
+        double se = 0.0, eps;
+        int nc = 0;
+        if (slot) {
+            for (int u = 0; u < 2; u++)
+                for (int v = 0; v < 2; v++) {
+                    int cc[3] = {q[0], q[1], q[2]};
+                    cc[C1] -= u;
+                    cc[C2] -= v;
+                    for (int a = 0; a < 3; a++) cc[a] = fold(cc[a], p.n[a], p.per[a]);
+                    if (cc[0] >= 0 && cc[1] >= 0 && cc[2] >= 0 && film_cell(p, F, cc[0], cc[1], cc[2], eps)) se += eps;
+                }
+            for (int u = 0; u < 2; u++) {
+                int cc[3] = {q[0], q[1], q[2]};
+                cc[C] -= u;
+                for (int a = 0; a < 3; a++) cc[a] = fold(cc[a], p.n[a], p.per[a]);
+                if (cc[0] >= 0 && cc[1] >= 0 && cc[2] >= 0 && film_cell(p, F, cc[0], cc[1], cc[2], eps)) nc++;
+            }
         }
+        dst[C * tb + t] = se;
+        dst[(3 + C) * tb + t] = (double)nc;
     }
-    const T *hp = A.lH[F] + p.slot(f[0], f[1], f[2]);
-    const int a1 = f[F1], a2 = f[F2];
-    const bool s1 = p.psiH[F][F1] && (a1 < p.nlo[F1] || a1 >= p.n[F1] - p.nhi[F1]);
-    const bool s2 = p.psiH[F][F2] && (a2 < p.nlo[F2] || a2 >= p.n[F2] - p.nhi[F2]);
-    if constexpr (sizeof(T) == 8) {
-        // float64: the slab state loaded where needed only (the unconditional
-        // form's registers cost a wave per SIMD here, and it measured slower)
-        const T lH = *hp;
-        const T g1 = -p.hc * lH, g2 = p.hc * lH;
-        aD0 = g1;
-        aD1 = g2;
-        if (s1) {
-            const long long q1 = p.psi_index(F1, f);
-            const T aps = A.lpsiH[F][F1][q1] + g1;
-            if (own) A.lpsiHo[F][F1][q1] = p.bH[F1][a1] * aps;
-            aD0 = g1 + p.cH[F1][a1] * aps;
-        }
-        if (s2) {
-            const long long q2 = p.psi_index(F2, f);
-            const T aps = A.lpsiH[F][F2][q2] + g2;
-            if (own) A.lpsiHo[F][F2][q2] = p.bH[F2][a2] * aps;
-            aD1 = g2 + p.cH[F2][a2] * aps;
-        }
-    } else {
-        const long long q1 = s1 ? p.psi_index(F1, f) : 0, q2 = s2 ? p.psi_index(F2, f) : 0;
-        const T lH = *hp;
-        const T ps1 = *(s1 ? A.lpsiH[F][F1] + q1 : hp), ps2 = *(s2 ? A.lpsiH[F][F2] + q2 : hp);
-        const T b1 = *(s1 ? p.bH[F1] + a1 : hp), c1 = *(s1 ? p.cH[F1] + a1 : hp);
-        const T b2 = *(s2 ? p.bH[F2] + a2 : hp), c2 = *(s2 ? p.cH[F2] + a2 : hp);
-        const T g1 = -p.hc * lH, g2 = p.hc * lH;
-        aD0 = g1;
-        aD1 = g2;
-        if (s1) {
-            const T aps = ps1 + g1;
-            if (own) A.lpsiHo[F][F1][q1] = b1 * aps;
-            aD0 = g1 + c1 * aps;
-        }
-        if (s2) {
-            const T aps = ps2 + g2;
-            if (own) A.lpsiHo[F][F2][q2] = b2 * aps;
-            aD1 = g2 + c2 * aps;
-        }
-    }
-}
-
-// float64: a neighbour face of family F at t - e_axis, false past a wall
-// (values zero)
-template <typename T, int F, int FILM>
-__device__ __forceinline__ bool hface_nb(const AdjParams<T> &A, const int *t, int axis, T &x0, T &x1) {
-    int u[3];
-    if (!nb<-1>(A.p.n, A.p.per, t, axis, u)) {
-        x0 = x1 = T(0);
-        return false;
-    }
-    hface<T, F, FILM>(A, u, false, x0, x1);
-    return true;
 }
 
 // the loss term of the state at the start of the step (film-energy
@@ -1298,32 +1243,25 @@ __device__ __forceinline__ bool hface_nb(const AdjParams<T> &A, const int *t, in
 template <typename T, int PART = 0>
 __device__ __forceinline__ void loss_term(const AdjParams<T> &A, const int *t, long long q, T &l0, T &l1, T &l2) {
     const KParams<T> &p = A.p;
-    const FilmDev &F = p.films[A.lfilm];
+    const FilmDev F = film_desc(p.films, A.lfilm);
     const int b0[3] = {F.cb[0], F.cb[1], F.cb[2]}, r[3] = {F.cb[3] + 1, F.cb[4] + 1, F.cb[5] + 1};
     const long long ri = region_index_folded(p.n, p.per, b0, r, t);
     if (ri < 0) return;
     const long long tb = (long long)r[0] * r[1] * r[2];
     T le[3] = {l0, l1, l2};
+#pragma unroll
     for (int C = 0; C < 3; C++) {
-        const int C1 = (C + 1) % 3, C2 = (C + 2) % 3;
-        double se = 0.0, eps;
-        for (int u = 0; u < 2; u++)
-            for (int v = 0; v < 2; v++) {
-                int cc[3] = {t[0], t[1], t[2]};
-                cc[C1] -= u;
-                cc[C2] -= v;
-                for (int a = 0; a < 3; a++) cc[a] = fold(cc[a], p.n[a], p.per[a]);
-                if (cc[0] >= 0 && cc[1] >= 0 && cc[2] >= 0 && film_cell(p, F, cc[0], cc[1], cc[2], eps)) se += eps;
-            }
-        if (PART != 2 && se != 0.0) le[C] += (T)(A.lscale * p.dV * p.eps0 * se * 0.25 * A.ltape[C * tb + ri]);
-        int nc = 0;
-        for (int u = 0; u < 2; u++) {
-            int cc[3] = {t[0], t[1], t[2]};
-            cc[C] -= u;
-            for (int a = 0; a < 3; a++) cc[a] = fold(cc[a], p.n[a], p.per[a]);
-            if (cc[0] >= 0 && cc[1] >= 0 && cc[2] >= 0 && film_cell(p, F, cc[0], cc[1], cc[2], eps)) nc++;
+        if (PART != 2) {
+            const double se = A.lw[C * tb + ri], x = A.ltape[C * tb + ri];
+            const T v = (T)(A.lscale * p.dV * p.eps0 * se * 0.25 * x);
+            le[C] = se != 0.0 ? le[C] + v : le[C];
         }
-        if (PART != 1 && nc) A.lH[C][q] += (T)(A.lscale * p.dV * p.mu0 * 0.5 * nc * A.ltape[(3 + C) * tb + ri]);
+        if (PART != 1) {
+            const double nc = A.lw[(3 + C) * tb + ri], x = A.ltape[(3 + C) * tb + ri];
+            const T h = A.lH[C][q];
+            const T v = (T)(A.lscale * p.dV * p.mu0 * 0.5 * nc * x);
+            if (nc != 0.0) A.lH[C][q] = h + v;
+        }
     }
     l0 = le[0];
     l1 = le[1];
@@ -1340,263 +1278,303 @@ __device__ __forceinline__ int adj_tile_flag(const uint8_t *tab) {
     return (int)((w >> (8 * (ti & 3))) & 0xffu);
 }
 
-// the six differences of the transposed curl a slot's half-step pass adds to
-// its lambda E, in a tile near a CPML slab (FILM = 0) or a film's reach
-// (FILM = 1): d = {d0a, d0b, d1a, d1b, d2a, d2b}, lambda E_C gaining
-// dCa + dCb.  Each own face's two curl-part adjoints are paired with their
-// neighbours' as soon as those are known, so few values are live at once.
-template <typename T, int FILM>
-__device__ __forceinline__ void hfield_general(const AdjParams<T> &A, const int *t, T *d) {
-    const KParams<T> &p = A.p;
-    T a, b, x0, x1;
-    bool ok;
-    if constexpr (sizeof(T) == 8) {
-        // own face of family 1: with the family-1 faces at k - 1 and i - 1
-        hface<T, 1, FILM>(A, t, true, a, b);
-        ok = hface_nb<T, 1, FILM>(A, t, 2, x0, x1);
-        d[0] = dif((ok ? x0 : T(0)) - a, T(0), p.dT[2], p.invd[2]);
-        ok = hface_nb<T, 1, FILM>(A, t, 0, x0, x1);
-        d[5] = dif((ok ? x1 : T(0)) - b, T(0), p.dT[0], p.invd[0]);
-        // family 2: with the family-2 faces at j - 1 and i - 1
-        hface<T, 2, FILM>(A, t, true, a, b);
-        ok = hface_nb<T, 2, FILM>(A, t, 1, x0, x1);
-        d[1] = dif((ok ? x1 : T(0)) - b, T(0), p.dT[1], p.invd[1]);
-        ok = hface_nb<T, 2, FILM>(A, t, 0, x0, x1);
-        d[2] = dif((ok ? x0 : T(0)) - a, T(0), p.dT[0], p.invd[0]);
-        // family 0: with the family-0 faces at k - 1 and j - 1
-        hface<T, 0, FILM>(A, t, true, a, b);
-        ok = hface_nb<T, 0, FILM>(A, t, 2, x0, x1);
-        d[3] = dif((ok ? x1 : T(0)) - b, T(0), p.dT[2], p.invd[2]);
-        ok = hface_nb<T, 0, FILM>(A, t, 1, x0, x1);
-        d[4] = dif((ok ? x0 : T(0)) - a, T(0), p.dT[1], p.invd[1]);
-    } else {
-        // the same in float32 with every neighbour evaluated (one past a wall
-        // at the own slot, its values dropped): no load waits on a branch
-        int u[3];
-        hface<T, 1, FILM>(A, t, true, a, b);
-        ok = nb_or_self<-1>(p.n, p.per, t, 2, u);
-        hface<T, 1, FILM>(A, u, false, x0, x1);
-        d[0] = dif((ok ? x0 : T(0)) - a, T(0), p.dT[2], p.invd[2]);
-        ok = nb_or_self<-1>(p.n, p.per, t, 0, u);
-        hface<T, 1, FILM>(A, u, false, x0, x1);
-        d[5] = dif((ok ? x1 : T(0)) - b, T(0), p.dT[0], p.invd[0]);
-        hface<T, 2, FILM>(A, t, true, a, b);
-        ok = nb_or_self<-1>(p.n, p.per, t, 1, u);
-        hface<T, 2, FILM>(A, u, false, x0, x1);
-        d[1] = dif((ok ? x1 : T(0)) - b, T(0), p.dT[1], p.invd[1]);
-        ok = nb_or_self<-1>(p.n, p.per, t, 0, u);
-        hface<T, 2, FILM>(A, u, false, x0, x1);
-        d[2] = dif((ok ? x0 : T(0)) - a, T(0), p.dT[0], p.invd[0]);
-        hface<T, 0, FILM>(A, t, true, a, b);
-        ok = nb_or_self<-1>(p.n, p.per, t, 2, u);
-        hface<T, 0, FILM>(A, u, false, x0, x1);
-        d[3] = dif((ok ? x1 : T(0)) - b, T(0), p.dT[2], p.invd[2]);
-        ok = nb_or_self<-1>(p.n, p.per, t, 1, u);
-        hface<T, 0, FILM>(A, u, false, x0, x1);
-        d[4] = dif((ok ? x0 : T(0)) - a, T(0), p.dT[1], p.invd[1]);
-    }
-}
-
 // ---------------------------------------------------------------------------
-// The merged pass of two consecutive half-step transposes on the E side: the
-// first half step of step m (with the E step's lambda E = ca lambda E', the
-// eps-box sums, the loss term's lambda E part and a weighted trace's term of
-// the state at step m's start), then the second half step of step m - 1,
-// whose lambda H of non-film faces is the same (the first pass changes lambda
-// E only; the film kernels between them change the film region's faces,
-// which both take from their own tables).  A face's CPML state goes through
-// both recursions in one thread (read from set lpsiH, stored in lpsiHo);
-// every value follows the two single passes' operation sequence, so the
-// results are theirs, bitwise.  Used only where no film's reach meets a CPML
-// slab (the film-region passes keep their state per half step).
+// the field passes of the tape schedule, by wavefront rows (rows.h): each of
+// the six differences of a transposed curl runs along one axis and is
+// stretched by that axis's CPML alone, so a row's y and z slabs are uniform
+// and only the x slab is a lane's matter
 // ---------------------------------------------------------------------------
 
-// the two half steps' curl-part adjoints (a0, a1: the first; b0, b1: the
-// second) of the face of family F at slot f; own: store its lambda psiH after
-// both maps
-template <typename T, int F, int FILM>
-__device__ __forceinline__ void hface2(const AdjParams<T> &A, const int *f, bool own, T &a0, T &a1, T &b0, T &b1) {
-    constexpr int F1 = (F + 1) % 3, F2 = (F + 2) % 3;
-    const KParams<T> &p = A.p;
-    if (FILM) {
-        long long lr;
-        const int fr = first_region(A, f, lr);
-        if (fr >= 0) {
-            const AdjFilmDev G = scalar_desc(A.af, fr), Gb = scalar_desc(A.afb, fr);
-            a0 = (T)G.aDr[(F * 2) * G.nr + lr];
-            a1 = (T)G.aDr[(F * 2 + 1) * G.nr + lr];
-            b0 = (T)Gb.aDr[(F * 2) * Gb.nr + lr];
-            b1 = (T)Gb.aDr[(F * 2 + 1) * Gb.nr + lr];
-            return;
-        }
-    }
-    const T lH = A.lH[F][p.slot(f[0], f[1], f[2])];
-    const T g1 = -p.hc * lH, g2 = p.hc * lH;
-    a0 = b0 = g1;
-    a1 = b1 = g2;
-    const int c1 = f[F1], c2 = f[F2];
-    if (p.psiH[F][F1] && (c1 < p.nlo[F1] || c1 >= p.n[F1] - p.nhi[F1])) {
-        const long long qq = p.psi_index(F1, f);
-        const T bb = p.bH[F1][c1], cc = p.cH[F1][c1];
-        const T aps = A.lpsiH[F][F1][qq] + g1;
-        a0 = g1 + cc * aps;
-        const T aps2 = bb * aps + g1;
-        b0 = g1 + cc * aps2;
-        if (own) A.lpsiHo[F][F1][qq] = bb * aps2;
-    }
-    if (p.psiH[F][F2] && (c2 < p.nlo[F2] || c2 >= p.n[F2] - p.nhi[F2])) {
-        const long long qq = p.psi_index(F2, f);
-        const T bb = p.bH[F2][c2], cc = p.cH[F2][c2];
-        const T aps = A.lpsiH[F][F2][qq] + g2;
-        a1 = g2 + cc * aps;
-        const T aps2 = bb * aps + g2;
-        b1 = g2 + cc * aps2;
-        if (own) A.lpsiHo[F][F2][qq] = bb * aps2;
-    }
-}
-
-// the six differences of each half step (d: the first, e: the second), as
-// hfield_general's
-template <typename T, int FILM>
-__device__ __forceinline__ void hfield_general2(const AdjParams<T> &A, const int *t, T *d, T *e) {
-    const KParams<T> &p = A.p;
-    T a0, a1, b0, b1, x0, x1, y0, y1;
-    int u[3];
-    bool ok;
-    // own face of family 1: with the family-1 faces at k - 1 and i - 1
-    hface2<T, 1, FILM>(A, t, true, a0, a1, b0, b1);
-    ok = nb_or_self<-1>(p.n, p.per, t, 2, u);
-    hface2<T, 1, FILM>(A, u, false, x0, x1, y0, y1);
-    d[0] = dif((ok ? x0 : T(0)) - a0, T(0), p.dT[2], p.invd[2]);
-    e[0] = dif((ok ? y0 : T(0)) - b0, T(0), p.dT[2], p.invd[2]);
-    ok = nb_or_self<-1>(p.n, p.per, t, 0, u);
-    hface2<T, 1, FILM>(A, u, false, x0, x1, y0, y1);
-    d[5] = dif((ok ? x1 : T(0)) - a1, T(0), p.dT[0], p.invd[0]);
-    e[5] = dif((ok ? y1 : T(0)) - b1, T(0), p.dT[0], p.invd[0]);
-    // family 2: with the family-2 faces at j - 1 and i - 1
-    hface2<T, 2, FILM>(A, t, true, a0, a1, b0, b1);
-    ok = nb_or_self<-1>(p.n, p.per, t, 1, u);
-    hface2<T, 2, FILM>(A, u, false, x0, x1, y0, y1);
-    d[1] = dif((ok ? x1 : T(0)) - a1, T(0), p.dT[1], p.invd[1]);
-    e[1] = dif((ok ? y1 : T(0)) - b1, T(0), p.dT[1], p.invd[1]);
-    ok = nb_or_self<-1>(p.n, p.per, t, 0, u);
-    hface2<T, 2, FILM>(A, u, false, x0, x1, y0, y1);
-    d[2] = dif((ok ? x0 : T(0)) - a0, T(0), p.dT[0], p.invd[0]);
-    e[2] = dif((ok ? y0 : T(0)) - b0, T(0), p.dT[0], p.invd[0]);
-    // family 0: with the family-0 faces at k - 1 and j - 1
-    hface2<T, 0, FILM>(A, t, true, a0, a1, b0, b1);
-    ok = nb_or_self<-1>(p.n, p.per, t, 2, u);
-    hface2<T, 0, FILM>(A, u, false, x0, x1, y0, y1);
-    d[3] = dif((ok ? x1 : T(0)) - a1, T(0), p.dT[2], p.invd[2]);
-    e[3] = dif((ok ? y1 : T(0)) - b1, T(0), p.dT[2], p.invd[2]);
-    ok = nb_or_self<-1>(p.n, p.per, t, 1, u);
-    hface2<T, 0, FILM>(A, u, false, x0, x1, y0, y1);
-    d[4] = dif((ok ? x0 : T(0)) - a0, T(0), p.dT[1], p.invd[1]);
-    e[4] = dif((ok ? y0 : T(0)) - b0, T(0), p.dT[1], p.invd[1]);
-}
+// the adjoint psi of a wavefront's slots and of their neighbours one slot off
+// (D = -1: faces below; +1: edges above) along one axis, for the two
+// components that differentiate along it
+template <typename T>
+struct AdjAxis {
+    bool s = false, sn = false; // in a slab: the slot, its neighbour (x: per lane; y, z: uniform)
+    T b = T(0), c = T(0), bn = T(0), cn = T(0);
+    T pa = T(0), pan = T(0), pb = T(0), pbn = T(0); // psi of the components axis + 1 and axis + 2
+    unsigned o = 0;                                 // byte offset of the slot's psi in its row
+    long long q = 0;                                // first element of that row
+};
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_adj_hfield2(AdjParams<T> A) {
+__device__ __forceinline__ unsigned x_psi_off(const KParams<T> &p, int i, bool in) {
+    const int sp = i < p.nlo[0] ? i : p.nlo[0] + (i - (p.n[0] - p.nhi[0]));
+    return (unsigned)(in ? sp : 0) * (unsigned)sizeof(T);
+}
+
+// pa, pb: the psi arrays (null without slabs on the axis); bt, ct: the
+// recursion's tables; io: the lane's byte offset in a padded row
+template <typename T, int D>
+__device__ __forceinline__ void adj_axis_x(const KParams<T> &p, const RowPos &r, const T *pa, const T *pb, const T *bt,
+                                           const T *ct, AdjAxis<T> &m) {
+    if (p.nlo[0] + p.nhi[0] == 0) return;
+    if (!(r.w0 + (D < 0 ? D : 0) < p.nlo[0] || r.w0 + 63 + (D > 0 ? D : 0) >= p.n[0] - p.nhi[0])) return; // uniform
+    const int i = min(r.i, p.n[0] - 1), in = i + D;
+    m.s = in_slab(p, 0, i);
+    m.sn = in >= 0 && in < p.n[0] && in_slab(p, 0, in);
+    m.q = row_psi(p, 0, r.j, r.k);
+    m.o = x_psi_off(p, i, m.s);
+    const unsigned on = x_psi_off(p, in, m.sn), es = (unsigned)sizeof(T);
+    const unsigned io = (unsigned)i * es, inn = (unsigned)(m.sn ? in : i) * es;
+    m.pa = row_ld(pa + m.q, m.o);
+    m.pan = row_ld(pa + m.q, on);
+    m.pb = row_ld(pb + m.q, m.o);
+    m.pbn = row_ld(pb + m.q, on);
+    m.b = row_ld(bt, io);
+    m.c = row_ld(ct, io);
+    m.bn = row_ld(bt, inn);
+    m.cn = row_ld(ct, inn);
+}
+
+template <typename T, int D, int W>
+__device__ __forceinline__ void adj_axis_yz(const KParams<T> &p, const RowPos &r, const T *pa, const T *pb,
+                                            const T *bt, const T *ct, unsigned io, AdjAxis<T> &m) {
+    if (p.nlo[W] + p.nhi[W] == 0) return;
+    const int x = W == 1 ? r.j : r.k, xn = x + D;
+    m.s = in_slab(p, W, x);
+    m.sn = xn >= 0 && xn < p.n[W] && in_slab(p, W, xn);
+    m.o = io;
+    if (m.s) {
+        m.q = row_psi(p, W, r.j, r.k);
+        m.pa = row_ld(pa + m.q, io);
+        m.pb = row_ld(pb + m.q, io);
+        m.b = scalar_ld(bt, x);
+        m.c = scalar_ld(ct, x);
+    }
+    if (m.sn) {
+        const long long qn = W == 1 ? row_psi(p, W, xn, r.k) : row_psi(p, W, r.j, xn);
+        m.pan = row_ld(pa + qn, io);
+        m.pbn = row_ld(pb + qn, io);
+        m.bn = scalar_ld(bt, xn);
+        m.cn = scalar_ld(ct, xn);
+    }
+}
+
+// the curl-part adjoint of a face from g = -/+ hc lambda H through its CPML
+// recursion (a: the first half step transposed; with PAIR the psi goes on
+// through the second, h); ps becomes the psi after the maps
+template <typename T, bool PAIR>
+__device__ __forceinline__ void adj_stretch(bool s, T g, T b, T c, T &ps, T &a, T &h) {
+    a = h = g;
+    const T aps = ps + g;
+    const T a1 = g + c * aps;
+    T out = b * aps, h1 = g;
+    if (PAIR) {
+        const T aps2 = b * aps + g;
+        h1 = g + c * aps2;
+        out = b * aps2;
+    }
+    a = s ? a1 : a;
+    h = s ? h1 : h;
+    ps = s ? out : ps;
+}
+
+// what a half-step field pass runs: the second half step of a step transposed
+// (writes mu for the E step's transpose), the first (scaling lambda E by ca
+// before, with the eps-box sums and the loss of the step's input state), or
+// the first of step m and the second of step m - 1 together
+enum { HF_SECOND = 0, HF_FIRST = 1, HF_PAIR = 2 };
+
+// inside a film's reach the curl-part adjoints come from the tables of the film
+// kernels: part w (2 F + part) of the slot's own face (o, h: of the first and
+// the second half step) and of the one before it along axis AX (n, hn).  The
+// first film that holds a face counts; returns whether one holds the slot's.
+template <typename T, bool PAIR, int AX>
+__device__ __forceinline__ bool film_part_values(const AdjParams<T> &A, const RowPos &r, int w, T &o, T &n, T &h,
+                                                 T &hn) {
     const KParams<T> &p = A.p;
-    const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
-    if (i >= p.n[0] || j >= p.n[1]) return;
-    const int t[3] = {i, j, k};
-    const long long q = p.slot(i, j, k);
-    const uint8_t fl = (uint8_t)adj_tile_flag(A.aflags);
+    int nb[3] = {r.i, r.j, r.k};
+    nb[AX] = nb[AX] > 0 ? nb[AX] - 1 : (p.per[AX] ? p.n[AX] - 1 : -1);
+    bool own = false;
+    for (int f = p.nfilm - 1; f >= 0; f--) {
+        const AdjFilmDev G = scalar_desc(A.af, f);
+        const double *t2 = G.aDr;
+        if (PAIR) t2 = scalar_desc(A.afb, f).aDr;
+        const int x = r.i - G.r0[0], y = r.j - G.r0[1], z = r.k - G.r0[2];
+        const int xn = nb[0] - G.r0[0], yn = nb[1] - G.r0[1], zn = nb[2] - G.r0[2];
+        if (y >= 0 && y < G.rn[1] && z >= 0 && z < G.rn[2] && x >= 0 && x < G.rn[0] && r.in) {
+            const long long q = w * G.nr + x + (long long)G.rn[0] * ((long long)y + (long long)G.rn[1] * z);
+            o = (T)G.aDr[q];
+            if (PAIR) h = (T)t2[q];
+            own = true;
+        }
+        if (yn >= 0 && yn < G.rn[1] && zn >= 0 && zn < G.rn[2] && xn >= 0 && xn < G.rn[0] && r.in) {
+            const long long q = w * G.nr + xn + (long long)G.rn[0] * ((long long)yn + (long long)G.rn[1] * zn);
+            n = (T)G.aDr[q];
+            if (PAIR) hn = (T)t2[q];
+        }
+    }
+    return own;
+}
+
+// the transposed half step(s) on the E side: lambda E_C += the transposed curl
+// of the faces' curl-part adjoints.  Six differences, by face family F and part
+// (index 2 F + part; part 0 runs along axis F + 1, part 1 along F + 2), each of
+// the slot's face and the one before it along that axis.
+// One pass for HF_PAIR: non-film faces see the same lambda H in both maps, the
+// film region's come from the film kernels' tables; every value follows the
+// two single passes' operation sequence, so the results are theirs, bitwise
+// (only where no film's reach meets a CPML slab: the film-region kernels keep
+// their psi per half step).
+// HF_PAIR moves 49 bytes a slot in float32 (lambda E, lambda H, the class in;
+// lambda E, mu out) and 16 a slab slot and axis: 175 us on a 512 x 256 x 128 grid
+// with CPML 10 at the rate of a copy.  With each slot walking its faces'
+// recursions by branches it took 390 us (252 vector instructions and nine
+// dependent psi fetches a wavefront); by rows 211 us.
+template <typename T, int MODE, int TX, int TY>
+__global__ void __launch_bounds__(256) k_adj_hfield(AdjParams<T> A) {
+    constexpr bool PAIR = MODE == HF_PAIR;
+    const KParams<T> &p = A.p;
+    const RowPos r = row_pos<TX>(p.n, blockIdx.x, blockIdx.y, TY, blockIdx.z);
+    if (r.j >= p.n[1]) return;
+    const unsigned es = (unsigned)sizeof(T);
+    const int ic = min(r.i, p.n[0] - 1), j = r.j, k = r.k;
+    const long long sz = (long long)p.px * p.n[1];
+    const unsigned io = (unsigned)ic * es, rowb = (unsigned)p.px * es, vo = io + (unsigned)j * rowb;
+    const bool okx = ic > 0 || p.per[0], oky = j > 0 || p.per[1], okz = k > 0 || p.per[2];
+    const unsigned vxm = ic > 0 ? vo - es : (p.per[0] ? vo + (unsigned)(p.n[0] - 1) * es : vo);
+    const unsigned vym = io + (unsigned)(j > 0 ? j - 1 : (p.per[1] ? p.n[1] - 1 : j)) * rowb;
+    const long long zo = k * sz, zb = (k > 0 ? k - 1 : (p.per[2] ? p.n[2] - 1 : k)) * sz;
+    const EdgeRow e = edge_class(p, ic, j, k, zo);
+    const T *Hx = A.lH[0] + zo, *Hy = A.lH[1] + zo, *Hz = A.lH[2] + zo;
+    const T x0 = row_ld(Hx, vo), x_z = row_ld(A.lH[0] + zb, vo), x_y = row_ld(Hx, vym);
+    const T y0 = row_ld(Hy, vo), y_z = row_ld(A.lH[1] + zb, vo), y_x = row_ld(Hy, vxm);
+    const T z0 = row_ld(Hz, vo), z_x = row_ld(Hz, vxm), z_y = row_ld(Hz, vym);
     // the slot's lambda E is touched once per pass: non-temporal (the lambda
     // H the neighbouring slots read again stays in L2)
-    T l0 = __builtin_nontemporal_load(A.lE[0] + q), l1 = __builtin_nontemporal_load(A.lE[1] + q),
-      l2 = __builtin_nontemporal_load(A.lE[2] + q);
+    T *Ex = A.lE[0] + zo, *Ey = A.lE[1] + zo, *Ez = A.lE[2] + zo;
+    T l[3] = {row_ld<true>(Ex, vo), row_ld<true>(Ey, vo), row_ld<true>(Ez, vo)};
+    AdjAxis<T> ax, ay, az;
+    adj_axis_x<T, -1>(p, r, A.lpsiH[1][0], A.lpsiH[2][0], p.bH[0], p.cH[0], ax);
+    adj_axis_yz<T, -1, 1>(p, r, A.lpsiH[2][1], A.lpsiH[0][1], p.bH[1], p.cH[1], io, ay);
+    adj_axis_yz<T, -1, 2>(p, r, A.lpsiH[0][2], A.lpsiH[1][2], p.bH[2], p.cH[2], io, az);
     T ca[3], cb[3];
     bool ok[3];
-    edge_coefs<T>(p, t, q, ca, cb, ok);
-    T dd[6], de[6];
-    if (fl == 0) {
-        // no CPML state, no film region: both half steps take -/+ hc lambda H
-        T o0[3], o1[3];
-        T n1m2 = T(0), n2m1 = T(0), n2m0 = T(0), n0m2 = T(0), n0m1 = T(0), n1m0 = T(0);
-        int u[3];
-#pragma unroll
-        for (int F = 0; F < 3; F++) {
-            const T l = A.lH[F][q];
-            o0[F] = -(p.hc * l);
-            o1[F] = p.hc * l;
-        }
-        bool ok2 = nb_or_self<-1>(p.n, p.per, t, 2, u);
-        const T h1m2 = A.lH[1][p.slot(u[0], u[1], u[2])], h0m2 = A.lH[0][p.slot(u[0], u[1], u[2])];
-        bool ok1 = nb_or_self<-1>(p.n, p.per, t, 1, u);
-        const T h2m1 = A.lH[2][p.slot(u[0], u[1], u[2])], h0m1 = A.lH[0][p.slot(u[0], u[1], u[2])];
-        bool ok0 = nb_or_self<-1>(p.n, p.per, t, 0, u);
-        const T h2m0 = A.lH[2][p.slot(u[0], u[1], u[2])], h1m0 = A.lH[1][p.slot(u[0], u[1], u[2])];
-        if (ok2) {
-            n1m2 = -(p.hc * h1m2);
-            n0m2 = p.hc * h0m2;
-        }
-        if (ok1) {
-            n2m1 = p.hc * h2m1;
-            n0m1 = -(p.hc * h0m1);
-        }
-        if (ok0) {
-            n2m0 = -(p.hc * h2m0);
-            n1m0 = p.hc * h1m0;
-        }
-        dd[0] = dif(n1m2 - o0[1], T(0), p.dT[2], p.invd[2]);
-        dd[1] = dif(n2m1 - o1[2], T(0), p.dT[1], p.invd[1]);
-        dd[2] = dif(n2m0 - o0[2], T(0), p.dT[0], p.invd[0]);
-        dd[3] = dif(n0m2 - o1[0], T(0), p.dT[2], p.invd[2]);
-        dd[4] = dif(n0m1 - o0[0], T(0), p.dT[1], p.invd[1]);
-        dd[5] = dif(n1m0 - o1[1], T(0), p.dT[0], p.invd[0]);
-#pragma unroll
-        for (int w = 0; w < 6; w++) de[w] = dd[w];
-    } else if (fl & 4) {
-        hfield_general2<T, 1>(A, t, dd, de);
-    } else {
-        hfield_general2<T, 0>(A, t, dd, de);
+    edge_row_coefs<T>(p, e, ic, j, k, ca, cb, ok);
+    // the differences one by one (a film tile's table values are then not all
+    // live at once): part 0 takes -hc lambda H, part 1 +hc lambda H
+    const T hn = -p.hc, hp = p.hc;
+    const int fl = p.nfilm ? adj_tile_flag(A.aflags) : 0;
+    bool film_own = false;
+#define MPX_DIFF(AX, W, HC, V0, VN, M, PS, PSN, OK, D, E)                                              \
+    {                                                                                                  \
+        T o = (HC) * (V0), n = (HC) * (VN), h = o, g = n;                                              \
+        if (AX == 0) {                                                                                 \
+            if (M.s || M.sn) {                                                                         \
+                adj_stretch<T, PAIR>(M.s, o, M.b, M.c, M.PS, o, h);                                    \
+                adj_stretch<T, PAIR>(M.sn, n, M.bn, M.cn, M.PSN, n, g);                                \
+            }                                                                                          \
+        } else {                                                                                       \
+            if (M.s) adj_stretch<T, PAIR>(true, o, M.b, M.c, M.PS, o, h);                              \
+            if (M.sn) adj_stretch<T, PAIR>(true, n, M.bn, M.cn, M.PSN, n, g);                          \
+        }                                                                                              \
+        if (fl & 4) film_own = film_part_values<T, PAIR, AX>(A, r, W, o, n, h, g);                     \
+        D = dif((OK ? n : T(0)) - o, T(0), p.dT[AX], p.invd[AX]);                                      \
+        if (PAIR) E = dif((OK ? g : T(0)) - h, T(0), p.dT[AX], p.invd[AX]);                            \
     }
-    if (A.btape) {
-        // dL/dca += lambda E' E^n, dL/dcb += lambda E' x^n over the eps box
-        const int r[3] = {A.bs[0] + 1, A.bs[1] + 1, A.bs[2] + 1};
-        const long long ri = region_index_folded(p.n, p.per, A.bb, r, t);
-        if (ri >= 0) {
-            const long long tb = (long long)r[0] * r[1] * r[2];
-            const T lv[3] = {l0, l1, l2};
+    T d, d2, e1 = T(0), e2 = T(0), dd[3], de[3] = {T(0), T(0), T(0)};
+    MPX_DIFF(2, 2, hn, y0, y_z, az, pb, pbn, okz, d, e1);
+    MPX_DIFF(1, 5, hp, z0, z_y, ay, pa, pan, oky, d2, e2);
+    dd[0] = d + d2;
+    if (PAIR) de[0] = e1 + e2;
+    MPX_DIFF(0, 4, hn, z0, z_x, ax, pb, pbn, okx, d, e1);
+    MPX_DIFF(2, 1, hp, x0, x_z, az, pa, pan, okz, d2, e2);
+    dd[1] = d + d2;
+    if (PAIR) de[1] = e1 + e2;
+    MPX_DIFF(1, 0, hn, x0, x_y, ay, pb, pbn, oky, d, e1);
+    MPX_DIFF(0, 3, hp, y0, y_x, ax, pa, pan, okx, d2, e2);
+    dd[2] = d + d2;
+    if (PAIR) de[2] = e1 + e2;
+#undef MPX_DIFF
+    const long long q = zo + (long long)p.px * j + ic;
+    const int t[3] = {ic, j, k};
+    const T lp[3] = {l[0], l[1], l[2]}; // lambda E' of the step
+    if (MODE != HF_SECOND) {
 #pragma unroll
-            for (int C = 0; C < 3; C++) {
-                A.gca_box[C * tb + ri] += (double)lv[C] * A.btape[C * tb + ri];
-                A.gcb_box[C * tb + ri] += (double)lv[C] * A.btape[(3 + C) * tb + ri];
+        for (int C = 0; C < 3; C++) l[C] = ok[C] ? ca[C] * l[C] : T(0);
+    }
+    l[0] = l[0] + dd[0];
+    l[1] = l[1] + dd[1];
+    l[2] = l[2] + dd[2];
+    if (MODE != HF_SECOND) {
+        if (A.ltape && (fl & 4) && A.seg0[0] + A.m > A.loss_from && r.in)
+            loss_term<T, PAIR ? 1 : 0>(A, t, q, l[0], l[1], l[2]);
+        if (A.pw && q == A.pw_slot && r.in) {
+            // the weighted trace's term of the state at the step's start (time n)
+            const long long n = A.seg0[0] + A.m;
+            if (n >= 1) {
+                const T v = (T)(A.pw_scale * A.pw[n - 1]);
+                if (A.pw_comp == 0)
+                    l[0] += v;
+                else if (A.pw_comp == 1)
+                    l[1] += v;
+                else
+                    l[2] += v;
             }
         }
     }
-    // the first half step of step m (the E step's scaling first)
-    l0 = ok[0] ? ca[0] * l0 : T(0);
-    l1 = ok[1] ? ca[1] * l1 : T(0);
-    l2 = ok[2] ? ca[2] * l2 : T(0);
-    l0 = l0 + (dd[0] + dd[1]);
-    l1 = l1 + (dd[2] + dd[3]);
-    l2 = l2 + (dd[4] + dd[5]);
-    if (A.ltape && (fl & 4) && A.seg0[0] + A.m > A.loss_from) loss_term<T, 1>(A, t, q, l0, l1, l2);
-    if (A.pw && q == A.pw_slot) {
-        const long long n = A.seg0[0] + A.m;
-        if (n >= 1) {
-            const T v = (T)(A.pw_scale * A.pw[n - 1]);
-            if (A.pw_comp == 0)
-                l0 += v;
-            else if (A.pw_comp == 1)
-                l1 += v;
-            else
-                l2 += v;
+    if (PAIR) {
+        // the second half step of step m - 1
+        l[0] = l[0] + de[0];
+        l[1] = l[1] + de[1];
+        l[2] = l[2] + de[2];
+    }
+    if (!r.in) return;
+    row_st<true>(Ex, vo, l[0]);
+    row_st<true>(Ey, vo, l[1]);
+    row_st<true>(Ez, vo, l[2]);
+    if (MODE != HF_FIRST) {
+        // the E-step adjoint's input: cb lambda E' (zero on a wall or PEC edge)
+        row_st(A.mu[0] + zo, vo, ok[0] ? cb[0] * l[0] : T(0));
+        row_st(A.mu[1] + zo, vo, ok[1] ? cb[1] * l[1] : T(0));
+        row_st(A.mu[2] + zo, vo, ok[2] ? cb[2] * l[2] : T(0));
+    }
+    // lambda psiH after the map(s), of the slot's own faces (a film region's
+    // faces: the film kernels')
+    if (film_own) ax.s = ay.s = az.s = false;
+    if (ax.s) {
+        row_st(A.lpsiHo[1][0] + ax.q, ax.o, ax.pa);
+        row_st(A.lpsiHo[2][0] + ax.q, ax.o, ax.pb);
+    }
+    if (ay.s) {
+        row_st(A.lpsiHo[2][1] + ay.q, io, ay.pa);
+        row_st(A.lpsiHo[0][1] + ay.q, io, ay.pb);
+    }
+    if (az.s) {
+        row_st(A.lpsiHo[0][2] + az.q, io, az.pa);
+        row_st(A.lpsiHo[1][2] + az.q, io, az.pb);
+    }
+    if (MODE != HF_SECOND) {
+        if (A.btape) {
+            // dL/dca += lambda E' E^n, dL/dcb += lambda E' x^n over the eps box
+            // (last: its float64 values are then live with little else)
+            const int rb[3] = {A.bs[0] + 1, A.bs[1] + 1, A.bs[2] + 1};
+            int lj = j - A.bb[1], lk = k - A.bb[2], li = ic - A.bb[0];
+            if (lj < 0 && p.per[1]) lj += p.n[1];
+            if (lk < 0 && p.per[2]) lk += p.n[2];
+            if (lj >= 0 && lj < rb[1] && lk >= 0 && lk < rb[2]) { // uniform
+                if (li < 0 && p.per[0]) li += p.n[0];
+                if (li >= 0 && li < rb[0]) {
+                    const long long ri = (long long)li + (long long)rb[0] * ((long long)lj + (long long)rb[1] * lk);
+                    const long long tb = (long long)rb[0] * rb[1] * rb[2];
+                    double ga[3], gb[3], ta[3], tx[3];
+#pragma unroll
+                    for (int C = 0; C < 3; C++) {
+                        ga[C] = A.gca_box[C * tb + ri];
+                        gb[C] = A.gcb_box[C * tb + ri];
+                        ta[C] = A.btape[C * tb + ri];
+                        tx[C] = A.btape[(3 + C) * tb + ri];
+                    }
+#pragma unroll
+                    for (int C = 0; C < 3; C++) {
+                        A.gca_box[C * tb + ri] = ga[C] + (double)lp[C] * ta[C];
+                        A.gcb_box[C * tb + ri] = gb[C] + (double)lp[C] * tx[C];
+                    }
+                }
+            }
         }
     }
-    // the second half step of step m - 1
-    l0 = l0 + (de[0] + de[1]);
-    l1 = l1 + (de[2] + de[3]);
-    l2 = l2 + (de[4] + de[5]);
-    __builtin_nontemporal_store(l0, A.lE[0] + q);
-    __builtin_nontemporal_store(l1, A.lE[1] + q);
-    __builtin_nontemporal_store(l2, A.lE[2] + q);
-    A.mu[0][q] = ok[0] ? cb[0] * l0 : T(0);
-    A.mu[1][q] = ok[1] ? cb[1] * l1 : T(0);
-    A.mu[2][q] = ok[2] ? cb[2] * l2 : T(0);
 }
 
 // the loss term's lambda H part of the state at step m's start, for the film
@@ -1607,11 +1585,12 @@ __global__ void __launch_bounds__(256) k_adj_loss_h(AdjParams<T> A) {
     if (!(A.seg0[0] + A.m > A.loss_from)) return;
     const FilmDev F = film_desc(p.films, A.lfilm);
     const int r[3] = {F.cb[3] + 1, F.cb[4] + 1, F.cb[5] + 1};
-    const long long lr = (long long)blockIdx.x * 256 + threadIdx.x;
+    const unsigned lr = blockIdx.x * 256u + threadIdx.x;
     if (lr >= (long long)r[0] * r[1] * r[2]) return;
-    int t[3] = {F.cb[0] + (int)(lr % r[0]), F.cb[1] + (int)((lr / r[0]) % r[1]),
-                F.cb[2] + (int)(lr / ((long long)r[0] * r[1]))};
+    int t[3];
+    box_split(lr, r, t);
     for (int a = 0; a < 3; a++) {
+        t[a] += F.cb[a];
         if (t[a] >= p.n[a] && p.per[a]) t[a] -= p.n[a];
         if (t[a] >= p.n[a]) return;
     }
@@ -1619,273 +1598,97 @@ __global__ void __launch_bounds__(256) k_adj_loss_h(AdjParams<T> A) {
     loss_term<T, 2>(A, t, p.slot(t[0], t[1], t[2]), l0, l1, l2);
 }
 
-// the transposed half step on the E side: lambda E_C += the transposed curl
-// of the faces' curl-part adjoints (lambda E = ca lambda E' first when SCALE)
-template <typename T, int SCALE>
-__global__ void __launch_bounds__(256) k_adj_hfield(AdjParams<T> A) {
-    const KParams<T> &p = A.p;
-    const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
-    if (i >= p.n[0] || j >= p.n[1]) return;
-    const int t[3] = {i, j, k};
-    const long long q = p.slot(i, j, k);
-    const uint8_t fl = (uint8_t)adj_tile_flag(A.aflags);
-    // lambda E and the edge coefficients (one class read) before the faces
-    T l0 = A.lE[0][q], l1 = A.lE[1][q], l2 = A.lE[2][q];
-    T ca[3], cb[3];
-    bool ok[3];
-    edge_coefs<T>(p, t, q, ca, cb, ok);
-    const T ca0 = ca[0], cb0 = cb[0], ca1 = ca[1], cb1 = cb[1], ca2 = ca[2], cb2 = cb[2];
-    const bool v0 = ok[0], v1 = ok[1], v2 = ok[2];
-    // dd: the transposed curl's six differences (see hfield_general)
-    T dd[6];
-    if (fl == 0) {
-        // own faces: aD0, aD1 of each family; neighbours, named by family
-        // and the axis of the -1 offset
-        T o0[3], o1[3];
-        T n1m2 = T(0), n2m1 = T(0), n2m0 = T(0), n0m2 = T(0), n0m1 = T(0), n1m0 = T(0);
-        int u[3];
-#pragma unroll
-        for (int F = 0; F < 3; F++) {
-            const T l = A.lH[F][q];
-            o0[F] = -(p.hc * l);
-            o1[F] = p.hc * l;
-        }
-        if constexpr (sizeof(T) == 8) {
-            if (nb<-1>(p.n, p.per, t, 2, u)) n1m2 = -(p.hc * A.lH[1][p.slot(u[0], u[1], u[2])]);
-            if (nb<-1>(p.n, p.per, t, 1, u)) n2m1 = p.hc * A.lH[2][p.slot(u[0], u[1], u[2])];
-            if (nb<-1>(p.n, p.per, t, 0, u)) n2m0 = -(p.hc * A.lH[2][p.slot(u[0], u[1], u[2])]);
-            if (nb<-1>(p.n, p.per, t, 2, u)) n0m2 = p.hc * A.lH[0][p.slot(u[0], u[1], u[2])];
-            if (nb<-1>(p.n, p.per, t, 1, u)) n0m1 = -(p.hc * A.lH[0][p.slot(u[0], u[1], u[2])]);
-            if (nb<-1>(p.n, p.per, t, 0, u)) n1m0 = p.hc * A.lH[1][p.slot(u[0], u[1], u[2])];
-        } else {
-            // the neighbours' lambda H (a wall's read at the own slot and dropped)
-            bool ok2 = nb_or_self<-1>(p.n, p.per, t, 2, u);
-            const T h1m2 = A.lH[1][p.slot(u[0], u[1], u[2])], h0m2 = A.lH[0][p.slot(u[0], u[1], u[2])];
-            bool ok1 = nb_or_self<-1>(p.n, p.per, t, 1, u);
-            const T h2m1 = A.lH[2][p.slot(u[0], u[1], u[2])], h0m1 = A.lH[0][p.slot(u[0], u[1], u[2])];
-            bool ok0 = nb_or_self<-1>(p.n, p.per, t, 0, u);
-            const T h2m0 = A.lH[2][p.slot(u[0], u[1], u[2])], h1m0 = A.lH[1][p.slot(u[0], u[1], u[2])];
-            if (ok2) {
-                n1m2 = -(p.hc * h1m2);
-                n0m2 = p.hc * h0m2;
-            }
-            if (ok1) {
-                n2m1 = p.hc * h2m1;
-                n0m1 = -(p.hc * h0m1);
-            }
-            if (ok0) {
-                n2m0 = -(p.hc * h2m0);
-                n1m0 = p.hc * h1m0;
-            }
-        }
-        dd[0] = dif(n1m2 - o0[1], T(0), p.dT[2], p.invd[2]);
-        dd[1] = dif(n2m1 - o1[2], T(0), p.dT[1], p.invd[1]);
-        dd[2] = dif(n2m0 - o0[2], T(0), p.dT[0], p.invd[0]);
-        dd[3] = dif(n0m2 - o1[0], T(0), p.dT[2], p.invd[2]);
-        dd[4] = dif(n0m1 - o0[0], T(0), p.dT[1], p.invd[1]);
-        dd[5] = dif(n1m0 - o1[1], T(0), p.dT[0], p.invd[0]);
-    } else if (fl & 4) {
-        hfield_general<T, 1>(A, t, dd);
-    } else {
-        hfield_general<T, 0>(A, t, dd);
-    }
-    if (SCALE && A.btape) {
-        // dL/dca += lambda E' E^n, dL/dcb += lambda E' x^n over the eps box
-        const int r[3] = {A.bs[0] + 1, A.bs[1] + 1, A.bs[2] + 1};
-        const long long ri = region_index_folded(p.n, p.per, A.bb, r, t);
-        if (ri >= 0) {
-            const long long tb = (long long)r[0] * r[1] * r[2];
-            const T lv[3] = {l0, l1, l2};
-#pragma unroll
-            for (int C = 0; C < 3; C++) {
-                A.gca_box[C * tb + ri] += (double)lv[C] * A.btape[C * tb + ri];
-                A.gcb_box[C * tb + ri] += (double)lv[C] * A.btape[(3 + C) * tb + ri];
-            }
-        }
-    }
-    if (SCALE) {
-        l0 = v0 ? ca0 * l0 : T(0);
-        l1 = v1 ? ca1 * l1 : T(0);
-        l2 = v2 ? ca2 * l2 : T(0);
-    }
-    l0 = l0 + (dd[0] + dd[1]);
-    l1 = l1 + (dd[2] + dd[3]);
-    l2 = l2 + (dd[4] + dd[5]);
-    if (SCALE && A.ltape && (fl & 4) && A.seg0[0] + A.m > A.loss_from)
-        loss_term(A, t, q, l0, l1, l2);
-    if (SCALE && A.pw && q == A.pw_slot) {
-        // the weighted trace's term of the state at the step's start (time n)
-        const long long n = A.seg0[0] + A.m;
-        if (n >= 1) {
-            const T v = (T)(A.pw_scale * A.pw[n - 1]);
-            if (A.pw_comp == 0)
-                l0 += v;
-            else if (A.pw_comp == 1)
-                l1 += v;
-            else
-                l2 += v;
-        }
-    }
-    A.lE[0][q] = l0;
-    A.lE[1][q] = l1;
-    A.lE[2][q] = l2;
-    if (!SCALE) {
-        // the E-step adjoint's input: cb lambda E' (zero on a wall or PEC edge)
-        A.mu[0][q] = v0 ? cb0 * l0 : T(0);
-        A.mu[1][q] = v1 ? cb1 * l1 : T(0);
-        A.mu[2][q] = v2 ? cb2 * l2 : T(0);
-    }
-}
-
-// curl-part adjoints (eD0, eD1) of the E edge of family X at slot e (in the
-// domain): mu = cb lambda E' with the CPML recursions along X+1 (in1 -> out1)
-// and X+2 (in2 -> out2); own: store lambda psiE after the map.  (On a wall or
-// PEC edge mu is zero, and so stays its lambda psiE.)
-template <typename T, int X, int PML>
-__device__ __forceinline__ void eedge(const AdjParams<T> &A, const int *e, const T *in1, const T *in2, PsiOut<T> *own,
-                                      T &eD0, T &eD1) {
-    constexpr int X1 = (X + 1) % 3, X2 = (X + 2) % 3;
-    const KParams<T> &p = A.p;
-    const T *mp = A.mu[X] + p.slot(e[0], e[1], e[2]);
-    const T lx = *mp;
-    eD0 = lx;
-    eD1 = -lx;
-    if (PML) {
-        const int a1 = e[X1], a2 = e[X2];
-        const bool s1 = p.psiE[X][X1] && (a1 < p.nlo[X1] || a1 >= p.n[X1] - p.nhi[X1]);
-        const bool s2 = p.psiE[X][X2] && (a2 < p.nlo[X2] || a2 >= p.n[X2] - p.nhi[X2]);
-        if constexpr (sizeof(T) == 8) {
-            // float64: the slab state loaded where needed only (fewer registers)
-            if (s1) {
-                const long long q1 = p.psi_index(X1, e);
-                const T aps = in1[q1] + lx;
-                if (own) {
-                    own->q1 = q1;
-                    own->v1 = p.bE[X1][a1] * aps;
-                }
-                eD0 = lx + p.cE[X1][a1] * aps;
-            }
-            if (s2) {
-                const long long q2 = p.psi_index(X2, e);
-                const T aps = in2[q2] - lx;
-                if (own) {
-                    own->q2 = q2;
-                    own->v2 = p.bE[X2][a2] * aps;
-                }
-                eD1 = -lx + p.cE[X2][a2] * aps;
-            }
-        } else {
-            // float32: unconditional loads (a lane outside a slab reads mu again
-            // and drops it), so that the loads of all of a thread's edges are in
-            // flight at once
-            const long long q1 = s1 ? p.psi_index(X1, e) : 0, q2 = s2 ? p.psi_index(X2, e) : 0;
-            const T ps1 = *(s1 ? in1 + q1 : mp), ps2 = *(s2 ? in2 + q2 : mp);
-            const T b1 = *(s1 ? p.bE[X1] + a1 : mp), c1 = *(s1 ? p.cE[X1] + a1 : mp);
-            const T b2 = *(s2 ? p.bE[X2] + a2 : mp), c2 = *(s2 ? p.cE[X2] + a2 : mp);
-            if (s1) {
-                const T aps = ps1 + lx;
-                if (own) {
-                    own->q1 = q1;
-                    own->v1 = b1 * aps;
-                }
-                eD0 = lx + c1 * aps;
-            }
-            if (s2) {
-                const T aps = ps2 - lx;
-                if (own) {
-                    own->q2 = q2;
-                    own->v2 = b2 * aps;
-                }
-                eD1 = -lx + c2 * aps;
-            }
-        }
-    }
-}
-
-// a neighbour edge of family X at t + e_axis: false past a wall (values
-// zero); float32 evaluates at the own slot there and drops the values (no
-// load waits on a branch), float64 branches (fewer registers)
-template <typename T, int X, int PML>
-__device__ __forceinline__ bool eedge_nb(const AdjParams<T> &A, const int *t, int axis, const T *in1, const T *in2,
-                                         T &x0, T &x1) {
-    int u[3];
-    if constexpr (sizeof(T) == 8) {
-        if (!nb<1>(A.p.n, A.p.per, t, axis, u)) {
-            x0 = x1 = T(0);
-            return false;
-        }
-        eedge<T, X, PML>(A, u, in1, in2, nullptr, x0, x1);
-        return true;
-    } else {
-        const bool ok = nb_or_self<1>(A.p.n, A.p.per, t, axis, u);
-        eedge<T, X, PML>(A, u, in1, in2, nullptr, x0, x1);
-        return ok;
-    }
+// the curl-part adjoint of an edge from +/- mu through its CPML recursion
+template <typename T>
+__device__ __forceinline__ void adj_edge_stretch(bool s, T b, T c, T &ps, T &v) {
+    const T aps = ps + v;
+    const T w = v + c * aps, out = b * aps;
+    v = s ? w : v;
+    ps = s ? out : ps;
 }
 
 // the transposed E step on the H side: lambda H_C += the transposed curl of
-// the edges' curl-part adjoints; lambda E' itself is scaled by ca in the
-// next half-step pass
-template <typename T, int PML>
-__device__ __forceinline__ void efield_body(const AdjParams<T> &A, const int *t, long long q) {
-    const KParams<T> &p = A.p;
-    const bool par = PML ? (((A.seg0[0] + A.m) & 1) != 0) : false;
-    // lambda psiE of step n: read set n & 1, write the other (one select per
-    // pointer: indexing the parameter block through a pointer would copy it
-    // to scratch)
-    const T *i0a = par ? A.lpsiE2[0][1] : A.lpsiE[0][1], *i0b = par ? A.lpsiE2[0][2] : A.lpsiE[0][2];
-    const T *i1a = par ? A.lpsiE2[1][2] : A.lpsiE[1][2], *i1b = par ? A.lpsiE2[1][0] : A.lpsiE[1][0];
-    const T *i2a = par ? A.lpsiE2[2][0] : A.lpsiE[2][0], *i2b = par ? A.lpsiE2[2][1] : A.lpsiE[2][1];
-    // every load of the thread before any store: lambda H of the slot, then
-    // the edges (own edges' new lambda psiE held until the end; the sets read
-    // and written are different arrays)
-    // (the slot's lambda H is touched once per pass: non-temporal; the mu
-    // the neighbouring edges read again stays in L2)
-    const T lh0 = __builtin_nontemporal_load(A.lH[0] + q), lh1 = __builtin_nontemporal_load(A.lH[1] + q),
-            lh2 = __builtin_nontemporal_load(A.lH[2] + q);
-    PsiOut<T> w0, w1, w2;
-    T o0[3], o1[3], x0, x1;
-    eedge<T, 0, PML>(A, t, i0a, i0b, PML ? &w0 : nullptr, o0[0], o1[0]);
-    eedge<T, 1, PML>(A, t, i1a, i1b, PML ? &w1 : nullptr, o0[1], o1[1]);
-    eedge<T, 2, PML>(A, t, i2a, i2b, PML ? &w2 : nullptr, o0[2], o1[2]);
-    T n1p2 = T(0), n2p1 = T(0), n2p0 = T(0), n0p2 = T(0), n0p1 = T(0), n1p0 = T(0);
-    // the +1 neighbours' edges
-    if (eedge_nb<T, 1, PML>(A, t, 2, i1a, i1b, x0, x1)) n1p2 = x0;
-    if (eedge_nb<T, 0, PML>(A, t, 2, i0a, i0b, x0, x1)) n0p2 = x1;
-    if (eedge_nb<T, 2, PML>(A, t, 1, i2a, i2b, x0, x1)) n2p1 = x1;
-    if (eedge_nb<T, 0, PML>(A, t, 1, i0a, i0b, x0, x1)) n0p1 = x0;
-    if (eedge_nb<T, 2, PML>(A, t, 0, i2a, i2b, x0, x1)) n2p0 = x0;
-    if (eedge_nb<T, 1, PML>(A, t, 0, i1a, i1b, x0, x1)) n1p0 = x1;
-    if (PML) {
-        T *o0a = par ? A.lpsiE[0][1] : A.lpsiE2[0][1], *o0b = par ? A.lpsiE[0][2] : A.lpsiE2[0][2];
-        T *o1a = par ? A.lpsiE[1][2] : A.lpsiE2[1][2], *o1b = par ? A.lpsiE[1][0] : A.lpsiE2[1][0];
-        T *o2a = par ? A.lpsiE[2][0] : A.lpsiE2[2][0], *o2b = par ? A.lpsiE[2][1] : A.lpsiE2[2][1];
-        if (w0.q1 >= 0) o0a[w0.q1] = w0.v1;
-        if (w0.q2 >= 0) o0b[w0.q2] = w0.v2;
-        if (w1.q1 >= 0) o1a[w1.q1] = w1.v1;
-        if (w1.q2 >= 0) o1b[w1.q2] = w1.v2;
-        if (w2.q1 >= 0) o2a[w2.q1] = w2.v1;
-        if (w2.q2 >= 0) o2b[w2.q2] = w2.v2;
-    }
-    __builtin_nontemporal_store(
-        lh0 + (dif(o0[1] - n1p2, T(0), p.dT[2], p.invd[2]) + dif(o1[2] - n2p1, T(0), p.dT[1], p.invd[1])), A.lH[0] + q);
-    __builtin_nontemporal_store(
-        lh1 + (dif(o0[2] - n2p0, T(0), p.dT[0], p.invd[0]) + dif(o1[0] - n0p2, T(0), p.dT[2], p.invd[2])), A.lH[1] + q);
-    __builtin_nontemporal_store(
-        lh2 + (dif(o0[0] - n0p1, T(0), p.dT[1], p.invd[1]) + dif(o1[1] - n1p0, T(0), p.dT[0], p.invd[0])), A.lH[2] + q);
-}
-
-template <typename T>
+// the edges' curl-part adjoints (mu = cb lambda E'; part 0 of edge family X
+// runs along axis X + 1 with +mu, part 1 along X + 2 with -mu); lambda E'
+// itself is scaled by ca in the next half-step pass.  On a wall or PEC edge mu
+// is zero, and so stays its lambda psiE.  36 bytes a slot in float32: 133 us on
+// that grid at the rate of a copy; 234 us before the row form, 123 with it (part
+// of mu is still in the last-level cache).
+template <typename T, int TX, int TY>
 __global__ void __launch_bounds__(256) k_adj_efield(AdjParams<T> A) {
     const KParams<T> &p = A.p;
-    const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
-    if (i >= p.n[0] || j >= p.n[1]) return;
-    const int t[3] = {i, j, k};
-    const long long q = p.slot(i, j, k);
-    if (adj_tile_flag(A.aflags) & 1)
-        efield_body<T, 1>(A, t, q);
-    else
-        efield_body<T, 0>(A, t, q);
+    const RowPos r = row_pos<TX>(p.n, blockIdx.x, blockIdx.y, TY, blockIdx.z);
+    if (r.j >= p.n[1]) return;
+    const unsigned es = (unsigned)sizeof(T);
+    const int ic = min(r.i, p.n[0] - 1), j = r.j, k = r.k;
+    const long long sz = (long long)p.px * p.n[1];
+    const unsigned io = (unsigned)ic * es, rowb = (unsigned)p.px * es, vo = io + (unsigned)j * rowb;
+    const bool okx = ic + 1 < p.n[0] || p.per[0], oky = j + 1 < p.n[1] || p.per[1], okz = k + 1 < p.n[2] || p.per[2];
+    const unsigned vxp = ic + 1 < p.n[0] ? vo + es : (p.per[0] ? vo - (unsigned)(p.n[0] - 1) * es : vo);
+    const unsigned vyp = io + (unsigned)(j + 1 < p.n[1] ? j + 1 : (p.per[1] ? 0 : j)) * rowb;
+    const long long zo = k * sz, za = (k + 1 < p.n[2] ? k + 1 : (p.per[2] ? 0 : k)) * sz;
+    const T *Mx = A.mu[0] + zo, *My = A.mu[1] + zo, *Mz = A.mu[2] + zo;
+    const T x0 = row_ld(Mx, vo), x_y = row_ld(Mx, vyp), x_z = row_ld(A.mu[0] + za, vo);
+    const T y0 = row_ld(My, vo), y_x = row_ld(My, vxp), y_z = row_ld(A.mu[1] + za, vo);
+    const T z0 = row_ld(Mz, vo), z_x = row_ld(Mz, vxp), z_y = row_ld(Mz, vyp);
+    // the slot's lambda H is touched once per pass: non-temporal (the mu the
+    // neighbouring edges read again stays in L2)
+    T *Hx = A.lH[0] + zo, *Hy = A.lH[1] + zo, *Hz = A.lH[2] + zo;
+    const T h0 = row_ld<true>(Hx, vo), h1 = row_ld<true>(Hy, vo), h2 = row_ld<true>(Hz, vo);
+    // lambda psiE of step n: read set n & 1, write the other
+    const bool par = ((A.seg0[0] + A.m) & 1) != 0;
+    AdjAxis<T> ax, ay, az;
+    adj_axis_x<T, 1>(p, r, par ? A.lpsiE2[1][0] : A.lpsiE[1][0], par ? A.lpsiE2[2][0] : A.lpsiE[2][0], p.bE[0],
+                     p.cE[0], ax);
+    adj_axis_yz<T, 1, 1>(p, r, par ? A.lpsiE2[2][1] : A.lpsiE[2][1], par ? A.lpsiE2[0][1] : A.lpsiE[0][1], p.bE[1],
+                         p.cE[1], io, ay);
+    adj_axis_yz<T, 1, 2>(p, r, par ? A.lpsiE2[0][2] : A.lpsiE[0][2], par ? A.lpsiE2[1][2] : A.lpsiE[1][2], p.bE[2],
+                         p.cE[2], io, az);
+    // by edge family X and part: part 0 +mu along X + 1, part 1 -mu along X + 2
+    T o[6] = {x0, -x0, y0, -y0, z0, -z0};
+    T n[6] = {x_y, -x_z, y_z, -y_x, z_x, -z_y};
+    if (ax.s || ax.sn) {
+        adj_edge_stretch(ax.s, ax.b, ax.c, ax.pa, o[3]);
+        adj_edge_stretch(ax.s, ax.b, ax.c, ax.pb, o[4]);
+        adj_edge_stretch(ax.sn, ax.bn, ax.cn, ax.pan, n[3]);
+        adj_edge_stretch(ax.sn, ax.bn, ax.cn, ax.pbn, n[4]);
+    }
+    if (ay.s) {
+        adj_edge_stretch(true, ay.b, ay.c, ay.pa, o[5]);
+        adj_edge_stretch(true, ay.b, ay.c, ay.pb, o[0]);
+    }
+    if (ay.sn) {
+        adj_edge_stretch(true, ay.bn, ay.cn, ay.pan, n[5]);
+        adj_edge_stretch(true, ay.bn, ay.cn, ay.pbn, n[0]);
+    }
+    if (az.s) {
+        adj_edge_stretch(true, az.b, az.c, az.pa, o[1]);
+        adj_edge_stretch(true, az.b, az.c, az.pb, o[2]);
+    }
+    if (az.sn) {
+        adj_edge_stretch(true, az.bn, az.cn, az.pan, n[1]);
+        adj_edge_stretch(true, az.bn, az.cn, az.pbn, n[2]);
+    }
+    const T dx = p.dT[0], dy = p.dT[1], dz = p.dT[2], ix = p.invd[0], iy = p.invd[1], iz = p.invd[2];
+    const T d0 = dif(o[2] - (okz ? n[2] : T(0)), T(0), dz, iz) + dif(o[5] - (oky ? n[5] : T(0)), T(0), dy, iy);
+    const T d1 = dif(o[4] - (okx ? n[4] : T(0)), T(0), dx, ix) + dif(o[1] - (okz ? n[1] : T(0)), T(0), dz, iz);
+    const T d2 = dif(o[0] - (oky ? n[0] : T(0)), T(0), dy, iy) + dif(o[3] - (okx ? n[3] : T(0)), T(0), dx, ix);
+    if (!r.in) return;
+    row_st<true>(Hx, vo, h0 + d0);
+    row_st<true>(Hy, vo, h1 + d1);
+    row_st<true>(Hz, vo, h2 + d2);
+    if (ax.s) {
+        row_st((par ? A.lpsiE[1][0] : A.lpsiE2[1][0]) + ax.q, ax.o, ax.pa);
+        row_st((par ? A.lpsiE[2][0] : A.lpsiE2[2][0]) + ax.q, ax.o, ax.pb);
+    }
+    if (ay.s) {
+        row_st((par ? A.lpsiE[2][1] : A.lpsiE2[2][1]) + ay.q, io, ay.pa);
+        row_st((par ? A.lpsiE[0][1] : A.lpsiE2[0][1]) + ay.q, io, ay.pb);
+    }
+    if (az.s) {
+        row_st((par ? A.lpsiE[0][2] : A.lpsiE2[0][2]) + az.q, io, az.pa);
+        row_st((par ? A.lpsiE[1][2] : A.lpsiE2[1][2]) + az.q, io, az.pb);
+    }
 }
 
 __global__ void __launch_bounds__(256) k_copy_segs(const CopySeg *segs) {
@@ -2013,6 +1816,25 @@ hipError_t launch_adj_eps_box(const KParams<T> &p, const int *box, const double 
     return hipGetLastError();
 }
 
+// the field passes' tiles: 256 x 1 slots on the grids whose forward passes use
+// them, else 64 x 4 (the flag table is of the same shape)
+static dim3 wide_grid(const int *n) { return dim3((n[0] + kWideTX - 1) / kWideTX, n[1], n[2]); }
+
+template <typename T, int MODE>
+static void launch_hfield(const AdjParams<T> &A, hipStream_t s) {
+    if (A.wide)
+        k_adj_hfield<T, MODE, kWideTX, kWideTY><<<wide_grid(A.p.n), dim3(kWideTX, kWideTY), 0, s>>>(A);
+    else
+        k_adj_hfield<T, MODE, 64, 4><<<slot_grid(A.p.n), dim3(64, 4), 0, s>>>(A);
+}
+
+template <typename T>
+hipError_t launch_adj_loss_weights(const KParams<T> &p, int film, double *dst, hipStream_t s, const int *cb) {
+    const long long tb = film_tape_size(cb) / 6;
+    k_adj_loss_weights<T><<<dim3((unsigned)((tb + 255) / 256)), dim3(256), 0, s>>>(p, film, dst);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_adj_half_fused(const AdjParams<T> &A, int nblk, int scale, const long long *film_nr,
                                  hipStream_t s) {
@@ -2021,9 +1843,9 @@ hipError_t launch_adj_half_fused(const AdjParams<T> &A, int nblk, int scale, con
         if (film_nr[f] > 0)
             k_adj_film_faces<T><<<dim3((unsigned)((film_nr[f] + 255) / 256), 3), dim3(256), 0, s>>>(A, f);
     if (scale)
-        k_adj_hfield<T, 1><<<slot_grid(A.p.n), dim3(64, 4), 0, s>>>(A);
+        launch_hfield<T, HF_FIRST>(A, s);
     else
-        k_adj_hfield<T, 0><<<slot_grid(A.p.n), dim3(64, 4), 0, s>>>(A);
+        launch_hfield<T, HF_SECOND>(A, s);
     return hipGetLastError();
 }
 
@@ -2040,7 +1862,7 @@ hipError_t launch_adj_film_part(const AdjParams<T> &A, int nblk, const long long
 
 template <typename T>
 hipError_t launch_adj_hfield2(const AdjParams<T> &A, hipStream_t s) {
-    k_adj_hfield2<T><<<slot_grid(A.p.n), dim3(64, 4), 0, s>>>(A);
+    launch_hfield<T, HF_PAIR>(A, s);
     return hipGetLastError();
 }
 
@@ -2053,7 +1875,10 @@ hipError_t launch_adj_loss_h(const AdjParams<T> &A, const int *film_cb, hipStrea
 
 template <typename T>
 hipError_t launch_adj_estep_fused(const AdjParams<T> &A, hipStream_t s) {
-    k_adj_efield<T><<<slot_grid(A.p.n), dim3(64, 4), 0, s>>>(A);
+    if (A.wide)
+        k_adj_efield<T, kWideTX, kWideTY><<<wide_grid(A.p.n), dim3(kWideTX, kWideTY), 0, s>>>(A);
+    else
+        k_adj_efield<T, 64, 4><<<slot_grid(A.p.n), dim3(64, 4), 0, s>>>(A);
     return hipGetLastError();
 }
 
@@ -2085,6 +1910,7 @@ hipError_t launch_copy_segs(const CopySeg *segs, int nseg, int nblk, hipStream_t
     template hipError_t launch_adj_estep_fused<T>(const AdjParams<T> &, hipStream_t);                           \
     template hipError_t launch_adj_film_part<T>(const AdjParams<T> &, int, const long long *, hipStream_t);     \
     template hipError_t launch_adj_hfield2<T>(const AdjParams<T> &, hipStream_t);                               \
+    template hipError_t launch_adj_loss_weights<T>(const KParams<T> &, int, double *, hipStream_t, const int *); \
     template hipError_t launch_adj_loss_h<T>(const AdjParams<T> &, const int *, hipStream_t);                    \
     template hipError_t launch_add_one<T>(T *, long long, double, hipStream_t);                                 \
     template hipError_t launch_tape_loss<T>(const KParams<T> &, int, int, double *, hipStream_t, const int *);   \

@@ -1074,6 +1074,7 @@ struct AdjHost {
     long long *d_seg0 = nullptr;                 // tape schedule: first step of the segment in hand
     void *lpsiH2[3][3] = {}, *lpsiE2[3][3] = {};  // tape schedule: second lambda psi sets
     uint8_t *d_aflags = nullptr;
+    double *d_lw = nullptr; // tape schedule: the film-energy gradient's weights
     void *mu[3] = {};
     std::vector<double *> aDr, aDr2; // per film: the reach's curl-part table of each half step of a step
     std::vector<long long> film_nr;
@@ -1110,6 +1111,7 @@ void adj_free(AdjHost &h) {
             (void)hipFree(h.lpsiE2[c][a]);
         }
     (void)hipFree(h.d_aflags);
+    (void)hipFree(h.d_lw);
     for (int c = 0; c < 3; c++) (void)hipFree(h.mu[c]);
     for (double *d : h.aDr) (void)hipFree(d);
     for (double *d : h.aDr2) (void)hipFree(d);
@@ -1642,6 +1644,7 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
     char *pages = nullptr; // the tapes kept from the forward run
     bool probe_added = false;
     double *d_lacc = nullptr; // the film-energy loss's own eps_r term per film cell
+    const bool adj_wide = s->n[0] >= kWideMinNx; // the field passes' tile shape
     bool merge = s->adj_schedule == 0; // one field pass for the two half-step transposes around an integer time
     auto body = [&]() -> mpx_status {
         mpx_status q;
@@ -1691,30 +1694,23 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
             g.aDr = d;
             h.film_nr.push_back(nr);
         }
-        // per-tile flags of the field passes: 1 CPML, 4 a film's reach, each
-        // within two slots of the tile
+        // per-tile flags of the field passes: 4, a film's reach within two
+        // slots of the tile
         {
-            const int nxt = (s->n[0] + kPassTX - 1) / kPassTX, nyt = (s->n[1] + kPassTY - 1) / kPassTY;
-            const int nt = pass_tiles(s->n);
-            std::vector<uint8_t> fl(nt, 0);
-            for (int t = 0; t < nt; t++) {
-                const int i0 = (t % nxt) * kPassTX, j0 = ((t / nxt) % nyt) * kPassTY, k = t / (nxt * nyt);
-                const int lo[3] = {i0 - 2, j0 - 2, k - 2}, hi[3] = {i0 + kPassTX + 1, j0 + kPassTY + 1, k + 2};
-                uint8_t fv = 0;
-                for (int a = 0; a < 3; a++) {
-                    if (s->nlo[a] > 0 && lo[a] < s->nlo[a]) fv |= 1;
-                    if (s->nhi[a] > 0 && hi[a] >= s->n[a] - s->nhi[a]) fv |= 1;
-                }
-                for (auto &g : h.af) {
-                    bool in = true;
-                    for (int a = 0; a < 3; a++)
-                        if (g.r0[a] + g.rn[a] <= lo[a] || g.r0[a] > hi[a]) in = false;
-                    if (in) fv |= 4;
-                }
-                fl[t] = fv;
+            const int tx = adj_wide ? kWideTX : kPassTX, ty = adj_wide ? kWideTY : kPassTY;
+            const int nxt = (s->n[0] + tx - 1) / tx, nyt = (s->n[1] + ty - 1) / ty;
+            std::vector<uint8_t> fl((size_t)nxt * nyt * s->n[2], 0);
+            for (auto &g : h.af) {
+                // tiles whose grown range [t - 2, t + size + 1] meets the reach
+                const int x0 = std::max(0, (g.r0[0] - 1 - tx) / tx), x1 = std::min(nxt - 1, (g.r0[0] + g.rn[0] + 1) / tx);
+                const int y0 = std::max(0, (g.r0[1] - 1 - ty) / ty), y1 = std::min(nyt - 1, (g.r0[1] + g.rn[1] + 1) / ty);
+                const int z0 = std::max(0, g.r0[2] - 2), z1 = std::min(s->n[2] - 1, g.r0[2] + g.rn[2] + 1);
+                for (int k = z0; k <= z1; k++)
+                    for (int y = y0; y <= y1; y++)
+                        for (int x = x0; x <= x1; x++) fl[x + (size_t)nxt * (y + (size_t)nyt * k)] = 4;
             }
-            CK(hipMalloc(&h.d_aflags, ((size_t)nt + 4) / 4 * 4)); // whole words (read through the scalar cache)
-            CK(hipMemcpy(h.d_aflags, fl.data(), nt, hipMemcpyHostToDevice));
+            CK(hipMalloc(&h.d_aflags, (fl.size() + 4) / 4 * 4)); // whole words (read through the scalar cache)
+            CK(hipMemcpy(h.d_aflags, fl.data(), fl.size(), hipMemcpyHostToDevice));
         }
         // the merged reverse pass needs the films' reaches off the CPML slabs
         // (their faces keep no CPML state between half steps)
@@ -1761,6 +1757,12 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
             CK(hipMemsetAsync(h.gbox_b, 0, gb, st));
         }
         CK(hipMalloc(&h.d_seg0, sizeof(long long)));
+        if (floss) {
+            KParams<T> p;
+            fill_params<T>(s, p, MODE_INPLACE, s->parity);
+            CK(hipMalloc(&h.d_lw, film_tape_size(LF.cb) * sizeof(double)));
+            CK(launch_adj_loss_weights<T>(p, film, h.d_lw, st, LF.cb));
+        }
         if ((q = tape_alloc(s, tp, K, LF.cb, eps_box)) != MPX_OK) return q;
         const SnapLayout L = snap_layout(s);
         // the last npage segments keep the tape their forward run writes (a
@@ -1963,6 +1965,8 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
             AdjParams<T> A;
             adj_params<T>(s, h, A);
             A.aflags = h.d_aflags;
+            A.wide = adj_wide ? 1 : 0;
+            A.lw = h.d_lw;
             A.seg0 = h.d_seg0;
             A.m = m;
             A.btape = neps > 0 ? tp.boxp(m) : nullptr;

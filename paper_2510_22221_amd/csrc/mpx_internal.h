@@ -204,8 +204,7 @@ struct AdjParams {
     const AdjFilmDev *afb;
     // fused schedule: destination set of lambda psiH (read from lpsiH), the
     // second lambda psiE set (the E-step adjoint of step n reads set n & 1
-    // and writes the other), per-tile flags (1 CPML, 4 film reach, with a
-    // two-slot halo), the segment's first step on the device, the step's
+    // and writes the other), the segment's first step on the device, the step's
     // index in the segment
     T *lpsiHo[3][3];
     T *lpsiE2[3][3];
@@ -226,7 +225,12 @@ struct AdjParams {
     long long pw_slot = -1;
     int pw_comp = 0;
     double pw_scale = 1.0;
+    // the weights of the film-energy gradient over the loss film's region
+    const double *lw = nullptr;
+    // per tile of the field passes (256 x 1 slots when wide, else 64 x 4):
+    // 4 = a film's reach within two slots
     const uint8_t *aflags;
+    int wide = 0;
     const long long *seg0;
     int m;
 };
@@ -262,6 +266,8 @@ hipError_t launch_adj_half_fused(const AdjParams<T> &A, int nblk, int scale, con
 template <typename T>
 hipError_t launch_adj_film_part(const AdjParams<T> &A, int nblk, const long long *film_nr, hipStream_t s);
 template <typename T> hipError_t launch_adj_hfield2(const AdjParams<T> &A, hipStream_t s);
+template <typename T>
+hipError_t launch_adj_loss_weights(const KParams<T> &p, int film, double *dst, hipStream_t s, const int *cb);
 template <typename T> hipError_t launch_adj_loss_h(const AdjParams<T> &A, const int *film_cb, hipStream_t s);
 template <typename T> hipError_t launch_adj_estep_fused(const AdjParams<T> &A, hipStream_t s);
 template <typename T> hipError_t launch_adj_estep(const AdjParams<T> &A, hipStream_t s);
