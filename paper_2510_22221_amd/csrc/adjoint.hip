@@ -647,27 +647,6 @@ __global__ void k_accum(const double *part, int n, double *acc, double scale) {
 // tape schedule
 // ---------------------------------------------------------------------------
 
-// A region of slots [b0, b0 + r) (a cell box grown by one slot on the high
-// side of each axis: the edges and faces of its cells).  Thread t owns the
-// slot of region index t after folding; a slot that the fold maps onto an
-// index the region already holds (a box spanning a periodic axis) belongs to
-// that index.  Returns false for no slot or a slot owned elsewhere.
-__device__ __forceinline__ bool region_slot(const int *n, const int *per, const int *b0, const int *r, unsigned t,
-                                            int *q) {
-    int loc[3];
-    box_split(t, r, loc);
-    for (int a = 0; a < 3; a++) {
-        int v = b0[a] + loc[a];
-        if (v >= n[a]) {
-            if (!per[a]) return false;
-            v -= n[a];
-            if (v >= b0[a]) return false;
-        }
-        q[a] = v;
-    }
-    return true;
-}
-
 // region index of the slot e (unfolded, inside [b0, b0 + r) or its wrap), -1
 // for no slot
 __device__ __forceinline__ long long region_index(const int *n, const int *per, const int *b0, const int *r,
@@ -685,67 +664,9 @@ __device__ __forceinline__ long long region_index(const int *n, const int *per, 
     return (long long)loc[0] + (long long)r[0] * ((long long)loc[1] + (long long)r[1] * loc[2]);
 }
 
-// the film's E and H at an integer time over its cell box grown by one slot:
-// [6][region] (Ex, Ey, Ez, Hx, Hy, Hz).  merged = 1: between the two film half
-// steps of a merged pair (magnetic faces' H in the film's staging, bulk faces'
-// H one bulk half step ahead of the stored H); 0: a state at an integer time.
-// No other film's faces lie in the region (films are at least two cells
-// apart); every load goes out at once, what a face does not use is dropped.
 template <typename T>
 __global__ void __launch_bounds__(256) k_tape_loss(KParams<T> p, int film, int merged, double *dst) {
-    const FilmDev F = film_desc(p.films, film);
-    const int b0[3] = {F.cb[0], F.cb[1], F.cb[2]}, r[3] = {F.cb[3] + 1, F.cb[4] + 1, F.cb[5] + 1};
-    const long long tb = (long long)r[0] * r[1] * r[2];
-    const unsigned t = blockIdx.x * 256u + threadIdx.x;
-    if (t >= tb) return;
-    int q[3];
-    if (!region_slot(p.n, p.per, b0, r, t, q)) {
-        for (int w = 0; w < 6; w++) dst[w * tb + t] = 0.0;
-        return;
-    }
-    const long long sl = p.slot(q[0], q[1], q[2]);
-    // the +1 neighbours along each axis (zero past a wall)
-    long long su[3];
-    bool ok[3];
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        int u[3] = {q[0], q[1], q[2]};
-        u[a] = fold(q[a] + 1, p.n[a], p.per[a]);
-        ok[a] = u[a] >= 0;
-        su[a] = ok[a] ? p.slot(u[0], u[1], u[2]) : sl;
-    }
-    T e[3], h[3], eu[3][3];
-    double h1[3] = {0.0, 0.0, 0.0}, ms[3] = {0.0, 0.0, 0.0};
-    bool inside = false;
-    long long l = 0;
-    if (merged && p.nfilm) l = film_local<T>(F, q, inside);
-#pragma unroll
-    for (int C = 0; C < 3; C++) {
-        e[C] = p.E[C][sl];
-        h[C] = p.H[C][sl];
-        if (merged) {
-            // E_C at +1 along the other two axes
-            eu[C][(C + 1) % 3] = p.E[C][su[(C + 1) % 3]];
-            eu[C][(C + 2) % 3] = p.E[C][su[(C + 2) % 3]];
-            if (p.nfilm) {
-                h1[C] = F.H1[C * F.ns + l];
-                ms[C] = F.prm[(C * 3) * F.ns + l];
-            }
-        }
-    }
-#pragma unroll
-    for (int C = 0; C < 3; C++) {
-        dst[C * tb + t] = (double)e[C];
-        double hv = (double)h[C];
-        if (merged) {
-            const int C1 = (C + 1) % 3, C2 = (C + 2) % 3;
-            const T d1 = dif(ok[C1] ? eu[C2][C1] : T(0), e[C2], p.dT[C1], p.invd[C1]);
-            const T d2 = dif(ok[C2] ? eu[C1][C2] : T(0), e[C1], p.dT[C2], p.invd[C2]);
-            hv = (double)(h[C] - p.hc * (d1 - d2));
-            if (inside && ms[C] > 0.0) hv = h1[C];
-        }
-        dst[(3 + C) * tb + t] = hv;
-    }
+    tape_loss_body(p, film, merged, dst, blockIdx.x);
 }
 
 // the loss term of the state a tape slot holds: scale x the gradient of the
@@ -850,60 +771,6 @@ __global__ void __launch_bounds__(256) k_adj_loss_eps_state(KParams<T> p, int fi
         we += e2 / 4.0;
     }
     acc[t] += scale * 0.5 * p.eps0 * p.dV * we;
-}
-
-// E^n and x^n = (d1 + psi1') - (d2 + psi2') - J^n (the E update's input, H at
-// n + 1/2) over the edges of a cell box: [6][region] (E0..2, x0..2); taken
-// just before the E pass
-template <typename T>
-__global__ void __launch_bounds__(256) k_tape_box(KParams<T> p, int4 bb, int4 bs, double *dst) {
-    const int b0[3] = {bb.x, bb.y, bb.z}, r[3] = {bs.x + 1, bs.y + 1, bs.z + 1};
-    const long long tb = (long long)r[0] * r[1] * r[2];
-    const unsigned t = blockIdx.x * 256u + threadIdx.x;
-    if (t >= tb) return;
-    int q[3];
-    if (!region_slot(p.n, p.per, b0, r, t, q)) {
-        for (int w = 0; w < 6; w++) dst[w * tb + t] = 0.0;
-        return;
-    }
-    const long long sl = p.slot(q[0], q[1], q[2]);
-    const long long step = p.step[0];
-    // H at the slot and at its -1 neighbours (zero past a wall), all at once
-    T h0[3], hm[3][3], e0[3];
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        int u[3] = {q[0], q[1], q[2]};
-        u[a] = fold(q[a] - 1, p.n[a], p.per[a]);
-        const bool ok = u[a] >= 0;
-        const long long su = ok ? p.slot(u[0], u[1], u[2]) : sl;
-        const T x1 = p.H[(a + 1) % 3][su], x2 = p.H[(a + 2) % 3][su];
-        hm[(a + 1) % 3][a] = ok ? x1 : T(0);
-        hm[(a + 2) % 3][a] = ok ? x2 : T(0);
-        h0[a] = p.H[a][sl];
-        e0[a] = p.E[a][sl];
-    }
-#pragma unroll
-    for (int C = 0; C < 3; C++) {
-        const int C1 = (C + 1) % 3, C2 = (C + 2) % 3;
-        T d1 = dif(h0[C2], hm[C2][C1], p.dT[C1], p.invd[C1]);
-        T d2 = dif(h0[C1], hm[C1][C2], p.dT[C2], p.invd[C2]);
-        const int a1 = q[C1], a2 = q[C2];
-        if (p.psiE[C][C1] && (a1 < p.nlo[C1] || a1 >= p.n[C1] - p.nhi[C1]))
-            d1 += p.bE[C1][a1] * p.psiE[C][C1][p.psi_index(C1, q)] + p.cE[C1][a1] * d1;
-        if (p.psiE[C][C2] && (a2 < p.nlo[C2] || a2 >= p.n[C2] - p.nhi[C2]))
-            d2 += p.bE[C2][a2] * p.psiE[C][C2][p.psi_index(C2, q)] + p.cE[C2][a2] * d2;
-        double J = 0.0;
-        for (int s = 0; s < p.nsrc; s++) {
-            const SrcDev &S = p.srcs[s];
-            if (S.comp != C) continue;
-            if (q[0] < S.box[0] || q[0] >= S.box[0] + S.box[3] || q[1] < S.box[1] || q[1] >= S.box[1] + S.box[4] ||
-                q[2] < S.box[2] || q[2] >= S.box[2] + S.box[5])
-                continue;
-            if (step < S.n) J += S.table[step];
-        }
-        dst[C * tb + t] = (double)e0[C];
-        dst[(3 + C) * tb + t] = (double)(d1 - d2) - J;
-    }
 }
 
 // dL/d eps_r of the box's cells from the box accumulators (eps of an edge:
@@ -1062,13 +929,42 @@ __device__ __forceinline__ int first_region(const AdjParams<T> &A, const int *id
     return -1;
 }
 
+// region index of the folded slot t in the region [b0, b0 + r) (which may
+// wrap on a periodic axis), -1 outside
+__device__ __forceinline__ long long region_index_folded(const int *n, const int *per, const int *b0, const int *r,
+                                                         const int *t) {
+    long long li = 0, mul = 1;
+    for (int a = 0; a < 3; a++) {
+        int loc = t[a] - b0[a];
+        if (loc < 0 && per[a]) loc += n[a];
+        if (loc < 0 || loc >= r[a]) return -1;
+        li += mul * loc;
+        mul *= r[a];
+    }
+    return li;
+}
+
+// the loss term's lambda H part (film-energy gradient of the state at the
+// step's start, scaled) of the face of family C at slot idx, zero off the
+// film's cells; used where the merged field pass takes the lambda E part
+template <typename T>
+__device__ __forceinline__ T face_loss(const AdjParams<T> &A, int C, const int *idx) {
+    const KParams<T> &p = A.p;
+    const FilmDev F = film_desc(p.films, A.lfilm);
+    const int b0[3] = {F.cb[0], F.cb[1], F.cb[2]}, r[3] = {F.cb[3] + 1, F.cb[4] + 1, F.cb[5] + 1};
+    const long long ri = region_index_folded(p.n, p.per, b0, r, idx);
+    const long long tb = (long long)r[0] * r[1] * r[2], o = (3 + C) * tb + (ri < 0 ? 0 : ri);
+    const double nc = A.lw[o], x = A.ltape[o];
+    return ri < 0 || nc == 0.0 ? T(0) : (T)(A.lscale * p.dV * p.mu0 * 0.5 * nc * x);
+}
+
 // adj_face_core for a face of family C at slot idx inside the reach of film F
 // that no other film's reach meets (G.alone), off the CPML slabs: only this
 // film's faces matter, and every load goes out at once (a face outside the
 // face box reads its element 0, and what it does not use is dropped)
 template <typename T, int C>
 __device__ __forceinline__ void adj_face_alone(const AdjParams<T> &A, const FilmDev &F, const AdjFilmDev &G,
-                                               const int *idx, T &ad0, T &ad1) {
+                                               const int *idx, T loss, T &ad0, T &ad1) {
     const KParams<T> &p = A.p;
     const long long q = p.slot(idx[0], idx[1], idx[2]);
     double lHp = (double)A.lH[C][q];
@@ -1129,12 +1025,12 @@ __device__ __forceinline__ void adj_face_alone(const AdjParams<T> &A, const Film
     if (mag) {
         const double lbs = lHp + lbs_f;
         const double lbt = lbn + lbs;
-        A.lH[C][q] = (T)lbt;
+        A.lH[C][q] = (T)lbt + loss;
         G.lMout[(C * 3 + C) * F.ns + lm] = omo + lbt;
         ad0 = (T)(-p.hcd * lbs);
         ad1 = (T)(p.hcd * lbs);
     } else {
-        A.lH[C][q] = (T)(lHp + lbn + lbs_f);
+        A.lH[C][q] = (T)(lHp + lbn + lbs_f) + loss;
         ad0 = (T)(-(double)p.hc * lHp - p.hcd * lbs_f);
         ad1 = (T)((double)p.hc * lHp + p.hcd * lbs_f);
     }
@@ -1157,15 +1053,16 @@ __global__ void __launch_bounds__(256) k_adj_film_faces(AdjParams<T> A, int f) {
     box_split(lr, G.rn, idx);
     for (int a = 0; a < 3; a++) idx[a] += G.r0[a];
     // one face family per grid row
-    T a0, a1;
+    T a0, a1, loss = T(0);
     const int F = blockIdx.y;
+    if (A.loss_h && A.seg0[0] + A.m > A.loss_from) loss = face_loss(A, F, idx);
     if (G.alone) {
         if (F == 0)
-            adj_face_alone<T, 0>(A, FD, G, idx, a0, a1);
+            adj_face_alone<T, 0>(A, FD, G, idx, loss, a0, a1);
         else if (F == 1)
-            adj_face_alone<T, 1>(A, FD, G, idx, a0, a1);
+            adj_face_alone<T, 1>(A, FD, G, idx, loss, a0, a1);
         else
-            adj_face_alone<T, 2>(A, FD, G, idx, a0, a1);
+            adj_face_alone<T, 2>(A, FD, G, idx, loss, a0, a1);
         G.aDr[(2 * F) * G.nr + lr] = (double)a0;
         G.aDr[(2 * F + 1) * G.nr + lr] = (double)a1;
         return;
@@ -1178,23 +1075,9 @@ __global__ void __launch_bounds__(256) k_adj_film_faces(AdjParams<T> A, int f) {
         adj_face_core<T, 1>(A, idx, A.lpsiH[1][2], A.lpsiH[1][0], A.lpsiHo[1][2], A.lpsiHo[1][0], a0, a1);
     else
         adj_face_core<T, 2>(A, idx, A.lpsiH[2][0], A.lpsiH[2][1], A.lpsiHo[2][0], A.lpsiHo[2][1], a0, a1);
+    if (loss != T(0)) A.lH[F][A.p.slot(idx[0], idx[1], idx[2])] += loss;
     G.aDr[(2 * F) * G.nr + lr] = (double)a0;
     G.aDr[(2 * F + 1) * G.nr + lr] = (double)a1;
-}
-
-// region index of the folded slot t in the region [b0, b0 + r) (which may
-// wrap on a periodic axis), -1 outside
-__device__ __forceinline__ long long region_index_folded(const int *n, const int *per, const int *b0, const int *r,
-                                                         const int *t) {
-    long long li = 0, mul = 1;
-    for (int a = 0; a < 3; a++) {
-        int loc = t[a] - b0[a];
-        if (loc < 0 && per[a]) loc += n[a];
-        if (loc < 0 || loc >= r[a]) return -1;
-        li += mul * loc;
-        mul *= r[a];
-    }
-    return li;
 }
 
 // the weights of the film-energy gradient over the loss film's region (its
@@ -1239,7 +1122,7 @@ __global__ void __launch_bounds__(256) k_adj_loss_weights(KParams<T> p, int film
 // gradient, scaled) for the slot t: added to its three lambda E values (in
 // registers) and to lambda H of its three faces (film faces: no other thread
 // of the pass reads them)
-// (PART: 0 both terms, 1 the lambda E term only, 2 the lambda H term only)
+// (PART: 0 both terms, 1 the lambda E term only)
 template <typename T, int PART = 0>
 __device__ __forceinline__ void loss_term(const AdjParams<T> &A, const int *t, long long q, T &l0, T &l1, T &l2) {
     const KParams<T> &p = A.p;
@@ -1251,7 +1134,7 @@ __device__ __forceinline__ void loss_term(const AdjParams<T> &A, const int *t, l
     T le[3] = {l0, l1, l2};
 #pragma unroll
     for (int C = 0; C < 3; C++) {
-        if (PART != 2) {
+        {
             const double se = A.lw[C * tb + ri], x = A.ltape[C * tb + ri];
             const T v = (T)(A.lscale * p.dV * p.eps0 * se * 0.25 * x);
             le[C] = se != 0.0 ? le[C] + v : le[C];
@@ -1577,27 +1460,6 @@ __global__ void __launch_bounds__(256) k_adj_hfield(AdjParams<T> A) {
     }
 }
 
-// the loss term's lambda H part of the state at step m's start, for the film
-// region's faces (before the film kernels of the next half step read them)
-template <typename T>
-__global__ void __launch_bounds__(256) k_adj_loss_h(AdjParams<T> A) {
-    const KParams<T> &p = A.p;
-    if (!(A.seg0[0] + A.m > A.loss_from)) return;
-    const FilmDev F = film_desc(p.films, A.lfilm);
-    const int r[3] = {F.cb[3] + 1, F.cb[4] + 1, F.cb[5] + 1};
-    const unsigned lr = blockIdx.x * 256u + threadIdx.x;
-    if (lr >= (long long)r[0] * r[1] * r[2]) return;
-    int t[3];
-    box_split(lr, r, t);
-    for (int a = 0; a < 3; a++) {
-        t[a] += F.cb[a];
-        if (t[a] >= p.n[a] && p.per[a]) t[a] -= p.n[a];
-        if (t[a] >= p.n[a]) return;
-    }
-    T l0 = T(0), l1 = T(0), l2 = T(0);
-    loss_term<T, 2>(A, t, p.slot(t[0], t[1], t[2]), l0, l1, l2);
-}
-
 // the curl-part adjoint of an edge from +/- mu through its CPML recursion
 template <typename T>
 __device__ __forceinline__ void adj_edge_stretch(bool s, T b, T c, T &ps, T &v) {
@@ -1799,14 +1661,6 @@ hipError_t launch_adj_loss_eps_state(const KParams<T> &p, int film, double scale
 }
 
 template <typename T>
-hipError_t launch_tape_box(const KParams<T> &p, const int *box, double *dst, hipStream_t s) {
-    const long long tb = box_tape_size(box) / 6;
-    k_tape_box<T><<<dim3((unsigned)((tb + 255) / 256)), dim3(256), 0, s>>>(
-        p, make_int4(box[0], box[1], box[2], 0), make_int4(box[3], box[4], box[5], 0), dst);
-    return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_adj_eps_box(const KParams<T> &p, const int *box, const double *gca, const double *gcb, double *out,
                               hipStream_t s) {
     const long long nc = (long long)box[3] * box[4] * box[5];
@@ -1867,13 +1721,6 @@ hipError_t launch_adj_hfield2(const AdjParams<T> &A, hipStream_t s) {
 }
 
 template <typename T>
-hipError_t launch_adj_loss_h(const AdjParams<T> &A, const int *film_cb, hipStream_t s) {
-    const long long nr = (long long)(film_cb[3] + 1) * (film_cb[4] + 1) * (film_cb[5] + 1);
-    if (nr > 0) k_adj_loss_h<T><<<dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, s>>>(A);
-    return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_adj_estep_fused(const AdjParams<T> &A, hipStream_t s) {
     if (A.wide)
         k_adj_efield<T, kWideTX, kWideTY><<<wide_grid(A.p.n), dim3(kWideTX, kWideTY), 0, s>>>(A);
@@ -1911,12 +1758,10 @@ hipError_t launch_copy_segs(const CopySeg *segs, int nseg, int nblk, hipStream_t
     template hipError_t launch_adj_film_part<T>(const AdjParams<T> &, int, const long long *, hipStream_t);     \
     template hipError_t launch_adj_hfield2<T>(const AdjParams<T> &, hipStream_t);                               \
     template hipError_t launch_adj_loss_weights<T>(const KParams<T> &, int, double *, hipStream_t, const int *); \
-    template hipError_t launch_adj_loss_h<T>(const AdjParams<T> &, const int *, hipStream_t);                    \
     template hipError_t launch_add_one<T>(T *, long long, double, hipStream_t);                                 \
     template hipError_t launch_tape_loss<T>(const KParams<T> &, int, int, double *, hipStream_t, const int *);   \
     template hipError_t launch_adj_loss_tape<T>(const AdjParams<T> &, int, double, const double *,              \
                                                 const long long *, int, long long, hipStream_t, const int *);   \
-    template hipError_t launch_tape_box<T>(const KParams<T> &, const int *, double *, hipStream_t);             \
     template hipError_t launch_adj_loss_eps_tape<T>(const KParams<T> &, int, double, const double *,             \
                                                     const long long *, int, long long, double *, hipStream_t,    \
                                                     const int *);                                                \

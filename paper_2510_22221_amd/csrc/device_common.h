@@ -128,14 +128,36 @@ __device__ __forceinline__ void block_order_sums3(const double *part, const int 
     }
 }
 
+// the same for one run of n >= 1 partials
+__device__ __forceinline__ double block_order_sum(const double *part, int n) {
+    const int t = (int)threadIdx.x; // 0..63
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int base = t; base < n; base += 256)
+        for (int q = 0; q < 4; q++) {
+            const int b = base + 64 * q;
+            const double x = part[b < n ? b : n - 1];
+            s[q] = b < n ? s[q] + x : s[q];
+        }
+    double r = (s[0] + s[2]) + (s[1] + s[3]); // levels 128 and 64
+    for (int st = 32; st > 0; st >>= 1) {
+        const double o = __shfl_down(r, st, 64);
+        if (t < st) r = r + o;
+    }
+    return r;
+}
+
 // the values of such a probe in the merged H/M launch's probe block, formed
 // by its first wavefront (the others take no part): the E component at its
-// site, or the film's mean M from its film blocks' partial sums in block
-// order; valid in lane 0
+// site, the film's mean M from its film blocks' partial sums in block order,
+// or the film's energy from its own partials; valid in lane 0
 template <typename T>
-__device__ __forceinline__ void probe_e_or_m_values(const KParams<T> &p, const ProbeDev &P, double *v) {
+__device__ __forceinline__ void folded_probe_values(const KParams<T> &p, const ProbeDev &P, double *v) {
     if (P.kind == 0) {
         if (threadIdx.x == 0) v[0] = (double)ldz(p, p.E[P.field], P.i, P.j, P.k);
+        return;
+    }
+    if (P.kind == 2) {
+        v[0] = block_order_sum(P.part, (int)P.npart) * p.dV;
         return;
     }
     const FilmDev &F = p.films[P.film];

@@ -233,4 +233,88 @@ __device__ __forceinline__ void film_commit_body(const KParams<T> &p, int blk, i
     p.Hw[c][p.slot(F.b0[0] + r[0], F.b0[1] + r[1], F.b0[2] + r[2])] = (T)h;
 }
 
+// A region of slots [b0, b0 + r) (a cell box grown by one slot on the high
+// side of each axis: the edges and faces of its cells).  Thread t owns the
+// slot of region index t after folding; a slot that the fold maps onto an
+// index the region already holds (a box spanning a periodic axis) belongs to
+// that index.  Returns false for no slot or a slot owned elsewhere.
+__device__ __forceinline__ bool region_slot(const int *n, const int *per, const int *b0, const int *r, unsigned t,
+                                            int *q) {
+    int loc[3];
+    box_split(t, r, loc);
+    for (int a = 0; a < 3; a++) {
+        int v = b0[a] + loc[a];
+        if (v >= n[a]) {
+            if (!per[a]) return false;
+            v -= n[a];
+            if (v >= b0[a]) return false;
+        }
+        q[a] = v;
+    }
+    return true;
+}
+
+// the film's E and H at an integer time over its cell box grown by one slot:
+// [6][region] (Ex, Ey, Ez, Hx, Hy, Hz).  merged = 1: between the two film half
+// steps of a merged pair (magnetic faces' H in the film's staging, bulk faces'
+// H one bulk half step ahead of the stored H); 0: a state at an integer time.
+// No other film's faces lie in the region (films are at least two cells
+// apart); every load goes out at once, what a face does not use is dropped.
+template <typename T>
+__device__ __forceinline__ void tape_loss_body(const KParams<T> &p, int film, int merged, double *dst, unsigned blk) {
+    const FilmDev F = film_desc(p.films, film);
+    const int b0[3] = {F.cb[0], F.cb[1], F.cb[2]}, r[3] = {F.cb[3] + 1, F.cb[4] + 1, F.cb[5] + 1};
+    const long long tb = (long long)r[0] * r[1] * r[2];
+    const unsigned t = blk * 256u + threadIdx.x;
+    if (t >= tb) return;
+    int q[3];
+    if (!region_slot(p.n, p.per, b0, r, t, q)) {
+        for (int w = 0; w < 6; w++) dst[w * tb + t] = 0.0;
+        return;
+    }
+    const long long sl = p.slot(q[0], q[1], q[2]);
+    // the +1 neighbours along each axis (zero past a wall)
+    long long su[3];
+    bool ok[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        int u[3] = {q[0], q[1], q[2]};
+        u[a] = fold(q[a] + 1, p.n[a], p.per[a]);
+        ok[a] = u[a] >= 0;
+        su[a] = ok[a] ? p.slot(u[0], u[1], u[2]) : sl;
+    }
+    T e[3], h[3], eu[3][3];
+    double h1[3] = {0.0, 0.0, 0.0}, ms[3] = {0.0, 0.0, 0.0};
+    bool inside = false;
+    long long l = 0;
+    if (merged && p.nfilm) l = film_local<T>(F, q, inside);
+#pragma unroll
+    for (int C = 0; C < 3; C++) {
+        e[C] = p.E[C][sl];
+        h[C] = p.H[C][sl];
+        if (merged) {
+            // E_C at +1 along the other two axes
+            eu[C][(C + 1) % 3] = p.E[C][su[(C + 1) % 3]];
+            eu[C][(C + 2) % 3] = p.E[C][su[(C + 2) % 3]];
+            if (p.nfilm) {
+                h1[C] = F.H1[C * F.ns + l];
+                ms[C] = F.prm[(C * 3) * F.ns + l];
+            }
+        }
+    }
+#pragma unroll
+    for (int C = 0; C < 3; C++) {
+        dst[C * tb + t] = (double)e[C];
+        double hv = (double)h[C];
+        if (merged) {
+            const int C1 = (C + 1) % 3, C2 = (C + 2) % 3;
+            const T d1 = dif(ok[C1] ? eu[C2][C1] : T(0), e[C2], p.dT[C1], p.invd[C1]);
+            const T d2 = dif(ok[C2] ? eu[C1][C2] : T(0), e[C1], p.dT[C2], p.invd[C2]);
+            hv = (double)(h[C] - p.hc * (d1 - d2));
+            if (inside && ms[C] > 0.0) hv = h1[C];
+        }
+        dst[(3 + C) * tb + t] = hv;
+    }
+}
+
 } // namespace mpx

@@ -511,12 +511,13 @@ mpx_status upload_profiles(mpx_sim *s) {
 }
 
 // the number of probes that ride in the H/M launch: all of them when every one
-// reads only E or a film's mean-M partials (which that launch does not write),
-// else none (the probe launch takes them)
-int folded_probes(const mpx_sim *s) {
+// reads only what that launch does not write (probe_folds; energy: also a
+// film's energy, whose partials a launch before it writes), else none (the
+// probe launch takes them)
+int folded_probes(const mpx_sim *s, bool energy = true) {
     const int np = (int)s->probes.size();
     for (const ProbeHost &pr : s->probes)
-        if (!probe_reads_e_or_m(pr.dev.kind, pr.dev.field)) return 0;
+        if (!probe_folds(pr.dev) || (pr.dev.kind == MPX_PROBE_FILM_ENERGY && !energy)) return 0;
     return np;
 }
 
@@ -580,7 +581,7 @@ mpx_status run_body(mpx_sim *s, int &par, bool timed) {
     if ((r = rec(0, 1)) != MPX_OK) return r;
     if ((r = rec(2, 0)) != MPX_OK) return r;
     CK(launch_film<T>(p, nblk, 1, 0, st));
-    if (npf == 0) CK(launch_probes<T>(p, np, s->probe_maxpart, st));
+    CK(launch_probes<T>(p, np, s->probe_maxpart, st, npf > 0));
     if ((r = rec(2, 1)) != MPX_OK) return r;
     if ((r = rec(1, 0)) != MPX_OK) return r;
     CK(launch_hbulk_film<T>(p, 2, nblk, 1, st, npf));
@@ -597,7 +598,7 @@ mpx_status run_last(mpx_sim *s, int par, hipStream_t st = nullptr) {
     CK(launch_epass<T>(p, st));
     CK(launch_film<T>(p, s->nblk, 1, 0, st));
     const int npf = folded_probes(s);
-    if (npf == 0) CK(launch_probes<T>(p, (int)s->probes.size(), s->probe_maxpart, st));
+    CK(launch_probes<T>(p, (int)s->probes.size(), s->probe_maxpart, st, npf > 0));
     CK(launch_hbulk_film<T>(p, 1, s->nblk, 1, st, npf));
     return MPX_OK;
 }
@@ -856,7 +857,7 @@ mpx_status batch_tables(mpx_batch *b) {
         }
         for (int k = 0; k < s->nblk; k++) wfilm.push_back(make_int2(q, k));
         for (int k = 0; k < s->nblk_ext; k++) wext.push_back(make_int2(q, k));
-        b->nfold.push_back(b->variant == 0 ? folded_probes(s) : 0);
+        b->nfold.push_back(b->variant == 0 ? folded_probes(s, false) : 0);
         const bool folded = b->nfold.back() > 0;
         if (!folded)
             for (int k = 0; k < (int)s->probes.size(); k++) wprobe.push_back(make_int2(q, k));
@@ -1793,7 +1794,12 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
         auto fwd = [&](int len, bool probes) -> mpx_status {
             KParams<T> p;
             fill_params<T>(s, p, MODE_INPLACE, s->parity);
-            const int np = (int)s->probes.size();
+            const int np = (int)s->probes.size(), npf = probes ? folded_probes(s) : 0;
+            BoxTape bt;
+            for (int a = 0; a < 3; a++) {
+                bt.b0[a] = eps_box[a];
+                bt.size[a] = eps_box[3 + a];
+            }
             p.films = tvar(tp, 0, V_R1);
             if (floss) CK(launch_tape_loss<T>(p, film, 0, tp.lossp(0), st, LF.cb));
             p.films = tvar(tp, 0, V_BR);
@@ -1801,20 +1807,25 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
             p.films = tvar(tp, 0, V_BRC);
             CK(launch_hbulk_film<T>(p, 1, nblk, 0, st));
             for (int m = 0; m < len; m++) {
-                if (neps > 0) CK(launch_tape_box<T>(p, eps_box, tp.boxp(m), st));
-                CK(launch_epass<T>(p, st));
+                bt.dst = tp.boxp(m);
+                CK(launch_epass<T>(p, st, neps > 0 ? &bt : nullptr));
                 p.films = tvar(tp, m, V_P1);
                 CK(launch_film<T>(p, nblk, 1, 0, st));
-                if (probes) CK(launch_probes<T>(p, np, s->probe_maxpart, st));
+                // the energy partials and the film-region state of step m + 1
+                LossTape lt;
+                lt.dst = tp.lossp(std::min(m + 1, K - 1));
+                lt.film = film;
+                lt.nblk = (int)((tp.loss_sz / 6 + 255) / 256);
+                const bool lost = floss && m + 1 < len;
+                CK(launch_probes<T>(p, probes ? np : 0, probes ? s->probe_maxpart : 0, st, npf > 0,
+                                    lost ? &lt : nullptr));
                 if (m + 1 < len) {
-                    if (floss) CK(launch_tape_loss<T>(p, film, 1, tp.lossp(m + 1), st, LF.cb));
                     // the film's second half step with the merged H/M pass
-                    // (one launch on wide grids, as in stepping)
                     p.films = tvar(tp, m, V_P2);
-                    CK(launch_hbulk_film<T>(p, 2, nblk, 1, st));
+                    CK(launch_hbulk_film<T>(p, 2, nblk, 1, st, npf));
                 } else {
                     p.films = tvar(tp, m, V_C);
-                    CK(launch_hbulk_film<T>(p, 1, nblk, 1, st));
+                    CK(launch_hbulk_film<T>(p, 1, nblk, 1, st, npf));
                 }
             }
             return MPX_OK;
@@ -1999,14 +2010,14 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
                     if (launch_adj_estep_fused<T>(A, st) != hipSuccess) return -1;
                 }
                 if (merge && m > 0) {
-                    // the first half step of step m: its film part, the loss
-                    // term's lambda H part of step m's input state
+                    // the first half step of step m: its film part, with the
+                    // loss term's lambda H part of step m's input state
                     AdjParams<T> A = params(m);
                     psi_sets(A, cur);
                     A.p.films = tvar(tp, m, V_R1);
                     A.af = h.d_af2;
+                    A.loss_h = floss ? 1 : 0;
                     if (launch_adj_film_part<T>(A, nblk, h.film_nr.data(), st) != hipSuccess) return -1;
-                    if (floss && launch_adj_loss_h<T>(A, LF.cb, st) != hipSuccess) return -1;
                     // the second half step of step m - 1: its film part
                     if (loss_eps(m - 1) != MPX_OK) return -1;
                     AdjParams<T> B = params(m - 1);

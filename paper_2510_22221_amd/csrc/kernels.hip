@@ -21,6 +21,8 @@
 // the fused pass all give bitwise identical float64 results.
 #include "film.h"
 
+#include <algorithm>
+
 namespace mpx {
 
 __device__ __forceinline__ int cell_id(const int *n, const int *per, int px, const uint8_t *id, int i, int j,
@@ -452,9 +454,14 @@ __device__ __forceinline__ void probe_parts_body(const KParams<T> &p, int pb) {
     }
 }
 
+// row y < nprobe: probe y's partials; the row after them: the film-region state
+// of an adjoint step (both read what the H/M launch will move)
 template <typename T>
-__global__ void __launch_bounds__(256) k_probe_parts(KParams<T> p) {
-    probe_parts_body(p, blockIdx.y);
+__global__ void __launch_bounds__(256) k_probe_parts(KParams<T> p, int nprobe, LossTape tape) {
+    if ((int)blockIdx.y < nprobe)
+        probe_parts_body(p, blockIdx.y);
+    else if ((int)blockIdx.x < tape.nblk)
+        tape_loss_body(p, tape.film, 1, tape.dst, blockIdx.x);
 }
 
 template <typename T>
@@ -605,10 +612,14 @@ hipError_t launch_tick(long long *step, hipStream_t s) {
 }
 
 template <typename T>
-hipError_t launch_probes(const KParams<T> &p, int nprobe, int maxpart, hipStream_t s) {
-    if (nprobe == 0) return hipSuccess;
-    if (maxpart > 0) hipLaunchKernelGGL(k_probe_parts<T>, dim3(maxpart, nprobe), dim3(256), 0, s, p);
-    hipLaunchKernelGGL(k_probes<T>, dim3(nprobe), dim3(256), 0, s, p);
+hipError_t launch_probes(const KParams<T> &p, int nprobe, int maxpart, hipStream_t s, bool folded,
+                         const LossTape *tape) {
+    const int rows = (maxpart > 0 ? nprobe : 0) + (tape ? 1 : 0);
+    const int blocks = std::max(maxpart, tape ? tape->nblk : 0);
+    if (rows > 0 && blocks > 0)
+        hipLaunchKernelGGL(k_probe_parts<T>, dim3(blocks, rows), dim3(256), 0, s, p, maxpart > 0 ? nprobe : 0,
+                           tape ? *tape : LossTape());
+    if (nprobe > 0 && !folded) hipLaunchKernelGGL(k_probes<T>, dim3(nprobe), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
@@ -656,7 +667,7 @@ hipError_t launch_tick_batch(const KParams<T> *plist, const int *inst, int n, hi
                                              hipStream_t);                                  \
     template hipError_t launch_probes_batch<T>(const KParams<T> *, const int2 *, int, int, hipStream_t); \
     template hipError_t launch_tick_batch<T>(const KParams<T> *, const int *, int, hipStream_t);   \
-    template hipError_t launch_probes<T>(const KParams<T> &, int, int, hipStream_t);        \
+    template hipError_t launch_probes<T>(const KParams<T> &, int, int, hipStream_t, bool, const LossTape *); \
     template hipError_t launch_energy<T>(const KParams<T> &, int, double *, double *, hipStream_t);
 
 MPX_INSTANTIATE(float)

@@ -59,11 +59,12 @@ struct ProbeDev {
     long long npart;
 };
 
-// a probe the merged H/M launch can take (it reads nothing that launch
-// writes): a point probe of an E component (kind 0, field below 3) or a
-// film's mean M (kind 1)
-__host__ __device__ inline bool probe_reads_e_or_m(int kind, int field) {
-    return (kind == 0 && field < 3) || kind == 1;
+// a probe the H/M launch can take (it reads nothing that launch writes): a
+// point probe of an E component (kind 0, field below 3), a film's mean M (kind
+// 1), or a film's energy (kind 2) whose partials another launch has written; a
+// wavefront sums at most eight rounds of 256 of them
+__host__ __device__ inline bool probe_folds(const ProbeDev &P) {
+    return (P.kind == 0 && P.field < 3) || P.kind == 1 || (P.kind == 2 && P.npart <= 2048);
 }
 
 // Coefficients of an edge, computed on the host with the same operation
@@ -217,6 +218,7 @@ struct AdjParams {
     int bb[3], bs[3];
     const double *ltape;
     int lfilm;
+    int loss_h = 0; // the film-region kernel adds the loss term's lambda H part
     double lscale;
     long long loss_from;
     // a weighted-trace loss: weight pw[n - 1] of E component pw_comp at slot
@@ -242,7 +244,6 @@ hipError_t launch_tape_loss(const KParams<T> &p, int film, int merged, double *d
 template <typename T>
 hipError_t launch_adj_loss_tape(const AdjParams<T> &A, int film, double scale, const double *tape,
                                 const long long *seg0, int m, long long loss_from, hipStream_t s, const int *cb);
-template <typename T> hipError_t launch_tape_box(const KParams<T> &p, const int *box, double *dst, hipStream_t s);
 template <typename T>
 hipError_t launch_adj_eps_box(const KParams<T> &p, const int *box, const double *gca, const double *gcb, double *out,
                               hipStream_t s);
@@ -268,7 +269,6 @@ hipError_t launch_adj_film_part(const AdjParams<T> &A, int nblk, const long long
 template <typename T> hipError_t launch_adj_hfield2(const AdjParams<T> &A, hipStream_t s);
 template <typename T>
 hipError_t launch_adj_loss_weights(const KParams<T> &p, int film, double *dst, hipStream_t s, const int *cb);
-template <typename T> hipError_t launch_adj_loss_h(const AdjParams<T> &A, const int *film_cb, hipStream_t s);
 template <typename T> hipError_t launch_adj_estep_fused(const AdjParams<T> &A, hipStream_t s);
 template <typename T> hipError_t launch_adj_estep(const AdjParams<T> &A, hipStream_t s);
 template <typename T> hipError_t launch_adj_loss(const AdjParams<T> &A, int film, double scale, hipStream_t s);
@@ -280,7 +280,12 @@ template <typename T> hipError_t launch_bhat(const KParams<T> &p, int phase, hip
 hipError_t launch_adj_init_ms(const int4 *blocktab, int nblk, const FilmDev *films, const AdjFilmDev *af,
                               const double *u, hipStream_t s);
 template <typename T> hipError_t launch_hbulk(const KParams<T> &p, int nhalf, int inc, hipStream_t s);
-template <typename T> hipError_t launch_epass(const KParams<T> &p, hipStream_t s);
+// tape: also write E^n and the curl input x^n of the eps box's edges to it
+struct BoxTape {
+    double *dst = nullptr; // [6][region], region: the box (b0, size) grown by one slot
+    int b0[3], size[3];
+};
+template <typename T> hipError_t launch_epass(const KParams<T> &p, hipStream_t s, const BoxTape *tape = nullptr);
 template <typename T>
 hipError_t launch_epass_batch(const KParams<T> *plist, const int4 *work, int nwork, const int2 *mwork, int nmwork,
                               bool xcls, hipStream_t s);
@@ -294,7 +299,7 @@ constexpr int kWideMinNx = 512;           // grids this wide use it
 
 // the bulk H/M pass with the film's part of it (nhalf 2: the second half step
 // of a merged pair; 1: the commit of a half step) and, nprobe > 0, the probes
-// (all of kinds probe_reads_e_or_m accepts)
+// (all of which probe_folds accepts)
 template <typename T>
 hipError_t launch_hbulk_film(const KParams<T> &p, int nhalf, int nblk, int inc, hipStream_t s, int nprobe = 0);
 template <typename T> hipError_t launch_film(const KParams<T> &p, int nblk, int phase, int inc, hipStream_t s);
@@ -314,7 +319,15 @@ template <typename T>
 hipError_t launch_probes_batch(const KParams<T> *plist, const int2 *work, int n, int maxpart, hipStream_t s);
 template <typename T> hipError_t launch_tick_batch(const KParams<T> *plist, const int *inst, int n, hipStream_t s);
 constexpr int kBatchProbes = -0x7fffffff; // x tile of a batch work entry that is a probe block
-template <typename T> hipError_t launch_probes(const KParams<T> &p, int nprobe, int maxpart, hipStream_t s);
+// the energy probes' partials; then (folded = false) every probe's sample.
+// tape: also the film-region state of an adjoint step, by further blocks
+struct LossTape {
+    double *dst = nullptr; // as launch_tape_loss writes it, merged = 1
+    int film = 0, nblk = 0;
+};
+template <typename T>
+hipError_t launch_probes(const KParams<T> &p, int nprobe, int maxpart, hipStream_t s, bool folded = false,
+                         const LossTape *tape = nullptr);
 template <typename T>
 hipError_t launch_energy(const KParams<T> &p, int nblk, double *part, double *out, hipStream_t s);
 

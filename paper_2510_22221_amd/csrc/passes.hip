@@ -36,7 +36,7 @@ constexpr int PTX = kPassTX, PTY = kPassTY;
 // ---------------------------------------------------------------------------
 // the current of the sources on the edge of component C at (i, j, k)
 template <typename T>
-__device__ __forceinline__ T src_current(const KParams<T> &p, int C, int i, int j, int k, long long step) {
+__device__ __forceinline__ double src_current(const KParams<T> &p, int C, int i, int j, int k, long long step) {
     double J = 0.0;
     for (int s = 0; s < p.nsrc; s++) {
         const SrcDev &S = p.srcs[s]; // device copy: no dynamic index into the kernel argument
@@ -46,16 +46,19 @@ __device__ __forceinline__ T src_current(const KParams<T> &p, int C, int i, int 
             continue;
         if (step < S.n) J += S.table[step];
     }
-    return T(J);
+    return J;
 }
 
+// TAPE: E^n and the curl input x^n = (d1 + psi1') - (d2 + psi2') - J^n of the
+// slots of an eps box go to the adjoint's tape as well (the pass holds both
+// anyway; a launch of its own took 4.6 us a step on a 128 x 64 x 64 grid).
 // CLS: the slot class read, 0 the class byte, 1 the 16-bit class (a grid
 // with extended triples), 2 whichever the instance has (batch members of one
 // launch differ; the test is uniform over a member's lanes).  f: the tile's
 // flag byte, first used after every field load has been issued (so that the
 // loads do not wait for it).
-template <typename T, int CLS>
-__device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, int f) {
+template <typename T, int CLS, bool TAPE = false>
+__device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, int f, const BoxTape &bt = BoxTape()) {
     if (r.j >= p.n[1]) return; // a partial tile's row (uniform)
     const unsigned es = (unsigned)sizeof(T);
     const int ic = min(r.i, p.n[0] - 1), j = r.j, k = r.k;
@@ -117,12 +120,40 @@ __device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, 
         pml_step(m.zy, m.bz, m.cz, bz);
     }
     T x0 = ay - az, x1 = bz - bx, x2 = cx - cy;
+    double xt[3] = {(double)x0, (double)x1, (double)x2}; // TAPE
+    (void)xt;
     if (f & 2) {
         const long long step = p.step[0];
         // (x - 0) is x bitwise, so subtracting only here matches the plain form
-        x0 = x0 - src_current(p, 0, r.i, j, k, step);
-        x1 = x1 - src_current(p, 1, r.i, j, k, step);
-        x2 = x2 - src_current(p, 2, r.i, j, k, step);
+        const double J0 = src_current(p, 0, r.i, j, k, step), J1 = src_current(p, 1, r.i, j, k, step),
+                     J2 = src_current(p, 2, r.i, j, k, step);
+        if constexpr (TAPE) {
+            xt[0] = (double)x0 - J0;
+            xt[1] = (double)x1 - J1;
+            xt[2] = (double)x2 - J2;
+        }
+        x0 = x0 - T(J0);
+        x1 = x1 - T(J1);
+        x2 = x2 - T(J2);
+    }
+    if constexpr (TAPE) {
+        const int rb[3] = {bt.size[0] + 1, bt.size[1] + 1, bt.size[2] + 1};
+        int lj = j - bt.b0[1], lk = k - bt.b0[2], li = r.i - bt.b0[0];
+        if (lj < 0 && p.per[1]) lj += p.n[1];
+        if (lk < 0 && p.per[2]) lk += p.n[2];
+        if (lj >= 0 && lj < rb[1] && lk >= 0 && lk < rb[2]) { // uniform
+            if (li < 0 && p.per[0]) li += p.n[0];
+            if (r.in && li >= 0 && li < rb[0]) {
+                const long long tb = (long long)rb[0] * rb[1] * rb[2];
+                double *d = bt.dst + li + (long long)rb[0] * ((long long)lj + (long long)rb[1] * lk);
+                d[0] = (double)e0;
+                d[tb] = (double)e1;
+                d[2 * tb] = (double)e2;
+                d[3 * tb] = xt[0];
+                d[4 * tb] = xt[1];
+                d[5 * tb] = xt[2];
+            }
+        }
     }
     if (!r.in || c0 == kSkip) return;
     row_st<true>(Ex, vo, u0 ? L.ca[0] * e0 + L.cb[0] * x0 : T(0));
@@ -160,9 +191,10 @@ __device__ __forceinline__ int tile_flag(const KParams<T> &p, int bx, int by, in
 
 // a block: the TX x TY slots (bx, by) of plane k, flags from the table of
 // that tile shape
-template <typename T, int CLS, int TX = PTX, int TY = PTY>
-__device__ __forceinline__ void epass_block(const KParams<T> &p, int bx, int by, int k) {
-    epass_row<T, CLS>(p, row_pos<TX>(p.n, bx, by, TY, k), tile_flag<T, TX, TY>(p, bx, by, k));
+template <typename T, int CLS, int TX = PTX, int TY = PTY, bool TAPE = false>
+__device__ __forceinline__ void epass_block(const KParams<T> &p, int bx, int by, int k,
+                                            const BoxTape &bt = BoxTape()) {
+    epass_row<T, CLS, TAPE>(p, row_pos<TX>(p.n, bx, by, TY, k), tile_flag<T, TX, TY>(p, bx, by, k), bt);
 }
 
 // the mixed slots, one thread each: the general path (folded loads; edge
@@ -313,6 +345,11 @@ __global__ void __launch_bounds__(TX *TY) k_epass(KParams<T> p) {
     epass_block<T, XC ? 1 : 0, TX, TY>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
+template <typename T, int TX, int TY, bool XC>
+__global__ void __launch_bounds__(TX *TY) k_epass_tape(KParams<T> p, BoxTape bt) {
+    epass_block<T, XC ? 1 : 0, TX, TY, true>(p, blockIdx.x, blockIdx.y, blockIdx.z, bt);
+}
+
 template <typename T, int NHALF, int TX, int TY>
 __global__ void __launch_bounds__(TX *TY) k_hbulk(KParams<T> p, int inc_step) {
     if (inc_step && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && threadIdx.y == 0)
@@ -328,9 +365,9 @@ __global__ void __launch_bounds__(TX *TY) k_hbulk(KParams<T> p, int inc_step) {
 // touch disjoint data: the film blocks read the prepass (or the scratch) the
 // first half step wrote and write M and H of magnetic faces, which the bulk
 // blocks load but never store or use.
-// The probes of an integer time when every one of them reads only E or the
-// film's mean-M partials (which this launch does not write) ride in the block
-// right after the film blocks: its first wavefront reads the step counter,
+// The probes of an integer time when every one of them reads only E, a film's
+// mean-M partials or its energy partials (which this launch does not write)
+// ride in the block right after the film blocks: its first wavefront reads the step counter,
 // samples each probe due and then advances the counter (no other block of
 // the launch reads it).
 // Every tile shape uses it: on a grid of 10^4..10^6 cells a launch of its own
@@ -346,7 +383,7 @@ __device__ __forceinline__ void probe_block(const KParams<T> &p, int nprobe, int
         long long sample;
         if (!probe_due(P, step, sample)) continue; // uniform over the wavefront
         double v[3] = {0.0, 0.0, 0.0};
-        probe_e_or_m_values(p, P, v);
+        folded_probe_values(p, P, v);
         probe_store(p, P, sample, v);
     }
     // lane 0 advances the counter after every lane has read it (one
@@ -440,18 +477,26 @@ static dim3 pass_grid(const int *n) {
     return dim3((n[0] + TX - 1) / TX, (n[1] + TY - 1) / TY, n[2]);
 }
 
+template <typename T, int TX, int TY>
+static void launch_e(const KParams<T> &p, hipStream_t s, const BoxTape *tape) {
+    const dim3 g = pass_grid<TX, TY>(p.n), b(TX, TY);
+    if (tape && p.cls16)
+        k_epass_tape<T, TX, TY, true><<<g, b, 0, s>>>(p, *tape);
+    else if (tape)
+        k_epass_tape<T, TX, TY, false><<<g, b, 0, s>>>(p, *tape);
+    else if (p.cls16)
+        k_epass<T, TX, TY, true><<<g, b, 0, s>>>(p);
+    else
+        k_epass<T, TX, TY, false><<<g, b, 0, s>>>(p);
+}
+
 // the E pass and then its mixed slots
 template <typename T>
-hipError_t launch_epass(const KParams<T> &p, hipStream_t s) {
-    const dim3 gw = pass_grid<kWideTX, kWideTY>(p.n), gn = pass_grid<PTX, PTY>(p.n);
-    if (p.wide && p.cls16)
-        k_epass<T, kWideTX, kWideTY, true><<<gw, dim3(kWideTX, kWideTY), 0, s>>>(p);
-    else if (p.wide)
-        k_epass<T, kWideTX, kWideTY, false><<<gw, dim3(kWideTX, kWideTY), 0, s>>>(p);
-    else if (p.cls16)
-        k_epass<T, PTX, PTY, true><<<gn, dim3(PTX, PTY), 0, s>>>(p);
+hipError_t launch_epass(const KParams<T> &p, hipStream_t s, const BoxTape *tape) {
+    if (p.wide)
+        launch_e<T, kWideTX, kWideTY>(p, s, tape);
     else
-        k_epass<T, PTX, PTY, false><<<gn, dim3(PTX, PTY), 0, s>>>(p);
+        launch_e<T, PTX, PTY>(p, s, tape);
     if (p.nmixed > 0) k_emixed<T><<<dim3((p.nmixed + 255) / 256), dim3(256), 0, s>>>(p);
     return hipGetLastError();
 }
@@ -527,7 +572,7 @@ hipError_t launch_hbulk_batch(const KParams<T> *plist, const int4 *work, int nwo
 }
 
 #define MPX_PASSES(T)                                                                                      \
-    template hipError_t launch_epass<T>(const KParams<T> &, hipStream_t);                                 \
+    template hipError_t launch_epass<T>(const KParams<T> &, hipStream_t, const BoxTape *);                \
     template hipError_t launch_hbulk<T>(const KParams<T> &, int, int, hipStream_t);                       \
     template hipError_t launch_hbulk_film<T>(const KParams<T> &, int, int, int, hipStream_t, int);             \
     template hipError_t launch_epass_batch<T>(const KParams<T> *, const int4 *, int, const int2 *, int,   \

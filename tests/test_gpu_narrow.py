@@ -1,5 +1,6 @@
 """Grids on 64 x 4 tiles: the film's part of the H/M pass and the probes that
-read only E or mean M ride in the H/M launch, alone and in batches.
+read only E, mean M or a film's energy ride in the H/M launch, alone and (E and
+mean M) in batches.
 
 One H-point probe more sends a simulation's probes to the probe launch; the
 fields, the shared traces and the step counter must be the same bits.  The
@@ -31,7 +32,8 @@ def build(w, prec, film, with_h):
             (s.add_probe(mpx.PROBE_FIELD, field=2, ijk=(5, 4, 3), cap=64, every=3), 1)]
     if film:
         pids += [(s.add_probe(mpx.PROBE_MEAN_M, film=0, cap=64), 3),
-                 (s.add_probe(mpx.PROBE_MEAN_M, film=0, cap=64, every=4), 3)]
+                 (s.add_probe(mpx.PROBE_MEAN_M, film=0, cap=64, every=4), 3),
+                 (s.add_probe(mpx.PROBE_FILM_ENERGY, film=0, cap=64), 1)]
     if with_h:
         s.add_probe(mpx.PROBE_FIELD, field=4, ijk=(7, 5, 4), cap=64)
     return s, pids
