@@ -123,6 +123,124 @@ __device__ __forceinline__ void film_gather(const int *n, const int *per, const 
     }
 }
 
+// film_gather() from the state the prepass reads, in the prepass's
+// operations: what a face takes from its own and eight neighbours' prepass is
+// 20 values of E, nine of H and of the films' tables.  With cu, the curl term
+// of the face's phase-2 values.
+template <typename T, int C>
+__device__ __forceinline__ void film_gather_state(const KParams<T> &p, const FilmDev &F, const int *r, unsigned l,
+                                                  double *P, double *Q, double &cu, int &le) {
+    constexpr int C1 = (C + 1) % 3, C2 = (C + 2) % 3;
+    // offsets of the -1, 0 and +1 neighbours along each axis, in the grid and
+    // in the face box (0 for one outside: its value is dropped)
+    const long long st[3] = {1, p.px, (long long)p.px * p.n[1]};
+    const int sl[3] = {1, F.bn[0], F.bn[0] * F.bn[1]}, se[3] = {1, F.en[0], F.en[0] * F.en[1]};
+    long long o[3], dg[3][3];
+    int dl[3][3];
+    bool dom[3], ok[3][3], in[3][3];
+    le = 0;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        const int i = F.b0[a] + r[a];
+        o[a] = i * st[a];
+        le += (i - F.e0[a]) * se[a];
+#pragma unroll
+        for (int u = 0; u < 3; u++) {
+            const int q = fold(i + u - 1, p.n[a], p.per[a]);
+            const bool d = q >= 0;
+            const int m = q - F.e0[a], b = q - F.b0[a];
+            ok[a][u] = d && m >= 0 && m < F.en[a];
+            in[a][u] = d && b >= 0 && b < F.bn[a];
+            dg[a][u] = d ? (q - i) * st[a] : 0;
+            dl[a][u] = in[a][u] ? (b - r[a]) * sl[a] : 0;
+            if (u == 2) dom[a] = d;
+        }
+    }
+    const long long g0 = o[0] + o[1] + o[2];
+    T eC[2][2][2], e1[3][2], e2[3][2]; // E_C [C][C1][C2], E_C1 [C][C2], E_C2 [C][C1]
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+        for (int v = 0; v < 2; v++)
+#pragma unroll
+            for (int w = 0; w < 2; w++)
+                eC[u][v][w] = p.E[C][g0 + dg[C][u] + (v ? dg[C1][2] : 0) + (w ? dg[C2][2] : 0)];
+#pragma unroll
+    for (int u = 0; u < 3; u++)
+#pragma unroll
+        for (int v = 0; v < 2; v++) {
+            e1[u][v] = p.E[C1][g0 + dg[C][u] + (v ? dg[C2][2] : 0)];
+            e2[u][v] = p.E[C2][g0 + dg[C][u] + (v ? dg[C1][2] : 0)];
+        }
+    T h[2][2][2], hC = p.H[C][g0]; // H of C1 and C2 [C][own axis]
+    double ms[2][2][2], m[2][2][2];
+    const double msC = F.prm[(C * 3) * F.ns + l], mC = F.M[(C * 3 + C) * F.ns + l];
+    bool use[2][2][2], mag[2][2][2];
+#pragma unroll
+    for (int w = 0; w < 2; w++) {
+        const int cp = w ? C2 : C1;
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int v = 0; v < 2; v++) {
+                use[w][u][v] = ok[C][u] && ok[cp][v + 1];
+                mag[w][u][v] = in[C][u] && in[cp][v + 1];
+                const long long n = (long long)l + (mag[w][u][v] ? dl[C][u] + dl[cp][v + 1] : 0);
+                h[w][u][v] = p.H[cp][g0 + dg[C][u] + dg[cp][v + 1]];
+                ms[w][u][v] = F.prm[(cp * 3) * F.ns + n];
+                m[w][u][v] = F.M[(cp * 3 + cp) * F.ns + n];
+            }
+    }
+    // zero past a wall
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+        for (int v = 0; v < 2; v++)
+#pragma unroll
+            for (int w = 0; w < 2; w++)
+                if ((v && !dom[C1]) || (w && !dom[C2])) eC[u][v][w] = T(0);
+#pragma unroll
+    for (int u = 0; u < 3; u++)
+#pragma unroll
+        for (int v = 0; v < 2; v++) {
+            if ((u == 2 && !dom[C]) || (v && !dom[C2])) e1[u][v] = T(0);
+            if ((u == 2 && !dom[C]) || (v && !dom[C1])) e2[u][v] = T(0);
+        }
+    {
+        const double d1 = over_spacing(p, (double)e2[1][1] - (double)e2[1][0], C1);
+        const double d2 = over_spacing(p, (double)e1[1][1] - (double)e1[1][0], C2);
+        cu = p.hcd * (d1 - d2);
+        const double b = msC > 0.0 ? (double)hC + mC : (double)hC + 0.0;
+        Q[C] = b;
+        P[C] = b - cu;
+    }
+#pragma unroll
+    for (int w = 0; w < 2; w++) {
+        const int cp = w ? C2 : C1;
+        double vn[2][2], vs[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int v = 0; v < 2; v++) {
+                double d1, d2;
+                if (w == 0) {
+                    d1 = over_spacing(p, (double)eC[u][v][1] - (double)eC[u][v][0], C2);
+                    d2 = over_spacing(p, (double)e2[u + 1][v] - (double)e2[u][v], C);
+                } else {
+                    d1 = over_spacing(p, (double)e1[u + 1][v] - (double)e1[u][v], C);
+                    d2 = over_spacing(p, (double)eC[u][1][v] - (double)eC[u][0][v], C1);
+                }
+                const double h0 = (double)h[w][u][v];
+                const double b = mag[w][u][v] && ms[w][u][v] > 0.0 ? h0 + m[w][u][v] : h0 + 0.0;
+                const double bs = b - p.hcd * (d1 - d2);
+                vn[u][v] = use[w][u][v] ? b : 0.0;
+                vs[u][v] = use[w][u][v] ? bs : 0.0;
+            }
+        Q[cp] = ((vn[0][0] + vn[1][0]) + (vn[0][1] + vn[1][1])) * 0.25;
+        P[cp] = ((vs[0][0] + vs[1][0]) + (vs[0][1] + vs[1][1])) * 0.25;
+    }
+}
+
 // keeps a value from being computed only behind the branch that uses it (the
 // compiler moves loads there, one round trip later)
 __device__ __forceinline__ void hold(double &v) { asm volatile("" : "+v"(v)); }
@@ -136,7 +254,8 @@ __device__ __forceinline__ void hold(double &v) { asm volatile("" : "+v"(v)); }
 // films stay at 30.5 us (bandwidth: 24 float64 loads a face, from cache)
 // tid: the thread's index in its block of 256 (film blocks also run in
 // launches whose blocks are 64 x 4)
-template <typename T, int C>
+// STATE: a first half step without its prepass (film_gather_state)
+template <typename T, int C, bool STATE>
 __device__ __forceinline__ double film_face(const KParams<T> &p, const FilmDev &F, int phase, unsigned l) {
     int r[3];
     box_split(l, F.bn, r);
@@ -148,10 +267,14 @@ __device__ __forceinline__ double film_face(const KParams<T> &p, const FilmDev &
 #pragma unroll
     for (int w = 0; w < 3; w++) M[w] = Msrc[(C * 3 + w) * F.ns + l];
     int le;
-    film_gather(p.n, p.per, F, C, r, phase == 1 ? F.Bn : F.Bn2, phase == 1 ? F.Bs : F.Bs2, P, Q, le);
-    // the curl term the prepass left for the face's phase-2 values
     double cu = 0.0;
-    if (phase == 1 && F.Bn2) cu = F.Bs2[C * F.nse + le];
+    if (STATE)
+        film_gather_state<T, C>(p, F, r, l, P, Q, cu, le);
+    else {
+        film_gather(p.n, p.per, F, C, r, phase == 1 ? F.Bn : F.Bn2, phase == 1 ? F.Bs : F.Bs2, P, Q, le);
+        // the curl term the prepass left for the face's phase-2 values
+        if (phase == 1 && F.Bn2) cu = F.Bs2[C * F.nse + le];
+    }
 #pragma unroll
     for (int w = 0; w < 3; w++) {
         hold(M[w]);
@@ -183,7 +306,7 @@ __device__ __forceinline__ double film_face(const KParams<T> &p, const FilmDev &
     return Mn[C];
 }
 
-template <typename T>
+template <typename T, bool STATE = false>
 __device__ __forceinline__ void film_body(const KParams<T> &p, int phase, int inc_step, int blk, int tid) {
     __shared__ double red[256];
     if (inc_step && blk == 0 && tid == 0) p.step[0] = p.step[0] + 1;
@@ -192,9 +315,9 @@ __device__ __forceinline__ void film_body(const KParams<T> &p, int phase, int in
     const unsigned l = (unsigned)bt.z + (unsigned)tid;
     double own = 0.0;
     if (l < (unsigned)F.ns)
-        own = bt.y == 0   ? film_face<T, 0>(p, F, phase, l)
-              : bt.y == 1 ? film_face<T, 1>(p, F, phase, l)
-                          : film_face<T, 2>(p, F, phase, l);
+        own = bt.y == 0   ? film_face<T, 0, STATE>(p, F, phase, l)
+              : bt.y == 1 ? film_face<T, 1, STATE>(p, F, phase, l)
+                          : film_face<T, 2, STATE>(p, F, phase, l);
     // block partial of the own component (mean-M probes, which read it
     // between the two half steps: the second half step's would go unread): a
     // halving tree, its first two levels over LDS, the rest in one wavefront

@@ -147,8 +147,8 @@ __device__ __forceinline__ void curl_e64_sel(const KParams<T> &p, int c, const i
     const double e2b = (double)ldz_sel(p, p.E[c2], u1[0], u1[1], u1[2]);
     const double e1a = (double)ldz_sel(p, p.E[c1], idx[0], idx[1], idx[2]);
     const double e1b = (double)ldz_sel(p, p.E[c1], u2[0], u2[1], u2[2]);
-    d1 = (e2b - e2a) / p.d[c1];
-    d2 = (e1b - e1a) / p.d[c2];
+    d1 = over_spacing(p, e2b - e2a, c1);
+    d2 = over_spacing(p, e1b - e1a, c2);
 }
 
 // bhat() for phase 1 at a face of film F's grown box, by the same
@@ -175,8 +175,10 @@ __device__ __forceinline__ void bhat_phase1(const KParams<T> &p, const FilmDev &
     bs = b - cu;
 }
 
-// B^ prepass: B^n and B^* of every face of the grown face box
-template <typename T>
+// B^ prepass: B^n and B^* of every face of the grown face box.  BESIDE: in
+// the launch of the film's first half step, whose blocks form what they need
+// of it themselves and write the magnetic faces' phase-2 values
+template <typename T, bool BESIDE = false>
 __device__ __forceinline__ void bhat_body(const KParams<T> &p, int phase, int blk) {
     const int4 bt = block_entry(p.blocktab_ext, blk);
     const int f = bt.x, c = bt.y;
@@ -198,7 +200,7 @@ __device__ __forceinline__ void bhat_body(const KParams<T> &p, int phase, int bl
         if (!mag) {
             F.Bn2[c * F.nse + l] = bn2;
             F.Bs2[c * F.nse + l] = bs2;
-        } else {
+        } else if (!BESIDE) {
             // a magnetic face: the film kernel completes it from its solve;
             // it finds the curl term here (only its own thread reads it)
             F.Bs2[c * F.nse + l] = cu;
@@ -216,6 +218,26 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_bhat_batch(const KParams<T> *__restrict__ plist, const int2 *__restrict__ work, int phase) {
     const int2 wk = work[blockIdx.x];
     bhat_body(plist[wk.x], phase, wk.y);
+}
+
+// the first half step and its prepass in one launch: the film's blocks, then
+// the prepass's
+template <typename T>
+__global__ void __launch_bounds__(256) k_film_first(KParams<T> p, int nblk) {
+    if ((int)blockIdx.x < nblk)
+        film_body<T, true>(p, 1, 0, blockIdx.x, threadIdx.x);
+    else
+        bhat_body<T, true>(p, 1, blockIdx.x - nblk);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_film_first_batch(const KParams<T> *__restrict__ plist, const int2 *__restrict__ work_ext, const int2 *__restrict__ work, int n) {
+    const int b = (int)blockIdx.x;
+    const int2 wk = b < n ? work[b] : work_ext[b - n];
+    if (b < n)
+        film_body<T, true>(plist[wk.x], 1, 0, wk.y, threadIdx.x);
+    else
+        bhat_body<T, true>(plist[wk.x], 1, wk.y);
 }
 
 template <typename T>
@@ -587,9 +609,22 @@ hipError_t launch_bhat(const KParams<T> &p, int phase, hipStream_t s) {
     return hipGetLastError();
 }
 
+// films of at most this many blocks (of 256 faces, over all families) run
+// their first half step and its prepass in one launch: a launch and its
+// latency chain less against five times the loads, which up to some three
+// blocks a CU hide in the chain.  Two launches : one, us of a step: 51 blocks
+// (128 x 64 x 64, float32) 24.5 : 22.7, 189 (256 x 128 x 48) 46.2 : 44.0 and in
+// float64 74.4 : 71.8, 351 (384 x 160 x 48) 66.0 : 63.2 and 114.0 : 112.3; us
+// of the kernels, 738 blocks 15.2 : 13.7 and 16.1 : 16.4, 3864 blocks 47 : 60
+constexpr int kFilmFirstMax = 1024;
+
 template <typename T>
 hipError_t launch_film(const KParams<T> &p, int nblk, int phase, int inc, hipStream_t s) {
     if (nblk == 0) return hipSuccess;
+    if (phase == 1 && !inc && nblk <= kFilmFirstMax) {
+        hipLaunchKernelGGL(k_film_first<T>, dim3(nblk + p.nblk_ext), dim3(256), 0, s, p, nblk);
+        return hipGetLastError();
+    }
     // phase 2 follows a phase 1 whose kernels wrote its prepass
     if (phase == 1) hipLaunchKernelGGL(k_bhat<T>, dim3(p.nblk_ext), dim3(256), 0, s, p, phase);
     hipLaunchKernelGGL(k_film<T>, dim3(nblk), dim3(256), 0, s, p, phase, inc);
@@ -640,6 +675,10 @@ template <typename T>
 hipError_t launch_film_batch(const KParams<T> *plist, const int2 *work_ext, int n_ext, const int2 *work, int n,
                              int phase, int inc, hipStream_t s) {
     if (n == 0) return hipSuccess;
+    if (phase == 1 && !inc && n <= kFilmFirstMax) {
+        hipLaunchKernelGGL(k_film_first_batch<T>, dim3(n + n_ext), dim3(256), 0, s, plist, work_ext, work, n);
+        return hipGetLastError();
+    }
     if (phase == 1) hipLaunchKernelGGL(k_bhat_batch<T>, dim3(n_ext), dim3(256), 0, s, plist, work_ext, phase);
     hipLaunchKernelGGL(k_film_batch<T>, dim3(n), dim3(256), 0, s, plist, work, phase, inc);
     return hipGetLastError();

@@ -92,6 +92,7 @@ struct KParams {
     int px;
     int per[3];
     double d[3];
+    double rd[3], rdl[3]; // 1 / d to nearest, and the rest of it
     T dT[3];
     T invd[3];
     T hc;        // dt / (2 mu0)
