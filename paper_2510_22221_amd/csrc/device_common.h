@@ -165,10 +165,43 @@ __device__ __forceinline__ double block_order_sum(const double *part, int n) {
     return r;
 }
 
+// the same for a run of n >= 1 pairs of partials, by a block of 256 threads
+// (valid in thread 0), four rounds of 256 pairs in flight: the launch's field
+// tiles (256 a round) take longer, so a step that samples a 160 x 144 x 128
+// grid in float64 keeps its 43.5 us (one wavefront for it all: 60 us; eight
+// rounds cost the launch its registers for seven wavefronts a SIMD)
+__device__ __forceinline__ void block_order_sum_pairs(const double *part, long long n, double *out) {
+    __shared__ double2 red[256];
+    const int t = (int)threadIdx.x + (int)blockDim.x * (int)threadIdx.y;
+    const double2 *pp = (const double2 *)part;
+    double2 s = make_double2(0.0, 0.0);
+#pragma unroll 4
+    for (long long r = 0; r < n; r += 256) {
+        const long long b = r + t;
+        const double2 x = pp[b < n ? b : n - 1];
+        s.x = b < n ? s.x + x.x : s.x;
+        s.y = b < n ? s.y + x.y : s.y;
+    }
+    __syncthreads();
+    red[t] = s;
+    __syncthreads();
+    if (t >= 64) return;
+    const double2 q0 = red[t], q1 = red[t + 64], q2 = red[t + 128], q3 = red[t + 192];
+    double r[2] = {(q0.x + q2.x) + (q1.x + q3.x), (q0.y + q2.y) + (q1.y + q3.y)}; // levels 128 and 64
+    for (int w = 0; w < 2; w++) {
+        for (int st = 32; st > 0; st >>= 1) {
+            const double o = __shfl_down(r[w], st, 64);
+            if (t < st) r[w] = r[w] + o;
+        }
+        out[w] = r[w];
+    }
+}
+
 // the values of such a probe in the merged H/M launch's probe block, formed
 // by its first wavefront (the others take no part): the E component at its
 // site, the film's mean M from its film blocks' partial sums in block order,
-// or the film's energy from its own partials; valid in lane 0
+// or the film's energy from its own partials (the grid's takes the whole
+// block); valid in lane 0
 template <typename T>
 __device__ __forceinline__ void folded_probe_values(const KParams<T> &p, const ProbeDev &P, double *v) {
     if (P.kind == 0) {

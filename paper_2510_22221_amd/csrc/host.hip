@@ -514,12 +514,12 @@ mpx_status upload_profiles(mpx_sim *s) {
 
 // the number of probes that ride in the H/M launch: all of them when every one
 // reads only what that launch does not write (probe_folds; energy: also a
-// film's energy, whose partials a launch before it writes), else none (the
-// probe launch takes them)
+// film's or the grid's energy, whose partials a launch before it writes), else
+// none (the probe launch takes them)
 int folded_probes(const mpx_sim *s, bool energy = true) {
     const int np = (int)s->probes.size();
     for (const ProbeHost &pr : s->probes)
-        if (!probe_folds(pr.dev) || (pr.dev.kind == MPX_PROBE_FILM_ENERGY && !energy)) return 0;
+        if (!probe_folds(pr.dev) || (pr.dev.kind >= MPX_PROBE_FILM_ENERGY && !energy)) return 0;
     return np;
 }
 

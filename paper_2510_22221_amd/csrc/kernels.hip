@@ -276,45 +276,107 @@ __device__ double h_integer_time(const KParams<T> &p, int c, const int *idx) {
     return (double)(h - p.hc * (d1 - d2));
 }
 
+// The energy kernels' materials: a block's copy in LDS, read by cell id
+struct EnergyMat {
+    double eps, pec;
+};
+
+template <typename T>
+__device__ __forceinline__ void energy_mats(const KParams<T> &p, EnergyMat *tab, int t) {
+    tab[t].eps = p.mat[t].eps_r;
+    tab[t].pec = p.mat[t].is_pec ? 1.0 : 0.0;
+}
+
 // the two energy sums of the slot idx: eps E^2 over its three edges (PEC and
 // lower-wall edges excluded) and H^2 - (hc curl E)^2 over its three faces (H
 // at the integer time times the product of the two neighbouring half-step
 // values), H being the stored field between steps (MID = 0) or, during the
 // merged pass, the integer-time value of h_integer_time rounded to the field
-// type (MID = 1), which is what the bracket half step would store
+// type (MID = 1), which is what the bracket half step would store.  The seven
+// cells around the slot that its edges touch, nine values of E and three of H
+// go out in one round trip; an edge that counts has its four cells in the
+// domain.
 template <typename T, int MID>
-__device__ __forceinline__ void energy_site(const KParams<T> &p, const int *idx, double &we, double &wh) {
+__device__ __forceinline__ void energy_site(const KParams<T> &p, const EnergyMat *tab, const int *idx, double &we,
+                                            double &wh) {
     const long long q = p.slot(idx[0], idx[1], idx[2]);
+    const long long st[3] = {1, p.px, (long long)p.px * p.n[1]};
+    long long lo[3], hi[3];
+    bool okl[3], okh[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        const int l = fold(idx[a] - 1, p.n[a], p.per[a]), u = fold(idx[a] + 1, p.n[a], p.per[a]);
+        okl[a] = l >= 0;
+        okh[a] = u >= 0;
+        lo[a] = okl[a] ? (l - idx[a]) * st[a] : 0;
+        hi[a] = okh[a] ? (u - idx[a]) * st[a] : 0;
+    }
+    int id[7]; // bit a of the index: one cell down along axis a
+    T e[3], h[3], eu[3][3];
+#pragma unroll
+    for (int b = 0; b < 7; b++)
+        id[b] = p.id[q + (b & 1 ? lo[0] : 0) + (b & 2 ? lo[1] : 0) + (b & 4 ? lo[2] : 0)];
+#pragma unroll
     for (int c = 0; c < 3; c++) {
         const int c1 = (c + 1) % 3, c2 = (c + 2) % 3;
-        if (!((!p.per[c1] && idx[c1] == 0) || (!p.per[c2] && idx[c2] == 0))) {
-            double se = 0.0;
-            int cnt = 0;
-            bool pec = false;
-            for (int u = -1; u <= 0; u++)
-                for (int v = -1; v <= 0; v++) {
-                    int cc[3];
-                    cc[c] = idx[c];
-                    cc[c1] = idx[c1] + u;
-                    cc[c2] = idx[c2] + v;
-                    const int m = cell_id(p.n, p.per, p.px, p.id, cc[0], cc[1], cc[2]);
-                    if (m < 0) continue;
-                    se += p.mat[m].eps_r;
-                    pec = pec || p.mat[m].is_pec;
-                    cnt++;
-                }
-            if (!pec && cnt) {
-                const double eps = p.eps0 * (se / cnt);
-                const double e = (double)p.E[c][q];
-                we += eps * e * e;
+        e[c] = p.E[c][q];
+        eu[c][c1] = p.E[c][q + hi[c1]];
+        eu[c][c2] = p.E[c][q + hi[c2]];
+        h[c] = p.H[c][q];
+    }
+    EnergyMat m[7];
+#pragma unroll
+    for (int b = 0; b < 7; b++) m[b] = tab[id[b]];
+    int f = -1;
+    if (MID)
+        for (int g = 0; g < p.nfilm; g++) {
+            const FilmDev &F = p.films[g];
+            if (idx[0] >= F.b0[0] && idx[0] < F.b0[0] + F.bn[0] && idx[1] >= F.b0[1] &&
+                idx[1] < F.b0[1] + F.bn[1] && idx[2] >= F.b0[2] && idx[2] < F.b0[2] + F.bn[2])
+                f = g;
+        }
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const int c1 = (c + 1) % 3, c2 = (c + 2) % 3;
+        const EnergyMat &m11 = m[(1 << c1) | (1 << c2)], &m10 = m[1 << c1], &m01 = m[1 << c2], &m00 = m[0];
+        const double eps = p.eps0 * ((((m11.eps + m10.eps) + m01.eps) + m00.eps) * 0.25);
+        const double ev = (double)e[c], wn = we + eps * ev * ev;
+        const bool counts = okl[c1] && okl[c2] && !(m11.pec + m10.pec + m01.pec + m00.pec > 0.0);
+        we = counts ? wn : we;
+        const T e2b = okh[c1] ? eu[c2][c1] : T(0), e1b = okh[c2] ? eu[c1][c2] : T(0);
+        const double cu = p.hcd * (over_spacing(p, (double)e2b - (double)e[c2], c1) -
+                                   over_spacing(p, (double)e1b - (double)e[c1], c2));
+        double hv = (double)h[c];
+        if (MID) {
+            hv = (double)(h[c] - p.hc * (dif(e2b, e[c2], p.dT[c1], p.invd[c1]) - dif(e1b, e[c1], p.dT[c2], p.invd[c2])));
+            if (f >= 0) {
+                const FilmDev &F = p.films[f];
+                bool inside;
+                const long long l = film_local<T>(F, idx, inside);
+                if (F.prm[(c * 3) * F.ns + l] > 0.0) hv = (double)(T)F.H1[c * F.ns + l];
             }
         }
-        double d1, d2;
-        curl_e64(p, c, idx, d1, d2);
-        const double cu = p.hcd * (d1 - d2);
-        const double h = MID ? (double)(T)h_integer_time(p, c, idx) : (double)p.H[c][q];
-        wh += h * h - cu * cu;
+        wh += hv * hv - cu * cu;
     }
+}
+
+// the sums of 256 values a and of 256 values b over a block, a halving tree
+// each (the first wavefront's, the second's): its first two levels over LDS,
+// one barrier, the rest by shuffles.  Valid in threads 0 (a) and 64 (b); red is
+// free again after the block's next barrier.
+__device__ __forceinline__ double block_tree2(double (*red)[256], int t, double a, double b) {
+    red[0][t] = a;
+    red[1][t] = b;
+    __syncthreads();
+    if (t >= 128) return 0.0;
+    const double *r = red[t >> 6];
+    const int l = t & 63;
+    double s = (r[l] + r[l + 128]) + (r[l + 64] + r[l + 192]);
+    for (int st = 32; st > 0; st >>= 1) {
+        const double o = __shfl_down(s, st, 64);
+        if (l < st) s = s + o;
+    }
+    return s;
 }
 
 template <typename T>
@@ -434,45 +496,62 @@ __device__ double film_cell_energy(const KParams<T> &p, const FilmDev &F, unsign
     return m.Ms > 0.0 ? w : 0.0;
 }
 
-// energy probes: block b of probe pb sums cells [256 b, 256 b + 256) of the
+// energy probes: partial b of probe pb sums cells [256 b, 256 b + 256) of the
 // film's cell box into P.part[b] (film energy), or slots [256 b, 256 b + 256)
-// of the grid (x fastest) into P.part[2 b], P.part[2 b + 1] (grid energy)
+// of the grid (x fastest) into P.part[2 b], P.part[2 b + 1] (grid energy).  A
+// block takes partials blockIdx.x, + gridDim.x, ...: a launch at a step that
+// samples nothing is over with its few blocks (160 x 144 x 128: 7.4 us with a
+// block a partial, 4.6 us; one that samples: 166 us with the ids of an edge's
+// cells and their materials read one after the other, 70 us).
 template <typename T>
 __device__ __forceinline__ void probe_parts_body(const KParams<T> &p, int pb) {
-    __shared__ double red[2][256];
+    __shared__ double red[2][2][256];
+    __shared__ EnergyMat tab[256];
     const ProbeDev &P = p.probes[pb];
     if ((P.kind != 2 && P.kind != 3) || (long long)blockIdx.x >= P.npart) return;
     long long sample;
     if (!probe_due(P, p.step[0], sample)) return;
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    const int nw = P.kind == 2 ? 1 : 2;
+    const int tid = (int)threadIdx.x;
     if (P.kind == 2) {
         const FilmDev F = film_desc(p.films, __builtin_amdgcn_readfirstlane(P.film));
-        const long long ncell = (long long)F.cb[3] * F.cb[4] * F.cb[5];
-        red[0][threadIdx.x] = t < ncell ? film_cell_energy(p, F, (unsigned)t) : 0.0;
-    } else {
-        double we = 0.0, wh = 0.0;
-        if (t < (long long)p.n[0] * p.n[1] * p.n[2]) {
-            const int idx[3] = {(int)(t % p.n[0]), (int)((t / p.n[0]) % p.n[1]),
-                                (int)(t / ((long long)p.n[0] * p.n[1]))};
-            energy_site<T, 1>(p, idx, we, wh);
+        const unsigned ncell = (unsigned)F.cb[3] * F.cb[4] * F.cb[5];
+        int w = 0;
+        for (unsigned b = blockIdx.x; b < P.npart; b += gridDim.x, w ^= 1) {
+            const unsigned t = b * 256u + tid;
+            const double v = t < ncell ? film_cell_energy(p, F, t) : 0.0;
+            const double s = block_tree2(red[w], tid, v, 0.0);
+            if (tid == 0) P.part[b] = s;
         }
-        red[0][threadIdx.x] = we;
-        red[1][threadIdx.x] = wh;
+        return;
     }
+    energy_mats(p, tab, tid);
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st)
-            for (int w = 0; w < nw; w++) red[w][threadIdx.x] += red[w][threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        if (P.kind == 2)
-            P.part[blockIdx.x] = red[0][0];
-        else {
-            P.part[2 * blockIdx.x] = red[0][0];
-            P.part[2 * blockIdx.x + 1] = red[1][0];
+    const long long rows = (long long)p.n[1] * p.n[2];
+    int w = 0;
+    for (long long b = blockIdx.x; b < P.npart; b += gridDim.x, w ^= 1) {
+        // the partial's first slot and row (one division of uniform values),
+        // then the thread's own from there
+        const long long t0 = b * 256;
+        long long row;
+        unsigned x;
+        if (t0 >> 32) {
+            row = t0 / p.n[0];
+            x = (unsigned)(t0 - row * p.n[0]);
+        } else {
+            row = (unsigned)t0 / (unsigned)p.n[0];
+            x = (unsigned)t0 - (unsigned)row * (unsigned)p.n[0];
         }
+        const unsigned xt = x + (unsigned)tid, dr = xt / (unsigned)p.n[0];
+        const long long rt = row + dr;
+        double we = 0.0, wh = 0.0;
+        if (rt < rows) {
+            const unsigned k = (unsigned)rt / (unsigned)p.n[1];
+            const int idx[3] = {(int)(xt - dr * (unsigned)p.n[0]), (int)((unsigned)rt - k * (unsigned)p.n[1]), (int)k};
+            energy_site<T, 1>(p, tab, idx, we, wh);
+        }
+        const double s = block_tree2(red[w], tid, we, wh);
+        if (tid == 0) P.part[2 * b] = s;
+        if (tid == 64) P.part[2 * b + 1] = s;
     }
 }
 
@@ -508,32 +587,23 @@ __global__ void __launch_bounds__(256) k_probes_batch(const KParams<T> *__restri
 // discrete energy at an integer time: per-block partials of
 // sum eps_e E^2, sum (H^2 - (hc curl E)^2) and sum H0_c M_c
 // ---------------------------------------------------------------------------
+// (partial b: tile b of 64 x 4 slots, x fastest)
 template <typename T>
-__global__ void __launch_bounds__(256) k_energy(KParams<T> p, double *part) {
-    __shared__ double red[3][256];
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = blockIdx.y * blockDim.y + threadIdx.y;
-    const int k = blockIdx.z;
-    const int t = threadIdx.x + blockDim.x * threadIdx.y;
-    double we = 0.0, wh = 0.0;
-    if (i < p.n[0] && j < p.n[1]) {
-        const int idx[3] = {i, j, k};
-        energy_site<T, 0>(p, idx, we, wh);
-    }
-    red[0][t] = we;
-    red[1][t] = wh;
+__global__ void __launch_bounds__(256) k_energy(KParams<T> p, double *part, unsigned gx, unsigned gy, unsigned nb) {
+    __shared__ double red[2][2][256];
+    __shared__ EnergyMat tab[256];
+    const int t = threadIdx.x;
+    energy_mats(p, tab, t);
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (t < s) {
-            red[0][t] += red[0][t + s];
-            red[1][t] += red[1][t + s];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        const long long b = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
-        part[2 * b] = red[0][0];
-        part[2 * b + 1] = red[1][0];
+    int w = 0;
+    for (unsigned b = blockIdx.x; b < nb; b += gridDim.x, w ^= 1) {
+        const unsigned r = b / gx, k = r / gy;
+        const int idx[3] = {(int)((b - r * gx) * 64u) + (t & 63), (int)((r - k * gy) * 4u) + (t >> 6), (int)k};
+        double we = 0.0, wh = 0.0;
+        if (idx[0] < p.n[0] && idx[1] < p.n[1]) energy_site<T, 0>(p, tab, idx, we, wh);
+        const double s = block_tree2(red[w], t, we, wh);
+        if (t == 0) part[2ll * b] = s;
+        if (t == 64) part[2ll * b + 1] = s;
     }
 }
 
@@ -646,11 +716,14 @@ hipError_t launch_tick(long long *step, hipStream_t s) {
     return hipGetLastError();
 }
 
+// blocks of an energy launch: eight a CU, each looping over its partials
+constexpr int kPartBlocks = 2048;
+
 template <typename T>
 hipError_t launch_probes(const KParams<T> &p, int nprobe, int maxpart, hipStream_t s, bool folded,
                          const LossTape *tape) {
     const int rows = (maxpart > 0 ? nprobe : 0) + (tape ? 1 : 0);
-    const int blocks = std::max(maxpart, tape ? tape->nblk : 0);
+    const int blocks = std::max(std::min(maxpart, kPartBlocks), tape ? tape->nblk : 0);
     if (rows > 0 && blocks > 0)
         hipLaunchKernelGGL(k_probe_parts<T>, dim3(blocks, rows), dim3(256), 0, s, p, maxpart > 0 ? nprobe : 0,
                            tape ? *tape : LossTape());
@@ -660,9 +733,10 @@ hipError_t launch_probes(const KParams<T> &p, int nprobe, int maxpart, hipStream
 
 template <typename T>
 hipError_t launch_energy(const KParams<T> &p, int nblk, double *part, double *out, hipStream_t s) {
-    dim3 blk(64, 4, 1), grd((p.n[0] + 63) / 64, (p.n[1] + 3) / 4, p.n[2]);
-    hipLaunchKernelGGL(k_energy<T>, grd, blk, 0, s, p, part);
-    const long long nb = (long long)grd.x * grd.y * grd.z;
+    const unsigned gx = (p.n[0] + 63) / 64, gy = (p.n[1] + 3) / 4;
+    const long long nb = (long long)gx * gy * p.n[2];
+    hipLaunchKernelGGL(k_energy<T>, dim3((unsigned)std::min<long long>(nb, kPartBlocks)), dim3(256), 0, s, p, part,
+                       gx, gy, (unsigned)nb);
     hipLaunchKernelGGL(k_sum_pairs, dim3(1), dim3(256), 0, s, part, nb, out);
     if (nblk) {
         hipLaunchKernelGGL(k_zeeman<T>, dim3(nblk), dim3(256), 0, s, p);
@@ -687,7 +761,7 @@ hipError_t launch_film_batch(const KParams<T> *plist, const int2 *work_ext, int 
 template <typename T>
 hipError_t launch_probes_batch(const KParams<T> *plist, const int2 *work, int n, int maxpart, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    if (maxpart > 0) hipLaunchKernelGGL(k_probe_parts_batch<T>, dim3(maxpart, n), dim3(256), 0, s, plist, work);
+    if (maxpart > 0) hipLaunchKernelGGL(k_probe_parts_batch<T>, dim3(std::min(maxpart, kPartBlocks), n), dim3(256), 0, s, plist, work);
     hipLaunchKernelGGL(k_probes_batch<T>, dim3(n), dim3(256), 0, s, plist, work);
     return hipGetLastError();
 }

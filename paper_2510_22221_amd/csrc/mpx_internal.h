@@ -61,10 +61,14 @@ struct ProbeDev {
 
 // a probe the H/M launch can take (it reads nothing that launch writes): a
 // point probe of an E component (kind 0, field below 3), a film's mean M (kind
-// 1), or a film's energy (kind 2) whose partials another launch has written; a
-// wavefront sums at most eight rounds of 256 of them
+// 1), or an energy whose partials another launch has written: a film's (kind
+// 2), which a wavefront sums in at most eight rounds of 256, or the grid's
+// (kind 3), whose sum takes the longer the more tiles the launch has beside it
+// (160 x 144 x 128 in float64: 20 us in the probe launch at a step that
+// samples, 5 us for a film's mean M alone at the others)
 __host__ __device__ inline bool probe_folds(const ProbeDev &P) {
-    return (P.kind == 0 && P.field < 3) || P.kind == 1 || (P.kind == 2 && P.npart <= 2048);
+    return (P.kind == 0 && P.field < 3) || P.kind == 1 || (P.kind == 2 && P.npart <= 2048) ||
+           P.kind == 3;
 }
 
 // Coefficients of an edge, computed on the host with the same operation

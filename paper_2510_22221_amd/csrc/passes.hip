@@ -376,18 +376,22 @@ __global__ void __launch_bounds__(TX *TY) k_hbulk(KParams<T> p, int inc_step) {
 // tid: the thread's index in its block of 256
 template <typename T>
 __device__ __forceinline__ void probe_block(const KParams<T> &p, int nprobe, int inc_step, int tid) {
-    if (tid >= 64) return; // one wavefront does it all
     const long long step = p.step[0];
     for (int pb = 0; pb < nprobe; pb++) {
         const ProbeDev &P = p.probes[pb];
         long long sample;
-        if (!probe_due(P, step, sample)) continue; // uniform over the wavefront
+        if (!probe_due(P, step, sample)) continue; // uniform over the block
         double v[3] = {0.0, 0.0, 0.0};
-        folded_probe_values(p, P, v);
-        probe_store(p, P, sample, v);
+        if (P.kind == 3) {
+            double sum[2];
+            block_order_sum_pairs(P.part, P.npart, sum);
+            v[0] = 0.5 * p.dV * (sum[0] + p.mu0 * sum[1]);
+        } else if (tid < 64) // one wavefront does it all
+            folded_probe_values(p, P, v);
+        if (tid < 64) probe_store(p, P, sample, v);
     }
-    // lane 0 advances the counter after every lane has read it (one
-    // wavefront: its reads above precede this store)
+    // the counter advances after every thread has read it
+    __syncthreads();
     if (inc_step && tid == 0) p.step[0] = step + 1;
 }
 

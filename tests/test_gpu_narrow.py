@@ -93,3 +93,27 @@ def test_batch_of_folded_and_unfolded_members_bitwise(prec):
     b.close()
     for s, _ in members:
         s.close()
+
+
+@pytest.mark.parametrize("prec", [mpx.F64, mpx.F32])
+@pytest.mark.parametrize("n", [(23, 13, 11), (301, 141, 13)])
+def test_grid_energy_beside_the_hm_pass_bitwise(prec, n):
+    # 13 partials, and 2156 (more than a launch has blocks for)
+    w = W.random_case(9, nx=n[0], ny=n[1], nz=n[2], bc=(W.PERIODIC, W.PERIODIC, W.PEC, W.PEC, W.PEC, W.PEC),
+                      film=True, nsteps=sum(CALLS))
+    w.probes = []
+    out = []
+    for with_h in (False, True):
+        print(f"{n}, H probe={with_h}, prec={prec}", flush=True)
+        s = mpx.from_workload(w, precision=prec, graph_steps=4)
+        pids = [(s.add_probe(mpx.PROBE_EM_ENERGY, cap=64), 1), (s.add_probe(mpx.PROBE_EM_ENERGY, cap=64, every=3), 1)]
+        if with_h:
+            s.add_probe(mpx.PROBE_FIELD, field=4, ijk=(7, 5, 4), cap=64)
+        for c in CALLS:
+            s.step(c)
+        s.sync()
+        out.append(state(s, pids))
+        s.close()
+    same(out[0], out[1], n)
+    t, t3 = out[0][12], out[0][13]
+    assert np.all(t > 0.0) and np.array_equal(t[2::3], t3)
