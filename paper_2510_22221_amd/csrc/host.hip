@@ -338,7 +338,7 @@ void fill_params(const mpx_sim *s, KParams<T> &p, int mode = MODE_INPLACE, int p
     p.srcs = s->d_srcs;
     p.pflags = s->d_pflags;
     p.pflags_w = s->d_pflags_w;
-    p.wide = s->d_pflags_w != nullptr && !s->narrow;
+    p.wide = s->narrow ? -1 : s->d_pflags_w != nullptr;
     p.mixed = s->d_mixed;
     p.nmixed = s->nmixed;
     p.cls16 = s->d_cls16;

@@ -122,8 +122,9 @@ struct KParams {
     const uint8_t *id;
     const uint8_t *cls; // per slot: the shared id of the 8 cells around it, or 255
     const uint8_t *pflags; // per separate-pass tile: 1 CPML, 2 source, 4 film within reach
-    // wide = 1: the single-instance passes use 256 x 1 tiles (rows of at least
-    // two tiles), with their flags in pflags_w; batches keep the 64 x 4 tiles
+    // wide = 1: rows of at least two 256-slot tiles, with flags per 256 x 1
+    // tile in pflags_w; -1: the single-instance passes use 64 x 4 tiles whatever
+    // the grid, as batches do
     const uint8_t *pflags_w;
     int wide;
     // slots of the mixed class left out of the 16-bit classes: (i, j, k,

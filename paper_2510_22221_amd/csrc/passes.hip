@@ -1,5 +1,5 @@
 // passes.hip -- the separate-pass schedule: an E pass, then an H/M pass, each
-// in place with one thread per slot (blocks of 64 x 4 slots of one plane).
+// in place with one or two slots a thread (blocks of 256 threads on one plane).
 // Also the bracket half steps of every schedule (an H/M pass with one half
 // step) and the E pass of a call's last step.
 //
@@ -7,7 +7,7 @@
 // follows eq. iterate_H, and eq. iterate_H with M = 0 for non-magnetic faces
 // (the magnetic ones are the film kernels' work).
 //
-// Memory access: a wavefront is 64 slots of one row (rows.h), so every array
+// Memory access: a wavefront is 64 or 128 slots of one row (rows.h), so every array
 // is read at a uniform plane base and a 32-bit lane offset; rows, slabs and
 // their coefficients are scalar.  One path serves interior and boundary.
 // Per-tile source / film flags come from a host table (one per tile shape);
@@ -57,11 +57,12 @@ __device__ __forceinline__ double src_current(const KParams<T> &p, int C, int i,
 // launch differ; the test is uniform over a member's lanes).  f: the tile's
 // flag byte, first used after every field load has been issued (so that the
 // loads do not wait for it).
-template <typename T, int CLS, bool TAPE = false>
+template <typename T, int CLS, int V = 1, bool TAPE = false>
 __device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, int f, const BoxTape &bt = BoxTape()) {
     if (r.j >= p.n[1]) return; // a partial tile's row (uniform)
     const unsigned es = (unsigned)sizeof(T);
-    const int ic = min(r.i, p.n[0] - 1), j = r.j, k = r.k;
+    // the lane's first slot, clamped to the row's last whole or partial group
+    const int ic = min(r.i, (p.n[0] - 1) & -V), j = r.j, k = r.k;
     const long long sz = (long long)p.px * p.n[1];
     const unsigned io = (unsigned)ic * es, rowb = (unsigned)p.px * es, vo = io + (unsigned)j * rowb;
     // the -1 neighbours: wrapped on a periodic axis, any in-range value at a wall
@@ -72,129 +73,204 @@ __device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, 
     // the class first: its coefficient row is the one load that waits for another
     bool c16 = CLS == 1;
     if constexpr (CLS == 2) c16 = p.cls16 != nullptr;
-    int c0;
-    if constexpr (CLS == 0)
-        c0 = row_ld<true>(p.cls + zo, (unsigned)ic + (unsigned)j * (unsigned)p.px);
-    else if constexpr (CLS == 1)
-        c0 = row_ld<true>(p.cls16 + zo, 2u * ((unsigned)ic + (unsigned)j * (unsigned)p.px));
-    else if (c16)
-        c0 = row_ld(p.cls16 + zo, 2u * ((unsigned)ic + (unsigned)j * (unsigned)p.px));
-    else
-        c0 = row_ld(p.cls + zo, (unsigned)ic + (unsigned)j * (unsigned)p.px);
+    int c0[V];
+    {
+        const unsigned vc = (unsigned)ic + (unsigned)j * (unsigned)p.px;
+        if (c16) {
+            uint16_t c[V];
+            row_ldv<V, CLS != 2>(p.cls16 + zo, 2u * vc, c);
+#pragma unroll
+            for (int v = 0; v < V; v++) c0[v] = c[v];
+        } else {
+            uint8_t c[V];
+            row_ldv<V, CLS != 2>(p.cls + zo, vc, c);
+#pragma unroll
+            for (int v = 0; v < V; v++) c0[v] = c[v];
+        }
+    }
     const T *Hx = p.H[0] + zo, *Hy = p.H[1] + zo, *Hz = p.H[2] + zo;
     // the -z plane's H is read here for the last time (the tiles of its own
     // plane and of the next row read it before): non-temporal
-    const T hx0 = row_ld(Hx, vo), hx_km = row_ld<true>(p.H[0] + zb, vo), hx_ym = row_ld(Hx, vym);
-    const T hy0 = row_ld(Hy, vo), hy_km = row_ld<true>(p.H[1] + zb, vo), hy_xm = row_ld(Hy, vxm);
-    const T hz0 = row_ld(Hz, vo), hz_xm = row_ld(Hz, vxm), hz_ym = row_ld(Hz, vym);
+    T hx0[V], hx_km[V], hx_ym[V], hy0[V], hy_km[V], hy_xm[V], hz0[V], hz_xm[V], hz_ym[V];
+    row_ldv<V>(Hx, vo, hx0);
+    row_ldv<V, true>(p.H[0] + zb, vo, hx_km);
+    row_ldv<V>(Hx, vym, hx_ym);
+    row_ldv<V>(Hy, vo, hy0);
+    row_ldv<V, true>(p.H[1] + zb, vo, hy_km);
+    hy_xm[0] = row_ld(Hy, vxm);
+    row_ldv<V>(Hz, vo, hz0);
+    hz_xm[0] = row_ld(Hz, vxm);
+    row_ldv<V>(Hz, vym, hz_ym);
     // E, the class and the new E are touched once per pass: non-temporal, so
     // that they leave L2 first and the H rows and planes the neighbouring
     // tiles read again, and the coefficient rows, stay
     T *Ex = p.E[0] + zo, *Ey = p.E[1] + zo, *Ez = p.E[2] + zo;
-    const T e0 = row_ld<true>(Ex, vo), e1 = row_ld<true>(Ey, vo), e2 = row_ld<true>(Ez, vo);
-    RowPml<T> m = row_pml<T, true>(p, r, io);
-    // the slot's six coefficients in one or two wide loads (a slot on the
+    T e0[V], e1[V], e2[V];
+    row_ldv<V, true>(Ex, vo, e0);
+    row_ldv<V, true>(Ey, vo, e1);
+    row_ldv<V, true>(Ez, vo, e2);
+    RowPml<T, V> m = row_pml<T, true, V>(p, r, io);
+    // the slots' six coefficients in one or two wide loads (a slot on the
     // mixed list, class byte 255 or 16-bit class 0xffff, reads row 0 and uses
     // none)
     const int kSkip = c16 ? 0xffff : kMixed;
-    const CoefRow<T> L = coef_row<T>(p.coefv, c0 == kSkip ? 0 : c0);
+#pragma unroll
+    for (int v = 1; v < V; v++)
+        if (ic + v >= p.n[0]) c0[v] = kSkip; // past the row: no class there
+    CoefRow<T> L[V];
+    // one class for the whole wavefront (most are inside one material): its
+    // row comes through the scalar cache, not as a gather of 24 (48) bytes a
+    // lane.  E pass, 512 x 256 x 128 float32 128 -> 122 us, 211 x 109 x 77
+    // float64 40.9 -> 37.4; a layout with a class for every block of cells, so
+    // many that it needs 16 bits, only pays for the test (866 -> 871)
+    const int cu = __builtin_amdgcn_readfirstlane(c0[0]);
+    bool same = true;
+#pragma unroll
+    for (int v = 0; v < V; v++) same = same && (c0[v] == cu || (v > 0 && ic + v >= p.n[0]));
+    if (CLS != 1 && __builtin_amdgcn_ballot_w64(!same) == 0) {
+        const T *q = p.coefv + kCoefRow<T> * (long long)(cu == kSkip ? 0 : cu);
+        CoefRow<T> S;
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            S.ca[c] = scalar_ld(q, 2 * c);
+            S.cb[c] = scalar_ld(q, 2 * c + 1);
+        }
+#pragma unroll
+        for (int v = 0; v < V; v++) L[v] = S;
+    } else {
+#pragma unroll
+        for (int v = 0; v < V; v++) L[v] = coef_row<T>(p.coefv, c0[v] == kSkip ? 0 : c0[v]);
+    }
+#pragma unroll
+    for (int v = 1; v < V; v++) {
+        hy_xm[v] = hy0[v - 1];
+        hz_xm[v] = hz0[v - 1];
+    }
     const T dx = p.dT[0], dy = p.dT[1], dz = p.dT[2], ix = p.invd[0], iy = p.invd[1], iz = p.invd[2];
-    // E_x: along y then z; E_y: z, x; E_z: x, y
-    T ay = dif(hz0, hz_ym, dy, iy), az = dif(hy0, hy_km, dz, iz);
-    T bz = dif(hx0, hx_km, dz, iz), bx = dif(hz0, hz_xm, dx, ix);
-    T cx = dif(hy0, hy_xm, dx, ix), cy = dif(hx0, hx_ym, dy, iy);
     // an edge on a lower wall (an axis other than its own) or on a conductor
     // (cb = 0) stays zero and keeps its psi
-    const bool ox = r.i > 0 || p.per[0], oy = j > 0 || p.per[1], oz = k > 0 || p.per[2];
-    const bool u0 = oy && oz && L.cb[0] != T(0), u1 = ox && oz && L.cb[1] != T(0), u2 = ox && oy && L.cb[2] != T(0);
-    if (m.wx) {
-        pml_step_if(m.sx, m.xy, m.bx, m.cx, bx);
-        pml_step_if(m.sx, m.xz, m.bx, m.cx, cx);
-    }
-    if (m.wy) {
-        pml_step(m.yx, m.by, m.cy, ay);
-        pml_step(m.yz, m.by, m.cy, cy);
-    }
-    if (m.wz) {
-        pml_step(m.zx, m.bz, m.cz, az);
-        pml_step(m.zy, m.bz, m.cz, bz);
-    }
-    T x0 = ay - az, x1 = bz - bx, x2 = cx - cy;
-    double xt[3] = {(double)x0, (double)x1, (double)x2}; // TAPE
-    (void)xt;
-    if (f & 2) {
-        const long long step = p.step[0];
-        // (x - 0) is x bitwise, so subtracting only here matches the plain form
-        const double J0 = src_current(p, 0, r.i, j, k, step), J1 = src_current(p, 1, r.i, j, k, step),
-                     J2 = src_current(p, 2, r.i, j, k, step);
-        if constexpr (TAPE) {
-            xt[0] = (double)x0 - J0;
-            xt[1] = (double)x1 - J1;
-            xt[2] = (double)x2 - J2;
+    const bool oy = j > 0 || p.per[1], oz = k > 0 || p.per[2];
+    bool s0[V], s1[V], s2[V], ok[V]; // the edge's psi moves; the slot is stored
+    T n0[V], n1[V], n2[V];
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+        // E_x: along y then z; E_y: z, x; E_z: x, y
+        T ay = dif(hz0[v], hz_ym[v], dy, iy), az = dif(hy0[v], hy_km[v], dz, iz);
+        T bz = dif(hx0[v], hx_km[v], dz, iz), bx = dif(hz0[v], hz_xm[v], dx, ix);
+        T cx = dif(hy0[v], hy_xm[v], dx, ix), cy = dif(hx0[v], hx_ym[v], dy, iy);
+        const bool ox = r.i + v > 0 || p.per[0];
+        const bool u0 = oy && oz && L[v].cb[0] != T(0), u1 = ox && oz && L[v].cb[1] != T(0),
+                   u2 = ox && oy && L[v].cb[2] != T(0);
+        if (m.wx) {
+            pml_step_if(m.sx[v], m.xy[v], m.bx[v], m.cx[v], bx);
+            pml_step_if(m.sx[v], m.xz[v], m.bx[v], m.cx[v], cx);
         }
-        x0 = x0 - T(J0);
-        x1 = x1 - T(J1);
-        x2 = x2 - T(J2);
-    }
-    if constexpr (TAPE) {
-        const int rb[3] = {bt.size[0] + 1, bt.size[1] + 1, bt.size[2] + 1};
-        int lj = j - bt.b0[1], lk = k - bt.b0[2], li = r.i - bt.b0[0];
-        if (lj < 0 && p.per[1]) lj += p.n[1];
-        if (lk < 0 && p.per[2]) lk += p.n[2];
-        if (lj >= 0 && lj < rb[1] && lk >= 0 && lk < rb[2]) { // uniform
-            if (li < 0 && p.per[0]) li += p.n[0];
-            if (r.in && li >= 0 && li < rb[0]) {
-                const long long tb = (long long)rb[0] * rb[1] * rb[2];
-                double *d = bt.dst + li + (long long)rb[0] * ((long long)lj + (long long)rb[1] * lk);
-                d[0] = (double)e0;
-                d[tb] = (double)e1;
-                d[2 * tb] = (double)e2;
-                d[3 * tb] = xt[0];
-                d[4 * tb] = xt[1];
-                d[5 * tb] = xt[2];
+        if (m.wy) {
+            pml_step(m.yx[v], m.by, m.cy, ay);
+            pml_step(m.yz[v], m.by, m.cy, cy);
+        }
+        if (m.wz) {
+            pml_step(m.zx[v], m.bz, m.cz, az);
+            pml_step(m.zy[v], m.bz, m.cz, bz);
+        }
+        T x0 = ay - az, x1 = bz - bx, x2 = cx - cy;
+        double xt[3] = {(double)x0, (double)x1, (double)x2}; // TAPE
+        (void)xt;
+        if (f & 2) {
+            const long long step = p.step[0];
+            // (x - 0) is x bitwise, so subtracting only here matches the plain form
+            const double J0 = src_current(p, 0, r.i + v, j, k, step), J1 = src_current(p, 1, r.i + v, j, k, step),
+                         J2 = src_current(p, 2, r.i + v, j, k, step);
+            if constexpr (TAPE) {
+                xt[0] = (double)x0 - J0;
+                xt[1] = (double)x1 - J1;
+                xt[2] = (double)x2 - J2;
+            }
+            x0 = x0 - T(J0);
+            x1 = x1 - T(J1);
+            x2 = x2 - T(J2);
+        }
+        ok[v] = r.i + v < p.n[0] && c0[v] != kSkip;
+        if constexpr (TAPE) {
+            const int rb[3] = {bt.size[0] + 1, bt.size[1] + 1, bt.size[2] + 1};
+            int lj = j - bt.b0[1], lk = k - bt.b0[2], li = r.i + v - bt.b0[0];
+            if (lj < 0 && p.per[1]) lj += p.n[1];
+            if (lk < 0 && p.per[2]) lk += p.n[2];
+            if (lj >= 0 && lj < rb[1] && lk >= 0 && lk < rb[2]) { // uniform
+                if (li < 0 && p.per[0]) li += p.n[0];
+                if (r.i + v < p.n[0] && li >= 0 && li < rb[0]) {
+                    const long long tb = (long long)rb[0] * rb[1] * rb[2];
+                    double *d = bt.dst + li + (long long)rb[0] * ((long long)lj + (long long)rb[1] * lk);
+                    d[0] = (double)e0[v];
+                    d[tb] = (double)e1[v];
+                    d[2 * tb] = (double)e2[v];
+                    d[3 * tb] = xt[0];
+                    d[4 * tb] = xt[1];
+                    d[5 * tb] = xt[2];
+                }
             }
         }
+        n0[v] = u0 ? L[v].ca[0] * e0[v] + L[v].cb[0] * x0 : T(0);
+        n1[v] = u1 ? L[v].ca[1] * e1[v] + L[v].cb[1] * x1 : T(0);
+        n2[v] = u2 ? L[v].ca[2] * e2[v] + L[v].cb[2] * x2 : T(0);
+        s0[v] = ok[v] && u0;
+        s1[v] = ok[v] && u1;
+        s2[v] = ok[v] && u2;
     }
-    if (!r.in || c0 == kSkip) return;
-    row_st<true>(Ex, vo, u0 ? L.ca[0] * e0 + L.cb[0] * x0 : T(0));
-    row_st<true>(Ey, vo, u1 ? L.ca[1] * e1 + L.cb[1] * x1 : T(0));
-    row_st<true>(Ez, vo, u2 ? L.ca[2] * e2 + L.cb[2] * x2 : T(0));
-    if (m.wx && m.sx) {
+    row_stv<V, true>(Ex, vo, n0, ok);
+    row_stv<V, true>(Ey, vo, n1, ok);
+    row_stv<V, true>(Ez, vo, n2, ok);
+    if (m.wx) {
         const long long q = row_psi(p, 0, j, k);
-        if (u1) row_st(p.psiE[1][0] + q, m.ox, m.xy);
-        if (u2) row_st(p.psiE[2][0] + q, m.ox, m.xz);
+#pragma unroll
+        for (int v = 0; v < V; v++)
+            if (m.sx[v]) {
+                if (s1[v]) row_st(p.psiE[1][0] + q, m.ox[v], m.xy[v]);
+                if (s2[v]) row_st(p.psiE[2][0] + q, m.ox[v], m.xz[v]);
+            }
     }
     if (m.wy) {
         const long long q = row_psi(p, 1, j, k);
-        if (u0) row_st<true>(p.psiE[0][1] + q, io, m.yx);
-        if (u2) row_st<true>(p.psiE[2][1] + q, io, m.yz);
+        row_stv<V, true>(p.psiE[0][1] + q, io, m.yx, s0);
+        row_stv<V, true>(p.psiE[2][1] + q, io, m.yz, s2);
     }
     if (m.wz) {
         const long long q = row_psi(p, 2, j, k);
-        if (u0) row_st<true>(p.psiE[0][2] + q, io, m.zx);
-        if (u1) row_st<true>(p.psiE[1][2] + q, io, m.zy);
+        row_stv<V, true>(p.psiE[0][2] + q, io, m.zx, s0);
+        row_stv<V, true>(p.psiE[1][2] + q, io, m.zy, s1);
     }
 }
 
-// the flag byte of tile (bx, by, k) of the TX x TY table, read through the
-// scalar cache (the aligned word that holds it; the tables are whole words):
-// a vector load here would put the field loads behind its wait, since the
-// vector memory counter completes in order
-template <typename T, int TX, int TY>
-__device__ __forceinline__ int tile_flag(const KParams<T> &p, int bx, int by, int k) {
-    const int nxt = (p.n[0] + TX - 1) / TX, nyt = (p.n[1] + TY - 1) / TY;
+// the flags of a wavefront's row: those of its tiles (one of 256 x 1 slots on
+// a wide grid, else V of 64 x 4), read through the scalar cache (the aligned
+// word that holds each; the tables are whole words): a vector load here would
+// put the field loads behind its wait, since the vector memory counter
+// completes in order.  A wavefront past the row reads the row's last tile.
+template <typename T, int V>
+__device__ __forceinline__ int row_flags(const KParams<T> &p, const RowPos &r, bool wide) {
     typedef __attribute__((address_space(4))) const uint32_t cword;
-    const long long ti = bx + (long long)nxt * (by + (long long)nyt * k);
-    const uint32_t w = ((cword *)(TX == PTX ? p.pflags : p.pflags_w))[ti >> 2];
-    return (int)((w >> (8 * (int)(ti & 3))) & 0xffu);
+    const int tx = wide ? kWideTX : PTX, ty = wide ? kWideTY : PTY;
+    const int nxt = (p.n[0] + tx - 1) / tx, nyt = (p.n[1] + ty - 1) / ty;
+    const cword *tab = (cword *)(wide ? p.pflags_w : p.pflags);
+    const int bx = min(r.w0 / tx, nxt - 1), by = min(r.j, p.n[1] - 1) / ty;
+    const long long t0 = (long long)nxt * (by + (long long)nyt * r.k);
+    int f = 0;
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+        const long long ti = t0 + min(bx + v, nxt - 1);
+        f |= (int)(tab[ti >> 2] >> (8 * (int)(ti & 3)));
+        if (wide) break;
+    }
+    return f & 0xff;
 }
 
-// a block: the TX x TY slots (bx, by) of plane k, flags from the table of
-// that tile shape
-template <typename T, int CLS, int TX = PTX, int TY = PTY, bool TAPE = false>
+// a block of 64 x 4 threads: 64 V WX x 4 / WX slots (bx, by) of plane k
+template <typename T, int CLS, int V, int WX, bool WIDE, bool TAPE = false>
 __device__ __forceinline__ void epass_block(const KParams<T> &p, int bx, int by, int k,
                                             const BoxTape &bt = BoxTape()) {
-    epass_row<T, CLS, TAPE>(p, row_pos<TX>(p.n, bx, by, TY, k), tile_flag<T, TX, TY>(p, bx, by, k), bt);
+    const RowPos r = row_pos_v<V, WX>(p.n, bx, by, k);
+    if (r.w0 >= p.n[0]) return; // uniform: a wavefront past the row
+    epass_row<T, CLS, V, TAPE>(p, r, row_flags<T, V>(p, r, WIDE), bt);
 }
 
 // the mixed slots, one thread each: the general path (folded loads; edge
@@ -237,124 +313,155 @@ __device__ __forceinline__ void emixed_slot(const KParams<T> &p, int m) {
 // on a periodic axis and reads zero at a wall (the E there is tangential to
 // it); lanes past the domain store nothing.
 // ---------------------------------------------------------------------------
-template <typename T, int NHALF>
+template <typename T, int NHALF, int V = 1>
 __device__ __forceinline__ void hpass_row(const KParams<T> &p, const RowPos &r, int f) {
     if (r.j >= p.n[1]) return; // a partial tile's row (uniform)
     const unsigned es = (unsigned)sizeof(T);
-    const int ic = min(r.i, p.n[0] - 1), j = r.j, k = r.k;
+    const int ic = min(r.i, (p.n[0] - 1) & -V), j = r.j, k = r.k;
     const long long sz = (long long)p.px * p.n[1];
     const unsigned io = (unsigned)ic * es, rowb = (unsigned)p.px * es, vo = io + (unsigned)j * rowb;
     // the +1 neighbours: wrapped on a periodic axis; past a wall the own
     // value is read and dropped
-    const bool wlx = !p.per[0] && ic + 1 >= p.n[0], wly = !p.per[1] && j + 1 >= p.n[1],
-               wlz = !p.per[2] && k + 1 >= p.n[2];
-    const unsigned vxp = ic + 1 < p.n[0] ? vo + es : (p.per[0] ? vo - (unsigned)(p.n[0] - 1) * es : vo);
+    const bool wly = !p.per[1] && j + 1 >= p.n[1], wlz = !p.per[2] && k + 1 >= p.n[2];
+    const unsigned vxp = ic + V < p.n[0] ? vo + V * es : (p.per[0] ? vo - io : vo);
     const unsigned jp = (unsigned)(j + 1 < p.n[1] ? j + 1 : (p.per[1] ? 0 : j)), vyp = io + jp * rowb;
     const int ka = k + 1 < p.n[2] ? k + 1 : (p.per[2] ? 0 : k);
     const long long zo = k * sz, za = ka * sz;
     const T *Ex = p.E[0] + zo, *Ey = p.E[1] + zo, *Ez = p.E[2] + zo;
-    T ex0 = row_ld(Ex, vo), ex_yp = row_ld(Ex, vyp), ex_kp = row_ld(p.E[0] + za, vo);
-    T ey0 = row_ld(Ey, vo), ey_xp = row_ld(Ey, vxp), ey_kp = row_ld(p.E[1] + za, vo);
-    T ez0 = row_ld(Ez, vo), ez_xp = row_ld(Ez, vxp), ez_yp = row_ld(Ez, vyp);
+    T ex0[V], ex_yp[V], ex_kp[V], ey0[V], ey_xp[V], ey_kp[V], ez0[V], ez_xp[V], ez_yp[V];
+    row_ldv<V>(Ex, vo, ex0);
+    row_ldv<V>(Ex, vyp, ex_yp);
+    row_ldv<V>(p.E[0] + za, vo, ex_kp);
+    row_ldv<V>(Ey, vo, ey0);
+    const T ey_nx = row_ld(Ey, vxp); // the slot after the lane's last
+    row_ldv<V>(p.E[1] + za, vo, ey_kp);
+    row_ldv<V>(Ez, vo, ez0);
+    const T ez_nx = row_ld(Ez, vxp);
+    row_ldv<V>(Ez, vyp, ez_yp);
     // H and the new H are touched once per pass: non-temporal (the E halo
     // stays in L2)
     T *Hx = p.H[0] + zo, *Hy = p.H[1] + zo, *Hz = p.H[2] + zo;
-    T h0 = row_ld<true>(Hx, vo), h1 = row_ld<true>(Hy, vo), h2 = row_ld<true>(Hz, vo);
-    RowPml<T> m = row_pml<T, false>(p, r, io);
+    T h0[V], h1[V], h2[V];
+    row_ldv<V, true>(Hx, vo, h0);
+    row_ldv<V, true>(Hy, vo, h1);
+    row_ldv<V, true>(Hz, vo, h2);
+    RowPml<T, V> m = row_pml<T, false, V>(p, r, io);
     // the tile's flags, first used after every field load has been issued
-    bool mag[3] = {false, false, false};
+    bool st0[V], st1[V], st2[V]; // stored: not past the row, not magnetic
+#pragma unroll
+    for (int v = 0; v < V; v++) st0[v] = st1[v] = st2[v] = r.i + v < p.n[0];
     if ((f & 4) && r.in) {
-        const int idx[3] = {ic, j, k};
-        mag[0] = face_is_magnetic(p, 0, idx);
-        mag[1] = face_is_magnetic(p, 1, idx);
-        mag[2] = face_is_magnetic(p, 2, idx);
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const int idx[3] = {min(ic + v, p.n[0] - 1), j, k};
+            st0[v] = st0[v] && !face_is_magnetic(p, 0, idx);
+            st1[v] = st1[v] && !face_is_magnetic(p, 1, idx);
+            st2[v] = st2[v] && !face_is_magnetic(p, 2, idx);
+        }
     }
-    ey_xp = wlx ? T(0) : ey_xp;
-    ez_xp = wlx ? T(0) : ez_xp;
-    if (wly) ex_yp = ez_yp = T(0);
-    if (wlz) ex_kp = ey_kp = T(0);
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+        // inside the lane's group the next slot's, unless the row ends there
+        // (a wall reads zero)
+        const bool end = ic + v + 1 >= p.n[0];
+        const T a = v + 1 < V ? ey0[v + 1 < V ? v + 1 : v] : ey_nx, b = v + 1 < V ? ez0[v + 1 < V ? v + 1 : v] : ez_nx;
+        ey_xp[v] = end ? (p.per[0] ? ey_nx : T(0)) : a;
+        ez_xp[v] = end ? (p.per[0] ? ez_nx : T(0)) : b;
+    }
+    if (wly)
+#pragma unroll
+        for (int v = 0; v < V; v++) ex_yp[v] = ez_yp[v] = T(0);
+    if (wlz)
+#pragma unroll
+        for (int v = 0; v < V; v++) ex_kp[v] = ey_kp[v] = T(0);
     const T dx = p.dT[0], dy = p.dT[1], dz = p.dT[2], ix = p.invd[0], iy = p.invd[1], iz = p.invd[2];
-    const T ay = dif(ez_yp, ez0, dy, iy), az = dif(ey_kp, ey0, dz, iz);
-    const T bz = dif(ex_kp, ex0, dz, iz), bx = dif(ez_xp, ez0, dx, ix);
-    const T cx = dif(ey_xp, ey0, dx, ix), cy = dif(ex_yp, ex0, dy, iy);
-    if (m.wx || m.wy || m.wz) {
+    const bool pml = m.wx || m.wy || m.wz;
 #pragma unroll
-        for (int hs = 0; hs < NHALF; hs++) {
-            T a1 = ay, a2 = az, b1 = bz, b2 = bx, c1 = cx, c2 = cy;
-            if (m.wx) {
-                pml_step_if(m.sx, m.xy, m.bx, m.cx, b2);
-                pml_step_if(m.sx, m.xz, m.bx, m.cx, c1);
-            }
-            if (m.wy) {
-                pml_step(m.yx, m.by, m.cy, a1);
-                pml_step(m.yz, m.by, m.cy, c2);
-            }
-            if (m.wz) {
-                pml_step(m.zx, m.bz, m.cz, a2);
-                pml_step(m.zy, m.bz, m.cz, b1);
-            }
-            h0 = h0 - p.hc * (a1 - a2);
-            h1 = h1 - p.hc * (b1 - b2);
-            h2 = h2 - p.hc * (c1 - c2);
-        }
-    } else {
-        const T g0 = p.hc * (ay - az), g1 = p.hc * (bz - bx), g2 = p.hc * (cx - cy);
+    for (int v = 0; v < V; v++) {
+        const T ay = dif(ez_yp[v], ez0[v], dy, iy), az = dif(ey_kp[v], ey0[v], dz, iz);
+        const T bz = dif(ex_kp[v], ex0[v], dz, iz), bx = dif(ez_xp[v], ez0[v], dx, ix);
+        const T cx = dif(ey_xp[v], ey0[v], dx, ix), cy = dif(ex_yp[v], ex0[v], dy, iy);
+        if (pml) {
 #pragma unroll
-        for (int hs = 0; hs < NHALF; hs++) {
-            h0 = h0 - g0;
-            h1 = h1 - g1;
-            h2 = h2 - g2;
+            for (int hs = 0; hs < NHALF; hs++) {
+                T a1 = ay, a2 = az, b1 = bz, b2 = bx, c1 = cx, c2 = cy;
+                if (m.wx) {
+                    pml_step_if(m.sx[v], m.xy[v], m.bx[v], m.cx[v], b2);
+                    pml_step_if(m.sx[v], m.xz[v], m.bx[v], m.cx[v], c1);
+                }
+                if (m.wy) {
+                    pml_step(m.yx[v], m.by, m.cy, a1);
+                    pml_step(m.yz[v], m.by, m.cy, c2);
+                }
+                if (m.wz) {
+                    pml_step(m.zx[v], m.bz, m.cz, a2);
+                    pml_step(m.zy[v], m.bz, m.cz, b1);
+                }
+                h0[v] = h0[v] - p.hc * (a1 - a2);
+                h1[v] = h1[v] - p.hc * (b1 - b2);
+                h2[v] = h2[v] - p.hc * (c1 - c2);
+            }
+        } else {
+            const T g0 = p.hc * (ay - az), g1 = p.hc * (bz - bx), g2 = p.hc * (cx - cy);
+#pragma unroll
+            for (int hs = 0; hs < NHALF; hs++) {
+                h0[v] = h0[v] - g0;
+                h1[v] = h1[v] - g1;
+                h2[v] = h2[v] - g2;
+            }
         }
     }
-    if (!r.in) return;
-    if (!mag[0]) row_st<true>(Hx, vo, h0);
-    if (!mag[1]) row_st<true>(Hy, vo, h1);
-    if (!mag[2]) row_st<true>(Hz, vo, h2);
-    if (m.wx && m.sx) {
+    row_stv<V, true>(Hx, vo, h0, st0);
+    row_stv<V, true>(Hy, vo, h1, st1);
+    row_stv<V, true>(Hz, vo, h2, st2);
+    if (m.wx) {
         const long long q = row_psi(p, 0, j, k);
-        if (!mag[1]) row_st(p.psiH[1][0] + q, m.ox, m.xy);
-        if (!mag[2]) row_st(p.psiH[2][0] + q, m.ox, m.xz);
+#pragma unroll
+        for (int v = 0; v < V; v++)
+            if (m.sx[v]) {
+                if (st1[v]) row_st(p.psiH[1][0] + q, m.ox[v], m.xy[v]);
+                if (st2[v]) row_st(p.psiH[2][0] + q, m.ox[v], m.xz[v]);
+            }
     }
     if (m.wy) {
         const long long q = row_psi(p, 1, j, k);
-        if (!mag[0]) row_st<true>(p.psiH[0][1] + q, io, m.yx);
-        if (!mag[2]) row_st<true>(p.psiH[2][1] + q, io, m.yz);
+        row_stv<V, true>(p.psiH[0][1] + q, io, m.yx, st0);
+        row_stv<V, true>(p.psiH[2][1] + q, io, m.yz, st2);
     }
     if (m.wz) {
         const long long q = row_psi(p, 2, j, k);
-        if (!mag[0]) row_st<true>(p.psiH[0][2] + q, io, m.zx);
-        if (!mag[1]) row_st<true>(p.psiH[1][2] + q, io, m.zy);
+        row_stv<V, true>(p.psiH[0][2] + q, io, m.zx, st0);
+        row_stv<V, true>(p.psiH[1][2] + q, io, m.zy, st1);
     }
 }
 
-template <typename T, int NHALF, int TX = PTX, int TY = PTY>
+template <typename T, int NHALF, int V, int WX, bool WIDE>
 __device__ __forceinline__ void hpass_block(const KParams<T> &p, int bx, int by, int k) {
-    hpass_row<T, NHALF>(p, row_pos<TX>(p.n, bx, by, TY, k), tile_flag<T, TX, TY>(p, bx, by, k));
+    const RowPos r = row_pos_v<V, WX>(p.n, bx, by, k);
+    if (r.w0 >= p.n[0]) return; // uniform: a wavefront past the row
+    hpass_row<T, NHALF, V>(p, r, row_flags<T, V>(p, r, WIDE));
 }
 
 // grid (x tiles, y tiles, planes) in natural order: the blocks resident at
 // one time cover a few consecutive planes, so neighbour rows and planes are
-// cache hits, and no block decodes its tile with divisions.  Tiles of 64 x 4
-// slots, or on grids at least two wide tiles across, 256 x 1 (each block
-// then reads and writes 256 consecutive slots of every array: measured 5 %
-// (float32) and 9 % (float64) faster per step on a 512-wide grid, slower on
-// narrow ones).  XC: the variant for grids with extended-table slots (16-bit
-// classes).
-template <typename T, int TX, int TY, bool XC>
-__global__ void __launch_bounds__(TX *TY) k_epass(KParams<T> p) {
-    epass_block<T, XC ? 1 : 0, TX, TY>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+// cache hits, and no block decodes its tile with divisions.  The tile is the
+// grid's (with_shape).  XC: the variant for grids with extended-table slots
+// (16-bit classes).
+template <typename T, int V, int WX, bool WIDE, bool XC>
+__global__ void __launch_bounds__(256) k_epass(KParams<T> p) {
+    epass_block<T, XC ? 1 : 0, V, WX, WIDE>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-template <typename T, int TX, int TY, bool XC>
-__global__ void __launch_bounds__(TX *TY) k_epass_tape(KParams<T> p, BoxTape bt) {
-    epass_block<T, XC ? 1 : 0, TX, TY, true>(p, blockIdx.x, blockIdx.y, blockIdx.z, bt);
+template <typename T, int V, int WX, bool WIDE, bool XC>
+__global__ void __launch_bounds__(256) k_epass_tape(KParams<T> p, BoxTape bt) {
+    epass_block<T, XC ? 1 : 0, V, WX, WIDE, true>(p, blockIdx.x, blockIdx.y, blockIdx.z, bt);
 }
 
-template <typename T, int NHALF, int TX, int TY>
-__global__ void __launch_bounds__(TX *TY) k_hbulk(KParams<T> p, int inc_step) {
+template <typename T, int NHALF, int V, int WX, bool WIDE>
+__global__ void __launch_bounds__(256) k_hbulk(KParams<T> p, int inc_step) {
     if (inc_step && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && threadIdx.y == 0)
         p.step[0] = p.step[0] + 1;
-    hpass_block<T, NHALF, TX, TY>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+    hpass_block<T, NHALF, V, WX, WIDE>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // the H/M pass and the film's part of it in one launch: the first zf planes
@@ -403,12 +510,11 @@ __device__ __forceinline__ void film_part(const KParams<T> &p, int blk, int tid)
         film_commit_body(p, blk, tid);
 }
 
-template <typename T, int NHALF, int TX, int TY>
-__global__ void __launch_bounds__(TX *TY) k_hbulk_film(KParams<T> p, int inc_step, int zf, int nfb, int nprobe) {
-    static_assert(TX * TY == 256, "film blocks are 256 threads");
+template <typename T, int NHALF, int V, int WX, bool WIDE>
+__global__ void __launch_bounds__(256) k_hbulk_film(KParams<T> p, int inc_step, int zf, int nfb, int nprobe) {
     if ((int)blockIdx.z < zf) {
         const int fb = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
-        const int tid = (int)threadIdx.x + TX * (int)threadIdx.y;
+        const int tid = (int)threadIdx.x + 64 * (int)threadIdx.y;
         if (fb < nfb)
             film_part<T, NHALF>(p, fb, tid);
         else if (fb == nfb && nprobe > 0)
@@ -419,7 +525,7 @@ __global__ void __launch_bounds__(TX *TY) k_hbulk_film(KParams<T> p, int inc_ste
     if (inc_step && nprobe == 0 && blockIdx.x == 0 && blockIdx.y == 0 && k == 0 && threadIdx.x == 0 &&
         threadIdx.y == 0)
         p.step[0] = p.step[0] + 1;
-    hpass_block<T, NHALF, TX, TY>(p, blockIdx.x, blockIdx.y, k);
+    hpass_block<T, NHALF, V, WX, WIDE>(p, blockIdx.x, blockIdx.y, k);
 }
 
 template <typename T>
@@ -435,7 +541,7 @@ __global__ void __launch_bounds__(PTX *PTY)
     const int w = blockIdx.x;
     if (w >= nwork) return;
     const int4 wk = work[w];
-    epass_block<T, XC ? 2 : 0>(plist[wk.x], wk.y, wk.z, wk.w);
+    epass_block<T, XC ? 2 : 0, 1, 1, false>(plist[wk.x], wk.y, wk.z, wk.w);
 }
 
 // work[w] = (instance, first list entry of a 256-entry block)
@@ -462,7 +568,7 @@ __global__ void __launch_bounds__(PTX *PTY)
     const int4 wk = work[w];
     const KParams<T> &p = plist[wk.x];
     if (wk.y < 0) {
-        const int tid = (int)threadIdx.x + PTX * (int)threadIdx.y;
+        const int tid = (int)threadIdx.x + 64 * (int)threadIdx.y;
         if (wk.y == kBatchProbes)
             probe_block(p, p.nfold, inc_step, tid);
         else
@@ -471,64 +577,95 @@ __global__ void __launch_bounds__(PTX *PTY)
     }
     if (inc_step && p.nfold == 0 && wk.y == 0 && wk.z == 0 && wk.w == 0 && threadIdx.x == 0 && threadIdx.y == 0)
         p.step[0] = p.step[0] + 1;
-    hpass_block<T, NHALF>(p, wk.y, wk.z, wk.w);
+    hpass_block<T, NHALF, 1, 1, false>(p, wk.y, wk.z, wk.w);
 }
 
 int pass_tiles(const int *n) { return ((n[0] + PTX - 1) / PTX) * ((n[1] + PTY - 1) / PTY) * n[2]; }
 
-template <int TX, int TY>
+template <int V, int WX>
 static dim3 pass_grid(const int *n) {
-    return dim3((n[0] + TX - 1) / TX, (n[1] + TY - 1) / TY, n[2]);
+    const int tx = 64 * V * WX, ty = 4 / WX;
+    return dim3((n[0] + tx - 1) / tx, (n[1] + ty - 1) / ty, n[2]);
 }
 
-template <typename T, int TX, int TY>
+template <typename T, int V, int WX, bool WIDE>
 static void launch_e(const KParams<T> &p, hipStream_t s, const BoxTape *tape) {
-    const dim3 g = pass_grid<TX, TY>(p.n), b(TX, TY);
+    const dim3 g = pass_grid<V, WX>(p.n), b(64, 4);
     if (tape && p.cls16)
-        k_epass_tape<T, TX, TY, true><<<g, b, 0, s>>>(p, *tape);
+        k_epass_tape<T, V, WX, WIDE, true><<<g, b, 0, s>>>(p, *tape);
     else if (tape)
-        k_epass_tape<T, TX, TY, false><<<g, b, 0, s>>>(p, *tape);
+        k_epass_tape<T, V, WX, WIDE, false><<<g, b, 0, s>>>(p, *tape);
     else if (p.cls16)
-        k_epass<T, TX, TY, true><<<g, b, 0, s>>>(p);
+        k_epass<T, V, WX, WIDE, true><<<g, b, 0, s>>>(p);
     else
-        k_epass<T, TX, TY, false><<<g, b, 0, s>>>(p);
+        k_epass<T, V, WX, WIDE, false><<<g, b, 0, s>>>(p);
+}
+
+template <typename T, int NHALF, int V, int WX, bool WIDE>
+static void launch_hm(const KParams<T> &p, int nblk, int inc, int nprobe, hipStream_t s) {
+    const dim3 g = pass_grid<V, WX>(p.n), b(64, 4);
+    if (nblk == 0 && nprobe == 0) {
+        k_hbulk<T, NHALF, V, WX, WIDE><<<g, b, 0, s>>>(p, inc);
+        return;
+    }
+    const int per_plane = (int)(g.x * g.y);
+    const int zf = (nblk + (nprobe > 0 ? 1 : 0) + per_plane - 1) / per_plane;
+    k_hbulk_film<T, NHALF, V, WX, WIDE><<<dim3(g.x, g.y, g.z + zf), b, 0, s>>>(p, inc, zf, nblk, nprobe);
+}
+
+// calls f with the shape of a grid's passes: V slots a lane, WX wavefronts
+// side by side in a block's 4 / WX rows, the wide or the 64 x 4 flag table.
+//
+// float64, V = 2: 16-byte loads and stores, half the instructions a slot; 4
+// wavefronts a SIMD instead of 7 still hold more bytes in flight.  E + H/M, us,
+// one slot a lane : two: 128 x 64 x 64 30 : 25, 211 x 109 x 77 78 : 70,
+// 512 x 256 x 128 516 : 480, 1536 x 384 x 64 1126 : 1056.  A row's last
+// wavefront is then emptier: with 160 or 192 slots (62 and 75 % of the lanes
+// instead of 83 and 100 %) 96 : 99 and 38 : 39, so V = 2 asks that 64-slot
+// wavefronts would have at least 90 % as many lanes.
+// float, V = 1: two slots a lane (8-byte loads) lose everywhere (33.4 : 38 us
+// on 256 x 128 x 48), four gain nothing (248 : 259 us on 512 x 256 x 128).
+//
+// WX: a block of several rows fetches fewer -y (+y) rows that another XCD's
+// block fetches too, a longer row fewer planes' worth of partly used lines:
+// 512 x 256 x 128 float 128 x 2 slots 249, 256 x 1 263; float64 256 x 2 480,
+// 128 x 4 504; from 1024 slots in float 256 x 1 (1024 x 384 x 96 555 : 562,
+// 1536 x 384 x 96 801 : 832; 768 x 256 x 96 279 : 272).  Narrow rows whose last
+// block would have an idle wavefront take one wavefront a row: blocks go
+// round-robin to the XCDs, and with an even number of blocks a row some XCDs
+// would get only the emptier ones (160 x 144 x 128 float64, 64 x 4 : 128 x 2
+// slots: 96 : 115 us; 160 x 100 x 60 float 26 : 29; but 256 x 128 x 48 float
+// 34.6 : 33.5, 96 x 64 x 48 13.6 : 13.2).
+template <int V, int WX, bool WIDE>
+struct PassShape {
+    static constexpr int v = V, wx = WX;
+    static constexpr bool wide = WIDE;
+};
+template <typename T, typename F>
+static void with_shape(const KParams<T> &p, F f) {
+    const int w64 = (p.n[0] + 63) / 64, w128 = (p.n[0] + 127) / 128; // wavefronts a row
+    if (p.wide < 0) return f(PassShape<1, 1, false>());
+    if constexpr (sizeof(T) == 8) {
+        if (10 * w64 < 18 * w128) return f(PassShape<1, 1, false>());
+        if (p.wide) return f(PassShape<2, 2, true>());
+        return f(PassShape<2, 1, false>());
+    } else {
+        if (p.wide && p.n[0] >= 1024) return f(PassShape<1, 4, true>());
+        if (p.wide) return f(PassShape<1, 2, true>());
+        if (w64 % 2 == 0) return f(PassShape<1, 2, false>());
+        return f(PassShape<1, 1, false>());
+    }
 }
 
 // the E pass and then its mixed slots
 template <typename T>
 hipError_t launch_epass(const KParams<T> &p, hipStream_t s, const BoxTape *tape) {
-    if (p.wide)
-        launch_e<T, kWideTX, kWideTY>(p, s, tape);
-    else
-        launch_e<T, PTX, PTY>(p, s, tape);
+    with_shape(p, [&](auto h) {
+        typedef decltype(h) S;
+        launch_e<T, S::v, S::wx, S::wide>(p, s, tape);
+    });
     if (p.nmixed > 0) k_emixed<T><<<dim3((p.nmixed + 255) / 256), dim3(256), 0, s>>>(p);
     return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_hbulk(const KParams<T> &p, int nhalf, int inc, hipStream_t s) {
-    if (p.wide) {
-        const dim3 g = pass_grid<kWideTX, kWideTY>(p.n), b(kWideTX, kWideTY);
-        if (nhalf == 1)
-            k_hbulk<T, 1, kWideTX, kWideTY><<<g, b, 0, s>>>(p, inc);
-        else
-            k_hbulk<T, 2, kWideTX, kWideTY><<<g, b, 0, s>>>(p, inc);
-    } else {
-        const dim3 g = pass_grid<PTX, PTY>(p.n), b(PTX, PTY);
-        if (nhalf == 1)
-            k_hbulk<T, 1, PTX, PTY><<<g, b, 0, s>>>(p, inc);
-        else
-            k_hbulk<T, 2, PTX, PTY><<<g, b, 0, s>>>(p, inc);
-    }
-    return hipGetLastError();
-}
-
-template <typename T, int NHALF, int TX, int TY>
-static void launch_hm(const KParams<T> &p, int nblk, int inc, int nprobe, hipStream_t s) {
-    const dim3 g = pass_grid<TX, TY>(p.n);
-    const int per_plane = (int)(g.x * g.y);
-    const int zf = (nblk + (nprobe > 0 ? 1 : 0) + per_plane - 1) / per_plane;
-    k_hbulk_film<T, NHALF, TX, TY><<<dim3(g.x, g.y, g.z + zf), dim3(TX, TY), 0, s>>>(p, inc, zf, nblk, nprobe);
 }
 
 // the H/M pass with the film's part (nblk blocks: the second half step of a
@@ -536,19 +673,19 @@ static void launch_hm(const KParams<T> &p, int nblk, int inc, int nprobe, hipStr
 // and nprobe probes
 template <typename T>
 hipError_t launch_hbulk_film(const KParams<T> &p, int nhalf, int nblk, int inc, hipStream_t s, int nprobe) {
-    if (nblk == 0 && nprobe == 0) return launch_hbulk<T>(p, nhalf, inc, s);
-    if (p.wide) {
+    with_shape(p, [&](auto h) {
+        typedef decltype(h) S;
         if (nhalf == 1)
-            launch_hm<T, 1, kWideTX, kWideTY>(p, nblk, inc, nprobe, s);
+            launch_hm<T, 1, S::v, S::wx, S::wide>(p, nblk, inc, nprobe, s);
         else
-            launch_hm<T, 2, kWideTX, kWideTY>(p, nblk, inc, nprobe, s);
-    } else {
-        if (nhalf == 1)
-            launch_hm<T, 1, PTX, PTY>(p, nblk, inc, nprobe, s);
-        else
-            launch_hm<T, 2, PTX, PTY>(p, nblk, inc, nprobe, s);
-    }
+            launch_hm<T, 2, S::v, S::wx, S::wide>(p, nblk, inc, nprobe, s);
+    });
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_hbulk(const KParams<T> &p, int nhalf, int inc, hipStream_t s) {
+    return launch_hbulk_film<T>(p, nhalf, 0, inc, s, 0);
 }
 
 template <typename T>

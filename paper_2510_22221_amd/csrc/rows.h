@@ -1,4 +1,5 @@
-// rows.h -- the stencil passes' view of a wavefront: 64 consecutive slots of
+// rows.h -- the stencil passes' view of a wavefront: 64 (or, with V slots a lane,
+// 64 V) consecutive slots of
 // one row (j, k), so that everything but the x position is uniform.
 //
 // What a pass spends beside its bytes is instructions: with per-lane rows,
@@ -20,7 +21,7 @@ namespace mpx {
 
 // the wavefront's row of a TX x TY tile (bx, by) of plane k
 struct RowPos {
-    int i;      // the lane's x position (may lie past the row)
+    int i;      // the lane's (first) x position (may lie past the row)
     int w0;     // the wavefront's first x position
     int j, k;   // its row
     bool in;    // i lies in the row
@@ -53,6 +54,61 @@ __device__ __forceinline__ void row_st(T *base, unsigned off, T v) {
         *a = v;
 }
 
+// the wavefront's row when a lane holds V consecutive slots: blocks of 64 x 4
+// threads, WX wavefronts side by side in x and 4 / WX rows
+template <int V, int WX>
+__device__ __forceinline__ RowPos row_pos_v(const int *n, int bx, int by, int k) {
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+    RowPos r;
+    r.w0 = (bx * WX + w % WX) * 64 * V;
+    r.i = r.w0 + (int)threadIdx.x * V;
+    r.j = by * (4 / WX) + w / WX;
+    r.k = k;
+    r.in = r.i < n[0];
+    return r;
+}
+
+// V consecutive elements (aligned to their size) `off` bytes past a base
+template <int V, bool NT = false, typename T>
+__device__ __forceinline__ void row_ldv(const T *base, unsigned off, T (&o)[V]) {
+    if constexpr (V == 1) {
+        o[0] = row_ld<NT>(base, off);
+    } else {
+        typedef T vec __attribute__((ext_vector_type(V)));
+        const vec *a = (const vec *)((const char *)base + off);
+        const vec x = NT ? __builtin_nontemporal_load(a) : *a;
+#pragma unroll
+        for (int v = 0; v < V; v++) o[v] = x[v];
+    }
+}
+// those of them with st[v]: one store where all of a lane's are
+template <int V, bool NT = false, typename T>
+__device__ __forceinline__ void row_stv(T *base, unsigned off, const T (&o)[V], const bool (&st)[V]) {
+    if constexpr (V == 1) {
+        if (st[0]) row_st<NT>(base, off, o[0]);
+    } else {
+        typedef T vec __attribute__((ext_vector_type(V)));
+        bool all = true;
+        vec x;
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            all = all && st[v];
+            x[v] = o[v];
+        }
+        if (all) {
+            vec *a = (vec *)((char *)base + off);
+            if (NT)
+                __builtin_nontemporal_store(x, a);
+            else
+                *a = x;
+        } else {
+#pragma unroll
+            for (int v = 0; v < V; v++)
+                if (st[v]) row_st<NT>(base, off + (unsigned)(v * (int)sizeof(T)), o[v]);
+        }
+    }
+}
+
 // a uniform element of a read-only table, through the scalar cache
 template <typename T>
 __device__ __forceinline__ T scalar_ld(const T *tab, int q) {
@@ -68,15 +124,15 @@ __device__ __forceinline__ T scalar_ld(const T *tab, int q) {
 // (non-temporal), a row's few x-slab values share cache lines with the next
 // row's (default policy).
 // ---------------------------------------------------------------------------
-template <typename T>
+template <typename T, int V = 1>
 struct RowPml {
     bool wx = false, wy = false, wz = false; // uniform: the wavefront has slab slots of this axis
-    bool sx = false;                         // the lane lies in an x slab
-    T bx = T(0), cx = T(0), by = T(0), cy = T(0), bz = T(0), cz = T(0);
-    T xy = T(0), xz = T(0); // psi along x of the y and z components
-    T yz = T(0), yx = T(0); // along y of the z and x components
-    T zx = T(0), zy = T(0); // along z of the x and y components
-    unsigned ox = 0;        // byte offset of the lane's x-slab value in its row
+    bool sx[V] = {};                         // the slot lies in an x slab
+    T bx[V] = {}, cx[V] = {}, by = T(0), cy = T(0), bz = T(0), cz = T(0);
+    T xy[V] = {}, xz[V] = {}; // psi along x of the y and z components
+    T yz[V] = {}, yx[V] = {}; // along y of the z and x components
+    T zx[V] = {}, zy[V] = {}; // along z of the x and y components
+    unsigned ox[V] = {};      // byte offset of the slot's x-slab value in its row
 };
 
 // uniform first element of the row's psi along axis w
@@ -98,37 +154,43 @@ __device__ __forceinline__ bool in_slab(const KParams<T> &p, int w, int q) {
 }
 
 // io: the lane's byte offset in a padded row (its x position clamped to the row)
-template <typename T, bool E>
-__device__ __forceinline__ RowPml<T> row_pml(const KParams<T> &p, const RowPos &r, unsigned io) {
-    RowPml<T> m;
+template <typename T, bool E, int V = 1>
+__device__ __forceinline__ RowPml<T, V> row_pml(const KParams<T> &p, const RowPos &r, unsigned io) {
+    RowPml<T, V> m;
     T *const(*a)[3] = E ? p.psiE : p.psiH;
     const T *const *bt = E ? p.bE : p.bH;
     const T *const *ct = E ? p.cE : p.cH;
-    m.wx = r.w0 < p.nlo[0] || r.w0 + 63 >= p.n[0] - p.nhi[0];
+    m.wx = r.w0 < p.nlo[0] || r.w0 + 64 * V - 1 >= p.n[0] - p.nhi[0];
     if (p.nlo[0] + p.nhi[0] == 0) m.wx = false;
     m.wy = in_slab(p, 1, r.j);
     m.wz = in_slab(p, 2, r.k);
     if (m.wx) {
-        m.sx = r.in && in_slab(p, 0, r.i);
-        const int sp = r.i < p.nlo[0] ? r.i : p.nlo[0] + (r.i - (p.n[0] - p.nhi[0]));
-        m.ox = (unsigned)(m.sx ? sp : 0) * (unsigned)sizeof(T);
         const long long q = row_psi(p, 0, r.j, r.k);
-        m.xy = row_ld(a[1][0] + q, m.ox);
-        m.xz = row_ld(a[2][0] + q, m.ox);
-        m.bx = row_ld(bt[0], io);
-        m.cx = row_ld(ct[0], io);
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const int i = r.i + v;
+            m.sx[v] = i < p.n[0] && in_slab(p, 0, i);
+            const int sp = i < p.nlo[0] ? i : p.nlo[0] + (i - (p.n[0] - p.nhi[0]));
+            m.ox[v] = (unsigned)(m.sx[v] ? sp : 0) * (unsigned)sizeof(T);
+            m.xy[v] = row_ld(a[1][0] + q, m.ox[v]);
+            m.xz[v] = row_ld(a[2][0] + q, m.ox[v]);
+            // (of the lane's slots past the row: its first one's, unused)
+            const unsigned ib = i < p.n[0] ? io + (unsigned)(v * (int)sizeof(T)) : io;
+            m.bx[v] = row_ld(bt[0], ib);
+            m.cx[v] = row_ld(ct[0], ib);
+        }
     }
     if (m.wy) {
         const long long q = row_psi(p, 1, r.j, r.k);
-        m.yz = row_ld<true>(a[2][1] + q, io);
-        m.yx = row_ld<true>(a[0][1] + q, io);
+        row_ldv<V, true>(a[2][1] + q, io, m.yz);
+        row_ldv<V, true>(a[0][1] + q, io, m.yx);
         m.by = scalar_ld(bt[1], r.j);
         m.cy = scalar_ld(ct[1], r.j);
     }
     if (m.wz) {
         const long long q = row_psi(p, 2, r.j, r.k);
-        m.zx = row_ld<true>(a[0][2] + q, io);
-        m.zy = row_ld<true>(a[1][2] + q, io);
+        row_ldv<V, true>(a[0][2] + q, io, m.zx);
+        row_ldv<V, true>(a[1][2] + q, io, m.zy);
         m.bz = scalar_ld(bt[2], r.k);
         m.cz = scalar_ld(ct[2], r.k);
     }
