@@ -890,7 +890,19 @@ __device__ __forceinline__ EdgeRow edge_class(const KParams<T> &p, int i, int j,
 template <typename T>
 __device__ __forceinline__ void edge_row_coefs(const KParams<T> &p, const EdgeRow &e, int i, int j, int k, T *ca,
                                                T *cb, bool *ok) {
-    const CoefRow<T> r = coef_row<T>(p.coefv, e.mixed ? 0 : e.c);
+    // one class for the whole wavefront: its row through the scalar cache
+    CoefRow<T> r;
+    const int cu = __builtin_amdgcn_readfirstlane(e.c);
+    if (__builtin_amdgcn_ballot_w64(e.c != cu || e.mixed) == 0) {
+        const T *q = p.coefv + kCoefRow<T> * (long long)cu;
+#pragma unroll
+        for (int C = 0; C < 3; C++) {
+            r.ca[C] = scalar_ld(q, 2 * C);
+            r.cb[C] = scalar_ld(q, 2 * C + 1);
+        }
+    } else {
+        r = coef_row<T>(p.coefv, e.mixed ? 0 : e.c);
+    }
     // an edge on a lower wall (a non-periodic axis other than its own) is held
     // at zero; a mixed slot's edges read the four cells around them, which
     // exist off the walls only
@@ -1264,8 +1276,8 @@ enum { HF_SECOND = 0, HF_FIRST = 1, HF_PAIR = 2 };
 // the second half step) and of the one before it along axis AX (n, hn).  The
 // first film that holds a face counts; returns whether one holds the slot's.
 template <typename T, bool PAIR, int AX>
-__device__ __forceinline__ bool film_part_values(const AdjParams<T> &A, const RowPos &r, int w, T &o, T &n, T &h,
-                                                 T &hn) {
+__device__ __forceinline__ bool film_part_values(const RowPos &r, int w, T &o, T &n, T &h, T &hn) {
+    const AdjParams<T> &A = args_again<AdjParams<T>>();
     const KParams<T> &p = A.p;
     int nb[3] = {r.i, r.j, r.k};
     nb[AX] = nb[AX] > 0 ? nb[AX] - 1 : (p.per[AX] ? p.n[AX] - 1 : -1);
@@ -1276,17 +1288,20 @@ __device__ __forceinline__ bool film_part_values(const AdjParams<T> &A, const Ro
         if (PAIR) t2 = scalar_desc(A.afb, f).aDr;
         const int x = r.i - G.r0[0], y = r.j - G.r0[1], z = r.k - G.r0[2];
         const int xn = nb[0] - G.r0[0], yn = nb[1] - G.r0[1], zn = nb[2] - G.r0[2];
-        if (y >= 0 && y < G.rn[1] && z >= 0 && z < G.rn[2] && x >= 0 && x < G.rn[0] && r.in) {
-            const long long q = w * G.nr + x + (long long)G.rn[0] * ((long long)y + (long long)G.rn[1] * z);
-            o = (T)G.aDr[q];
-            if (PAIR) h = (T)t2[q];
-            own = true;
+        const bool in = r.in && y >= 0 && y < G.rn[1] && z >= 0 && z < G.rn[2] && x >= 0 && x < G.rn[0];
+        const bool inn = r.in && yn >= 0 && yn < G.rn[1] && zn >= 0 && zn < G.rn[2] && xn >= 0 && xn < G.rn[0];
+        // a reach holds fewer than 2^31 sites; all four loads go out at once,
+        // at a part's first site where the face is outside (then dropped)
+        const int q = in ? x + G.rn[0] * (y + G.rn[1] * z) : 0, qn = inn ? xn + G.rn[0] * (yn + G.rn[1] * zn) : 0;
+        const double *d = G.aDr + w * G.nr, *d2 = t2 + w * G.nr;
+        const T vo = (T)d[q], vn = (T)d[qn], vh = PAIR ? (T)d2[q] : T(0), vhn = PAIR ? (T)d2[qn] : T(0);
+        o = in ? vo : o;
+        n = inn ? vn : n;
+        if (PAIR) {
+            h = in ? vh : h;
+            hn = inn ? vhn : hn;
         }
-        if (yn >= 0 && yn < G.rn[1] && zn >= 0 && zn < G.rn[2] && xn >= 0 && xn < G.rn[0] && r.in) {
-            const long long q = w * G.nr + xn + (long long)G.rn[0] * ((long long)yn + (long long)G.rn[1] * zn);
-            n = (T)G.aDr[q];
-            if (PAIR) hn = (T)t2[q];
-        }
+        own = own || in;
     }
     return own;
 }
@@ -1304,7 +1319,11 @@ __device__ __forceinline__ bool film_part_values(const AdjParams<T> &A, const Ro
 // lambda E, mu out) and 16 a slab slot and axis: 175 us on a 512 x 256 x 128 grid
 // with CPML 10 at the rate of a copy.  With each slot walking its faces'
 // recursions by branches it took 390 us (252 vector instructions and nine
-// dependent psi fetches a wavefront); by rows 211 us.
+// dependent psi fetches a wavefront); by rows 211 us, with the tables of a film
+// tile in one round trip a difference, one class's coefficients through the
+// scalar cache and the last part's arguments fetched there (92 scalar registers
+// had gone through vector lanes, now 20) 193; 128 x 64 x 64 15.7 -> 13.6 us, 96 x
+// 64 x 48 float64 17.2 -> 15.8.
 template <typename T, int MODE, int TX, int TY>
 __global__ void __launch_bounds__(256) k_adj_hfield(AdjParams<T> A) {
     constexpr bool PAIR = MODE == HF_PAIR;
@@ -1352,7 +1371,7 @@ __global__ void __launch_bounds__(256) k_adj_hfield(AdjParams<T> A) {
             if (M.s) adj_stretch<T, PAIR>(true, o, M.b, M.c, M.PS, o, h);                              \
             if (M.sn) adj_stretch<T, PAIR>(true, n, M.bn, M.cn, M.PSN, n, g);                          \
         }                                                                                              \
-        if (fl & 4) film_own = film_part_values<T, PAIR, AX>(A, r, W, o, n, h, g);                     \
+        if (fl & 4) film_own = film_part_values<T, PAIR, AX>(r, W, o, n, h, g);                     \
         D = dif((OK ? n : T(0)) - o, T(0), p.dT[AX], p.invd[AX]);                                      \
         if (PAIR) E = dif((OK ? g : T(0)) - h, T(0), p.dT[AX], p.invd[AX]);                            \
     }
@@ -1370,7 +1389,8 @@ __global__ void __launch_bounds__(256) k_adj_hfield(AdjParams<T> A) {
     dd[2] = d + d2;
     if (PAIR) de[2] = e1 + e2;
 #undef MPX_DIFF
-    const long long q = zo + (long long)p.px * j + ic;
+    const AdjParams<T> &B = args_again<AdjParams<T>>();
+    const long long q = zo + (long long)B.p.px * j + ic;
     const int t[3] = {ic, j, k};
     const T lp[3] = {l[0], l[1], l[2]}; // lambda E' of the step
     if (MODE != HF_SECOND) {
@@ -1381,16 +1401,16 @@ __global__ void __launch_bounds__(256) k_adj_hfield(AdjParams<T> A) {
     l[1] = l[1] + dd[1];
     l[2] = l[2] + dd[2];
     if (MODE != HF_SECOND) {
-        if (A.ltape && (fl & 4) && A.seg0[0] + A.m > A.loss_from && r.in)
-            loss_term<T, PAIR ? 1 : 0>(A, t, q, l[0], l[1], l[2]);
-        if (A.pw && q == A.pw_slot && r.in) {
+        if (B.ltape && (fl & 4) && B.seg0[0] + B.m > B.loss_from && r.in)
+            loss_term<T, PAIR ? 1 : 0>(B, t, q, l[0], l[1], l[2]);
+        if (B.pw && q == B.pw_slot && r.in) {
             // the weighted trace's term of the state at the step's start (time n)
-            const long long n = A.seg0[0] + A.m;
+            const long long n = B.seg0[0] + B.m;
             if (n >= 1) {
-                const T v = (T)(A.pw_scale * A.pw[n - 1]);
-                if (A.pw_comp == 0)
+                const T v = (T)(B.pw_scale * B.pw[n - 1]);
+                if (B.pw_comp == 0)
                     l[0] += v;
-                else if (A.pw_comp == 1)
+                else if (B.pw_comp == 1)
                     l[1] += v;
                 else
                     l[2] += v;
@@ -1404,55 +1424,55 @@ __global__ void __launch_bounds__(256) k_adj_hfield(AdjParams<T> A) {
         l[2] = l[2] + de[2];
     }
     if (!r.in) return;
-    row_st<true>(Ex, vo, l[0]);
-    row_st<true>(Ey, vo, l[1]);
-    row_st<true>(Ez, vo, l[2]);
+    row_st<true>(B.lE[0] + zo, vo, l[0]);
+    row_st<true>(B.lE[1] + zo, vo, l[1]);
+    row_st<true>(B.lE[2] + zo, vo, l[2]);
     if (MODE != HF_FIRST) {
         // the E-step adjoint's input: cb lambda E' (zero on a wall or PEC edge)
-        row_st(A.mu[0] + zo, vo, ok[0] ? cb[0] * l[0] : T(0));
-        row_st(A.mu[1] + zo, vo, ok[1] ? cb[1] * l[1] : T(0));
-        row_st(A.mu[2] + zo, vo, ok[2] ? cb[2] * l[2] : T(0));
+        row_st(B.mu[0] + zo, vo, ok[0] ? cb[0] * l[0] : T(0));
+        row_st(B.mu[1] + zo, vo, ok[1] ? cb[1] * l[1] : T(0));
+        row_st(B.mu[2] + zo, vo, ok[2] ? cb[2] * l[2] : T(0));
     }
     // lambda psiH after the map(s), of the slot's own faces (a film region's
     // faces: the film kernels')
     if (film_own) ax.s = ay.s = az.s = false;
     if (ax.s) {
-        row_st(A.lpsiHo[1][0] + ax.q, ax.o, ax.pa);
-        row_st(A.lpsiHo[2][0] + ax.q, ax.o, ax.pb);
+        row_st(B.lpsiHo[1][0] + ax.q, ax.o, ax.pa);
+        row_st(B.lpsiHo[2][0] + ax.q, ax.o, ax.pb);
     }
     if (ay.s) {
-        row_st(A.lpsiHo[2][1] + ay.q, io, ay.pa);
-        row_st(A.lpsiHo[0][1] + ay.q, io, ay.pb);
+        row_st(B.lpsiHo[2][1] + ay.q, io, ay.pa);
+        row_st(B.lpsiHo[0][1] + ay.q, io, ay.pb);
     }
     if (az.s) {
-        row_st(A.lpsiHo[0][2] + az.q, io, az.pa);
-        row_st(A.lpsiHo[1][2] + az.q, io, az.pb);
+        row_st(B.lpsiHo[0][2] + az.q, io, az.pa);
+        row_st(B.lpsiHo[1][2] + az.q, io, az.pb);
     }
     if (MODE != HF_SECOND) {
-        if (A.btape) {
+        if (B.btape) {
             // dL/dca += lambda E' E^n, dL/dcb += lambda E' x^n over the eps box
             // (last: its float64 values are then live with little else)
-            const int rb[3] = {A.bs[0] + 1, A.bs[1] + 1, A.bs[2] + 1};
-            int lj = j - A.bb[1], lk = k - A.bb[2], li = ic - A.bb[0];
-            if (lj < 0 && p.per[1]) lj += p.n[1];
-            if (lk < 0 && p.per[2]) lk += p.n[2];
+            const int rb[3] = {B.bs[0] + 1, B.bs[1] + 1, B.bs[2] + 1};
+            int lj = j - B.bb[1], lk = k - B.bb[2], li = ic - B.bb[0];
+            if (lj < 0 && B.p.per[1]) lj += B.p.n[1];
+            if (lk < 0 && B.p.per[2]) lk += B.p.n[2];
             if (lj >= 0 && lj < rb[1] && lk >= 0 && lk < rb[2]) { // uniform
-                if (li < 0 && p.per[0]) li += p.n[0];
+                if (li < 0 && B.p.per[0]) li += B.p.n[0];
                 if (li >= 0 && li < rb[0]) {
                     const long long ri = (long long)li + (long long)rb[0] * ((long long)lj + (long long)rb[1] * lk);
                     const long long tb = (long long)rb[0] * rb[1] * rb[2];
                     double ga[3], gb[3], ta[3], tx[3];
 #pragma unroll
                     for (int C = 0; C < 3; C++) {
-                        ga[C] = A.gca_box[C * tb + ri];
-                        gb[C] = A.gcb_box[C * tb + ri];
-                        ta[C] = A.btape[C * tb + ri];
-                        tx[C] = A.btape[(3 + C) * tb + ri];
+                        ga[C] = B.gca_box[C * tb + ri];
+                        gb[C] = B.gcb_box[C * tb + ri];
+                        ta[C] = B.btape[C * tb + ri];
+                        tx[C] = B.btape[(3 + C) * tb + ri];
                     }
 #pragma unroll
                     for (int C = 0; C < 3; C++) {
-                        A.gca_box[C * tb + ri] = ga[C] + (double)lp[C] * ta[C];
-                        A.gcb_box[C * tb + ri] = gb[C] + (double)lp[C] * tx[C];
+                        B.gca_box[C * tb + ri] = ga[C] + (double)lp[C] * ta[C];
+                        B.gcb_box[C * tb + ri] = gb[C] + (double)lp[C] * tx[C];
                     }
                 }
             }

@@ -109,6 +109,18 @@ __device__ __forceinline__ void row_stv(T *base, unsigned off, const T (&o)[V], 
     }
 }
 
+// a kernel's first argument once more, from its argument segment: what is read
+// through it is read from here on.  Arguments named plainly are all fetched at
+// the kernel's start, and those of its last part, past the scalar registers,
+// then go to vector lanes and come back one instruction each.
+template <typename P>
+__device__ __forceinline__ const P &args_again() {
+    typedef __attribute__((address_space(4))) const char cbyte;
+    cbyte *q = (cbyte *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(q));
+    return *(const P *)q;
+}
+
 // a uniform element of a read-only table, through the scalar cache
 template <typename T>
 __device__ __forceinline__ T scalar_ld(const T *tab, int q) {
