@@ -798,6 +798,7 @@ struct mpx_batch {
     int2 *d_wmixed = nullptr; // mixed-slot blocks: (instance, first entry)
     int nwmixed = 0;
     bool any_xcls = false; // a member has extended-table slots
+    bool any_big = false;  // a member's arrays reach 4 GiB
     int2 *d_wfilm = nullptr, *d_wext = nullptr, *d_wprobe = nullptr;
     int nwfilm = 0, nwext = 0, nwprobe = 0;
     int probe_maxpart = 0;
@@ -836,7 +837,7 @@ void batch_drop_graph(mpx_batch *b) {
 
 template <typename T>
 mpx_status batch_tables(mpx_batch *b) {
-    b->any_xcls = false;
+    b->any_xcls = b->any_big = false;
     b->nfold.clear();
     // tiles instance by instance, in the single-instance order
     std::vector<int4> work, work2, workh;
@@ -851,6 +852,7 @@ mpx_status batch_tables(mpx_batch *b) {
                     for (int bx = 0; bx < nxt; bx++) work2.push_back(make_int4(q, bx, by, k));
             for (int m = 0; m < s->nmixed; m += 256) wmixed.push_back(make_int2(q, m));
             if (s->d_cls16) b->any_xcls = true;
+            if (big_array(s->px, s->n, s->esz)) b->any_big = true;
         } else {
             // tiles of 64 x 4 columns (register sweep) or 64 x 8 (LDS-staged)
             const int nxt = (s->n[0] + 63) / 64, nyt = b->variant == 1 ? (s->n[1] + 3) / 4 : (s->n[1] + 7) / 8;
@@ -953,10 +955,10 @@ mpx_status batch_body(mpx_batch *b, int f) {
         // E pass, the films' first half step and the probes that read H, then
         // the H/M pass with the films' second half step and the other probes
         // (it moves every instance's step counter)
-        BCK(launch_epass_batch<T>(pa, b->d_work2, b->nwork2, b->d_wmixed, b->nwmixed, b->any_xcls, st));
+        BCK(launch_epass_batch<T>(pa, b->d_work2, b->nwork2, b->d_wmixed, b->nwmixed, b->any_xcls, b->any_big, st));
         BCK(launch_film_batch<T>(pa, b->d_wext, b->nwext, b->d_wfilm, b->nwfilm, 1, 0, st));
         BCK(launch_probes_batch<T>(pa, b->d_wprobe, b->nwprobe, b->probe_maxpart, st));
-        BCK(launch_hbulk_batch<T>(pa, b->d_workh, b->nworkh, 2, 1, st));
+        BCK(launch_hbulk_batch<T>(pa, b->d_workh, b->nworkh, 1, b->any_big, st));
         return MPX_OK;
     }
     if (b->variant == 1)

@@ -294,10 +294,15 @@ struct BoxTape {
 template <typename T> hipError_t launch_epass(const KParams<T> &p, hipStream_t s, const BoxTape *tape = nullptr);
 template <typename T>
 hipError_t launch_epass_batch(const KParams<T> *plist, const int4 *work, int nwork, const int2 *mwork, int nmwork,
-                              bool xcls, hipStream_t s);
+                              bool xcls, bool big, hipStream_t s);
 template <typename T>
-hipError_t launch_hbulk_batch(const KParams<T> *plist, const int4 *work, int nwork, int nhalf, int inc,
+hipError_t launch_hbulk_batch(const KParams<T> *plist, const int4 *work, int nwork, int inc, bool big,
                               hipStream_t s);
+// the passes address arrays below 4 GiB by 32-bit offsets from their first
+// element, larger ones from a plane's
+inline bool big_array(int px, const int *n, size_t es) {
+    return (unsigned long long)px * n[1] * n[2] * es >= 1ull << 32;
+}
 int pass_tiles(const int *n);
 constexpr int kPassTX = 64, kPassTY = 4; // separate-pass tile: 64 x 4 slots of one plane
 constexpr int kWideTX = 256, kWideTY = 1; // the wide tile of the single-instance passes

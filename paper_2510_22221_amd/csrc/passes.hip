@@ -8,8 +8,12 @@
 // (the magnetic ones are the film kernels' work).
 //
 // Memory access: a wavefront is 64 or 128 slots of one row (rows.h), so every array
-// is read at a uniform plane base and a 32-bit lane offset; rows, slabs and
-// their coefficients are scalar.  One path serves interior and boundary.
+// is read at its own base and a 32-bit lane offset (arrays of 4 GiB and more:
+// at the plane's base); rows, slabs and their coefficients are scalar.  With a
+// 64-bit plane base per array, and 64-bit tile and psi indices, the float32 E
+// pass of a 512 x 256 x 128 grid issued 196 scalar instructions a wavefront,
+// now 138: 128 x 64 x 64 8.4 -> 7.2 us (H/M 8.8 -> 7.2), a batch of 32
+// resonators 225 -> 215 (239 -> 226).  One path serves interior and boundary.
 // Per-tile source / film flags come from a host table (one per tile shape);
 // edge coefficients come from the packed row of the slot's class (its six
 // values in one or two 16-byte loads; no per-block staging).
@@ -57,25 +61,29 @@ __device__ __forceinline__ double src_current(const KParams<T> &p, int C, int i,
 // launch differ; the test is uniform over a member's lanes).  f: the tile's
 // flag byte, first used after every field load has been issued (so that the
 // loads do not wait for it).
-template <typename T, int CLS, int V = 1, bool TAPE = false>
+template <typename T, int CLS, int V, bool BIG, bool TAPE = false>
 __device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, int f, const BoxTape &bt = BoxTape()) {
     if (r.j >= p.n[1]) return; // a partial tile's row (uniform)
     const unsigned es = (unsigned)sizeof(T);
     // the lane's first slot, clamped to the row's last whole or partial group
     const int ic = min(r.i, (p.n[0] - 1) & -V), j = r.j, k = r.k;
-    const long long sz = (long long)p.px * p.n[1];
-    const unsigned io = (unsigned)ic * es, rowb = (unsigned)p.px * es, vo = io + (unsigned)j * rowb;
+    // an array below 4 GiB: bases are the kernel's arguments, the plane is in
+    // the lanes' 32-bit offsets; else (BIG) bases are the plane's
+    const unsigned plane = (unsigned)p.px * (unsigned)p.n[1], rowb = (unsigned)p.px * es;
+    const unsigned io = (unsigned)ic * es, po = BIG ? 0u : (unsigned)k * plane * es, vo = io + (po + (unsigned)j * rowb);
+    const long long zo = BIG ? (long long)((unsigned long long)plane * (unsigned)k) : 0;
     // the -1 neighbours: wrapped on a periodic axis, any in-range value at a wall
     const unsigned vxm = ic > 0 ? vo - es : (p.per[0] ? vo + (unsigned)(p.n[0] - 1) * es : vo);
-    const unsigned jm = (unsigned)(j > 0 ? j - 1 : (p.per[1] ? p.n[1] - 1 : j)), vym = io + jm * rowb;
-    const int kb = k > 0 ? k - 1 : (p.per[2] ? p.n[2] - 1 : k);
-    const long long zo = k * sz, zb = kb * sz;
+    const unsigned jm = (unsigned)(j > 0 ? j - 1 : (p.per[1] ? p.n[1] - 1 : j)), vym = io + (po + jm * rowb);
+    const unsigned kb = (unsigned)(k > 0 ? k - 1 : (p.per[2] ? p.n[2] - 1 : k));
+    const unsigned vzm = BIG ? vo : io + (kb * plane * es + (unsigned)j * rowb);
+    const long long zb = BIG ? (long long)((unsigned long long)plane * kb) : 0;
     // the class first: its coefficient row is the one load that waits for another
     bool c16 = CLS == 1;
     if constexpr (CLS == 2) c16 = p.cls16 != nullptr;
     int c0[V];
     {
-        const unsigned vc = (unsigned)ic + (unsigned)j * (unsigned)p.px;
+        const unsigned vc = (unsigned)ic + ((BIG ? 0u : (unsigned)k * plane) + (unsigned)j * (unsigned)p.px);
         if (c16) {
             uint16_t c[V];
             row_ldv<V, CLS != 2>(p.cls16 + zo, 2u * vc, c);
@@ -93,10 +101,10 @@ __device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, 
     // plane and of the next row read it before): non-temporal
     T hx0[V], hx_km[V], hx_ym[V], hy0[V], hy_km[V], hy_xm[V], hz0[V], hz_xm[V], hz_ym[V];
     row_ldv<V>(Hx, vo, hx0);
-    row_ldv<V, true>(p.H[0] + zb, vo, hx_km);
+    row_ldv<V, true>(p.H[0] + zb, vzm, hx_km);
     row_ldv<V>(Hx, vym, hx_ym);
     row_ldv<V>(Hy, vo, hy0);
-    row_ldv<V, true>(p.H[1] + zb, vo, hy_km);
+    row_ldv<V, true>(p.H[1] + zb, vzm, hy_km);
     hy_xm[0] = row_ld(Hy, vxm);
     row_ldv<V>(Hz, vo, hz0);
     hz_xm[0] = row_ld(Hz, vxm);
@@ -249,28 +257,27 @@ __device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, 
 template <typename T, int V>
 __device__ __forceinline__ int row_flags(const KParams<T> &p, const RowPos &r, bool wide) {
     typedef __attribute__((address_space(4))) const uint32_t cword;
-    const int tx = wide ? kWideTX : PTX, ty = wide ? kWideTY : PTY;
-    const int nxt = (p.n[0] + tx - 1) / tx, nyt = (p.n[1] + ty - 1) / ty;
+    const unsigned tx = wide ? kWideTX : PTX, ty = wide ? kWideTY : PTY;
+    const unsigned nxt = ((unsigned)p.n[0] + tx - 1) / tx, nyt = ((unsigned)p.n[1] + ty - 1) / ty;
     const cword *tab = (cword *)(wide ? p.pflags_w : p.pflags);
-    const int bx = min(r.w0 / tx, nxt - 1), by = min(r.j, p.n[1] - 1) / ty;
-    const long long t0 = (long long)nxt * (by + (long long)nyt * r.k);
+    const unsigned bx = (unsigned)r.w0 / tx, t0 = bx + nxt * ((unsigned)min(r.j, p.n[1] - 1) / ty + nyt * (unsigned)r.k);
     int f = 0;
 #pragma unroll
-    for (int v = 0; v < V; v++) {
-        const long long ti = t0 + min(bx + v, nxt - 1);
-        f |= (int)(tab[ti >> 2] >> (8 * (int)(ti & 3)));
+    for (unsigned v = 0; v < (unsigned)V; v++) {
+        const unsigned ti = v == 0 || bx + v < nxt ? t0 + v : t0;
+        f |= (int)(tab[ti >> 2] >> (8 * (ti & 3)));
         if (wide) break;
     }
     return f & 0xff;
 }
 
 // a block of 64 x 4 threads: 64 V WX x 4 / WX slots (bx, by) of plane k
-template <typename T, int CLS, int V, int WX, bool WIDE, bool TAPE = false>
+template <typename T, int CLS, int V, int WX, bool WIDE, bool BIG, bool TAPE = false>
 __device__ __forceinline__ void epass_block(const KParams<T> &p, int bx, int by, int k,
                                             const BoxTape &bt = BoxTape()) {
     const RowPos r = row_pos_v<V, WX>(p.n, bx, by, k);
     if (r.w0 >= p.n[0]) return; // uniform: a wavefront past the row
-    epass_row<T, CLS, V, TAPE>(p, r, row_flags<T, V>(p, r, WIDE), bt);
+    epass_row<T, CLS, V, BIG, TAPE>(p, r, row_flags<T, V>(p, r, WIDE), bt);
 }
 
 // the mixed slots, one thread each: the general path (folded loads; edge
@@ -313,31 +320,39 @@ __device__ __forceinline__ void emixed_slot(const KParams<T> &p, int m) {
 // on a periodic axis and reads zero at a wall (the E there is tangential to
 // it); lanes past the domain store nothing.
 // ---------------------------------------------------------------------------
-template <typename T, int NHALF, int V = 1>
+// LATE: the neighbours in the plane are loaded last
+template <typename T, int NHALF, int V, bool BIG, bool LATE>
 __device__ __forceinline__ void hpass_row(const KParams<T> &p, const RowPos &r, int f) {
     if (r.j >= p.n[1]) return; // a partial tile's row (uniform)
     const unsigned es = (unsigned)sizeof(T);
     const int ic = min(r.i, (p.n[0] - 1) & -V), j = r.j, k = r.k;
-    const long long sz = (long long)p.px * p.n[1];
-    const unsigned io = (unsigned)ic * es, rowb = (unsigned)p.px * es, vo = io + (unsigned)j * rowb;
+    // an array below 4 GiB: bases are the kernel's arguments, the plane is in
+    // the lanes' 32-bit offsets; else (BIG) bases are the plane's
+    const unsigned plane = (unsigned)p.px * (unsigned)p.n[1], rowb = (unsigned)p.px * es;
+    const unsigned io = (unsigned)ic * es, po = BIG ? 0u : (unsigned)k * plane * es, vo = io + (po + (unsigned)j * rowb);
+    const long long zo = BIG ? (long long)((unsigned long long)plane * (unsigned)k) : 0;
     // the +1 neighbours: wrapped on a periodic axis; past a wall the own
     // value is read and dropped
     const bool wly = !p.per[1] && j + 1 >= p.n[1], wlz = !p.per[2] && k + 1 >= p.n[2];
     const unsigned vxp = ic + V < p.n[0] ? vo + V * es : (p.per[0] ? vo - io : vo);
-    const unsigned jp = (unsigned)(j + 1 < p.n[1] ? j + 1 : (p.per[1] ? 0 : j)), vyp = io + jp * rowb;
-    const int ka = k + 1 < p.n[2] ? k + 1 : (p.per[2] ? 0 : k);
-    const long long zo = k * sz, za = ka * sz;
+    const unsigned jp = (unsigned)(j + 1 < p.n[1] ? j + 1 : (p.per[1] ? 0 : j)), vyp = io + (po + jp * rowb);
+    const unsigned ka = (unsigned)(k + 1 < p.n[2] ? k + 1 : (p.per[2] ? 0 : k));
+    const unsigned vzp = BIG ? vo : io + (ka * plane * es + (unsigned)j * rowb);
+    const long long za = BIG ? (long long)((unsigned long long)plane * ka) : 0;
     const T *Ex = p.E[0] + zo, *Ey = p.E[1] + zo, *Ez = p.E[2] + zo;
     T ex0[V], ex_yp[V], ex_kp[V], ey0[V], ey_xp[V], ey_kp[V], ez0[V], ez_xp[V], ez_yp[V];
+    T ey_nx, ez_nx; // the slot after the lane's last
     row_ldv<V>(Ex, vo, ex0);
-    row_ldv<V>(Ex, vyp, ex_yp);
-    row_ldv<V>(p.E[0] + za, vo, ex_kp);
+    if constexpr (!LATE) row_ldv<V>(Ex, vyp, ex_yp);
+    row_ldv<V>(p.E[0] + za, vzp, ex_kp);
     row_ldv<V>(Ey, vo, ey0);
-    const T ey_nx = row_ld(Ey, vxp); // the slot after the lane's last
-    row_ldv<V>(p.E[1] + za, vo, ey_kp);
+    if constexpr (!LATE) ey_nx = row_ld(Ey, vxp);
+    row_ldv<V>(p.E[1] + za, vzp, ey_kp);
     row_ldv<V>(Ez, vo, ez0);
-    const T ez_nx = row_ld(Ez, vxp);
-    row_ldv<V>(Ez, vyp, ez_yp);
+    if constexpr (!LATE) {
+        ez_nx = row_ld(Ez, vxp);
+        row_ldv<V>(Ez, vyp, ez_yp);
+    }
     // H and the new H are touched once per pass: non-temporal (the E halo
     // stays in L2)
     T *Hx = p.H[0] + zo, *Hy = p.H[1] + zo, *Hz = p.H[2] + zo;
@@ -346,6 +361,17 @@ __device__ __forceinline__ void hpass_row(const KParams<T> &p, const RowPos &r, 
     row_ldv<V, true>(Hy, vo, h1);
     row_ldv<V, true>(Hz, vo, h2);
     RowPml<T, V> m = row_pml<T, false, V>(p, r, io);
+    if constexpr (LATE) {
+        // the neighbours in the plane last: by then their own wavefronts have
+        // asked for the same lines (512 x 256 x 128 float32: 126 us, with them
+        // first 138; but float64 with two slots a lane 252, among the others
+        // 244, and a batch of 32 small grids 232 : 226)
+        __builtin_amdgcn_sched_barrier(0);
+        ey_nx = row_ld(Ey, vxp);
+        ez_nx = row_ld(Ez, vxp);
+        row_ldv<V>(Ex, vyp, ex_yp);
+        row_ldv<V>(Ez, vyp, ez_yp);
+    }
     // the tile's flags, first used after every field load has been issued
     bool st0[V], st1[V], st2[V]; // stored: not past the row, not magnetic
 #pragma unroll
@@ -435,11 +461,11 @@ __device__ __forceinline__ void hpass_row(const KParams<T> &p, const RowPos &r, 
     }
 }
 
-template <typename T, int NHALF, int V, int WX, bool WIDE>
+template <typename T, int NHALF, int V, int WX, bool WIDE, bool BIG, bool LATE = V == 1>
 __device__ __forceinline__ void hpass_block(const KParams<T> &p, int bx, int by, int k) {
     const RowPos r = row_pos_v<V, WX>(p.n, bx, by, k);
     if (r.w0 >= p.n[0]) return; // uniform: a wavefront past the row
-    hpass_row<T, NHALF, V>(p, r, row_flags<T, V>(p, r, WIDE));
+    hpass_row<T, NHALF, V, BIG, LATE>(p, r, row_flags<T, V>(p, r, WIDE));
 }
 
 // grid (x tiles, y tiles, planes) in natural order: the blocks resident at
@@ -447,21 +473,21 @@ __device__ __forceinline__ void hpass_block(const KParams<T> &p, int bx, int by,
 // cache hits, and no block decodes its tile with divisions.  The tile is the
 // grid's (with_shape).  XC: the variant for grids with extended-table slots
 // (16-bit classes).
-template <typename T, int V, int WX, bool WIDE, bool XC>
+template <typename T, int V, int WX, bool WIDE, bool BIG, bool XC>
 __global__ void __launch_bounds__(256) k_epass(KParams<T> p) {
-    epass_block<T, XC ? 1 : 0, V, WX, WIDE>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+    epass_block<T, XC ? 1 : 0, V, WX, WIDE, BIG>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-template <typename T, int V, int WX, bool WIDE, bool XC>
+template <typename T, int V, int WX, bool WIDE, bool BIG, bool XC>
 __global__ void __launch_bounds__(256) k_epass_tape(KParams<T> p, BoxTape bt) {
-    epass_block<T, XC ? 1 : 0, V, WX, WIDE, true>(p, blockIdx.x, blockIdx.y, blockIdx.z, bt);
+    epass_block<T, XC ? 1 : 0, V, WX, WIDE, BIG, true>(p, blockIdx.x, blockIdx.y, blockIdx.z, bt);
 }
 
-template <typename T, int NHALF, int V, int WX, bool WIDE>
+template <typename T, int NHALF, int V, int WX, bool WIDE, bool BIG>
 __global__ void __launch_bounds__(256) k_hbulk(KParams<T> p, int inc_step) {
     if (inc_step && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && threadIdx.y == 0)
         p.step[0] = p.step[0] + 1;
-    hpass_block<T, NHALF, V, WX, WIDE>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+    hpass_block<T, NHALF, V, WX, WIDE, BIG>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // the H/M pass and the film's part of it in one launch: the first zf planes
@@ -510,7 +536,7 @@ __device__ __forceinline__ void film_part(const KParams<T> &p, int blk, int tid)
         film_commit_body(p, blk, tid);
 }
 
-template <typename T, int NHALF, int V, int WX, bool WIDE>
+template <typename T, int NHALF, int V, int WX, bool WIDE, bool BIG>
 __global__ void __launch_bounds__(256) k_hbulk_film(KParams<T> p, int inc_step, int zf, int nfb, int nprobe) {
     if ((int)blockIdx.z < zf) {
         const int fb = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
@@ -525,7 +551,7 @@ __global__ void __launch_bounds__(256) k_hbulk_film(KParams<T> p, int inc_step, 
     if (inc_step && nprobe == 0 && blockIdx.x == 0 && blockIdx.y == 0 && k == 0 && threadIdx.x == 0 &&
         threadIdx.y == 0)
         p.step[0] = p.step[0] + 1;
-    hpass_block<T, NHALF, V, WX, WIDE>(p, blockIdx.x, blockIdx.y, k);
+    hpass_block<T, NHALF, V, WX, WIDE, BIG>(p, blockIdx.x, blockIdx.y, k);
 }
 
 template <typename T>
@@ -535,13 +561,13 @@ __global__ void __launch_bounds__(256) k_emixed(KParams<T> p) {
 }
 
 // batched: work[w] = (instance, x tile, y tile, plane)
-template <typename T, bool XC>
+template <typename T, bool XC, bool BIG>
 __global__ void __launch_bounds__(PTX *PTY)
     k_epass_batch(const KParams<T> *__restrict__ plist, const int4 *__restrict__ work, int nwork) {
     const int w = blockIdx.x;
     if (w >= nwork) return;
     const int4 wk = work[w];
-    epass_block<T, XC ? 2 : 0, 1, 1, false>(plist[wk.x], wk.y, wk.z, wk.w);
+    epass_block<T, XC ? 2 : 0, 1, 1, false, BIG>(plist[wk.x], wk.y, wk.z, wk.w);
 }
 
 // work[w] = (instance, first list entry of a 256-entry block)
@@ -560,7 +586,7 @@ __global__ void __launch_bounds__(256)
 // 0, 0), or (instance, kBatchProbes, 0, 0): the film blocks and the probe
 // block of an instance ride in the launch as in k_hbulk_film.  The step
 // counter of an instance moves with its probe block, or else its first tile.
-template <typename T, int NHALF>
+template <typename T, int NHALF, bool BIG>
 __global__ void __launch_bounds__(PTX *PTY)
     k_hbulk_batch(const KParams<T> *__restrict__ plist, const int4 *__restrict__ work, int nwork, int inc_step) {
     const int w = blockIdx.x;
@@ -577,7 +603,7 @@ __global__ void __launch_bounds__(PTX *PTY)
     }
     if (inc_step && p.nfold == 0 && wk.y == 0 && wk.z == 0 && wk.w == 0 && threadIdx.x == 0 && threadIdx.y == 0)
         p.step[0] = p.step[0] + 1;
-    hpass_block<T, NHALF, 1, 1, false>(p, wk.y, wk.z, wk.w);
+    hpass_block<T, NHALF, 1, 1, false, BIG, false>(p, wk.y, wk.z, wk.w);
 }
 
 int pass_tiles(const int *n) { return ((n[0] + PTX - 1) / PTX) * ((n[1] + PTY - 1) / PTY) * n[2]; }
@@ -588,29 +614,29 @@ static dim3 pass_grid(const int *n) {
     return dim3((n[0] + tx - 1) / tx, (n[1] + ty - 1) / ty, n[2]);
 }
 
-template <typename T, int V, int WX, bool WIDE>
+template <typename T, int V, int WX, bool WIDE, bool BIG>
 static void launch_e(const KParams<T> &p, hipStream_t s, const BoxTape *tape) {
     const dim3 g = pass_grid<V, WX>(p.n), b(64, 4);
     if (tape && p.cls16)
-        k_epass_tape<T, V, WX, WIDE, true><<<g, b, 0, s>>>(p, *tape);
+        k_epass_tape<T, V, WX, WIDE, BIG, true><<<g, b, 0, s>>>(p, *tape);
     else if (tape)
-        k_epass_tape<T, V, WX, WIDE, false><<<g, b, 0, s>>>(p, *tape);
+        k_epass_tape<T, V, WX, WIDE, BIG, false><<<g, b, 0, s>>>(p, *tape);
     else if (p.cls16)
-        k_epass<T, V, WX, WIDE, true><<<g, b, 0, s>>>(p);
+        k_epass<T, V, WX, WIDE, BIG, true><<<g, b, 0, s>>>(p);
     else
-        k_epass<T, V, WX, WIDE, false><<<g, b, 0, s>>>(p);
+        k_epass<T, V, WX, WIDE, BIG, false><<<g, b, 0, s>>>(p);
 }
 
-template <typename T, int NHALF, int V, int WX, bool WIDE>
+template <typename T, int NHALF, int V, int WX, bool WIDE, bool BIG>
 static void launch_hm(const KParams<T> &p, int nblk, int inc, int nprobe, hipStream_t s) {
     const dim3 g = pass_grid<V, WX>(p.n), b(64, 4);
     if (nblk == 0 && nprobe == 0) {
-        k_hbulk<T, NHALF, V, WX, WIDE><<<g, b, 0, s>>>(p, inc);
+        k_hbulk<T, NHALF, V, WX, WIDE, BIG><<<g, b, 0, s>>>(p, inc);
         return;
     }
     const int per_plane = (int)(g.x * g.y);
     const int zf = (nblk + (nprobe > 0 ? 1 : 0) + per_plane - 1) / per_plane;
-    k_hbulk_film<T, NHALF, V, WX, WIDE><<<dim3(g.x, g.y, g.z + zf), b, 0, s>>>(p, inc, zf, nblk, nprobe);
+    k_hbulk_film<T, NHALF, V, WX, WIDE, BIG><<<dim3(g.x, g.y, g.z + zf), b, 0, s>>>(p, inc, zf, nblk, nprobe);
 }
 
 // calls f with the shape of a grid's passes: V slots a lane, WX wavefronts
@@ -636,20 +662,24 @@ static void launch_hm(const KParams<T> &p, int nblk, int inc, int nprobe, hipStr
 // would get only the emptier ones (160 x 144 x 128 float64, 64 x 4 : 128 x 2
 // slots: 96 : 115 us; 160 x 100 x 60 float 26 : 29; but 256 x 128 x 48 float
 // 34.6 : 33.5, 96 x 64 x 48 13.6 : 13.2).
-template <int V, int WX, bool WIDE>
+template <int V, int WX, bool WIDE, bool BIG = false>
 struct PassShape {
     static constexpr int v = V, wx = WX;
-    static constexpr bool wide = WIDE;
+    static constexpr bool wide = WIDE, big = BIG;
 };
 template <typename T, typename F>
 static void with_shape(const KParams<T> &p, F f) {
     const int w64 = (p.n[0] + 63) / 64, w128 = (p.n[0] + 127) / 128; // wavefronts a row
-    if (p.wide < 0) return f(PassShape<1, 1, false>());
+    const bool big = big_array(p.px, p.n, sizeof(T));
+    // (schedule 6 takes the large arrays' form at every size)
+    if (p.wide < 0 || (big && !p.wide)) return f(PassShape<1, 1, false, true>());
     if constexpr (sizeof(T) == 8) {
         if (10 * w64 < 18 * w128) return f(PassShape<1, 1, false>());
+        if (big && p.wide) return f(PassShape<2, 2, true, true>());
         if (p.wide) return f(PassShape<2, 2, true>());
         return f(PassShape<2, 1, false>());
     } else {
+        if (big && p.wide) return f(PassShape<1, 4, true, true>());
         if (p.wide && p.n[0] >= 1024) return f(PassShape<1, 4, true>());
         if (p.wide) return f(PassShape<1, 2, true>());
         if (w64 % 2 == 0) return f(PassShape<1, 2, false>());
@@ -662,7 +692,7 @@ template <typename T>
 hipError_t launch_epass(const KParams<T> &p, hipStream_t s, const BoxTape *tape) {
     with_shape(p, [&](auto h) {
         typedef decltype(h) S;
-        launch_e<T, S::v, S::wx, S::wide>(p, s, tape);
+        launch_e<T, S::v, S::wx, S::wide, S::big>(p, s, tape);
     });
     if (p.nmixed > 0) k_emixed<T><<<dim3((p.nmixed + 255) / 256), dim3(256), 0, s>>>(p);
     return hipGetLastError();
@@ -676,9 +706,9 @@ hipError_t launch_hbulk_film(const KParams<T> &p, int nhalf, int nblk, int inc, 
     with_shape(p, [&](auto h) {
         typedef decltype(h) S;
         if (nhalf == 1)
-            launch_hm<T, 1, S::v, S::wx, S::wide>(p, nblk, inc, nprobe, s);
+            launch_hm<T, 1, S::v, S::wx, S::wide, S::big>(p, nblk, inc, nprobe, s);
         else
-            launch_hm<T, 2, S::v, S::wx, S::wide>(p, nblk, inc, nprobe, s);
+            launch_hm<T, 2, S::v, S::wx, S::wide, S::big>(p, nblk, inc, nprobe, s);
     });
     return hipGetLastError();
 }
@@ -690,25 +720,27 @@ hipError_t launch_hbulk(const KParams<T> &p, int nhalf, int inc, hipStream_t s) 
 
 template <typename T>
 hipError_t launch_epass_batch(const KParams<T> *plist, const int4 *work, int nwork, const int2 *mwork, int nmwork,
-                              bool xcls, hipStream_t s) {
+                              bool xcls, bool big, hipStream_t s) {
     if (nwork == 0) return hipSuccess;
-    if (xcls)
-        k_epass_batch<T, true><<<dim3(nwork), dim3(PTX, PTY), 0, s>>>(plist, work, nwork);
+    if (big)
+        k_epass_batch<T, true, true><<<dim3(nwork), dim3(PTX, PTY), 0, s>>>(plist, work, nwork);
+    else if (xcls)
+        k_epass_batch<T, true, false><<<dim3(nwork), dim3(PTX, PTY), 0, s>>>(plist, work, nwork);
     else
-        k_epass_batch<T, false><<<dim3(nwork), dim3(PTX, PTY), 0, s>>>(plist, work, nwork);
+        k_epass_batch<T, false, false><<<dim3(nwork), dim3(PTX, PTY), 0, s>>>(plist, work, nwork);
     if (nmwork > 0) k_emixed_batch<T><<<dim3(nmwork), dim3(256), 0, s>>>(plist, mwork, nmwork);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_hbulk_batch(const KParams<T> *plist, const int4 *work, int nwork, int nhalf, int inc,
+hipError_t launch_hbulk_batch(const KParams<T> *plist, const int4 *work, int nwork, int inc, bool big,
                               hipStream_t s) {
     if (nwork == 0) return hipSuccess;
     const dim3 g(nwork), b(PTX, PTY);
-    if (nhalf == 1)
-        k_hbulk_batch<T, 1><<<g, b, 0, s>>>(plist, work, nwork, inc);
+    if (big)
+        k_hbulk_batch<T, 2, true><<<g, b, 0, s>>>(plist, work, nwork, inc);
     else
-        k_hbulk_batch<T, 2><<<g, b, 0, s>>>(plist, work, nwork, inc);
+        k_hbulk_batch<T, 2, false><<<g, b, 0, s>>>(plist, work, nwork, inc);
     return hipGetLastError();
 }
 
@@ -717,8 +749,8 @@ hipError_t launch_hbulk_batch(const KParams<T> *plist, const int4 *work, int nwo
     template hipError_t launch_hbulk<T>(const KParams<T> &, int, int, hipStream_t);                       \
     template hipError_t launch_hbulk_film<T>(const KParams<T> &, int, int, int, hipStream_t, int);             \
     template hipError_t launch_epass_batch<T>(const KParams<T> *, const int4 *, int, const int2 *, int,   \
-                                              bool, hipStream_t);                                         \
-    template hipError_t launch_hbulk_batch<T>(const KParams<T> *, const int4 *, int, int, int, hipStream_t);
+                                              bool, bool, hipStream_t);                                   \
+    template hipError_t launch_hbulk_batch<T>(const KParams<T> *, const int4 *, int, int, bool, hipStream_t);
 MPX_PASSES(float)
 MPX_PASSES(double)
 

@@ -147,17 +147,21 @@ struct RowPml {
     unsigned ox[V] = {};      // byte offset of the slot's x-slab value in its row
 };
 
-// uniform first element of the row's psi along axis w
+// uniform first element of the row's psi along axis w (row counts fit 32 bits)
 template <typename T>
 __device__ __forceinline__ long long row_psi(const KParams<T> &p, int w, int j, int k) {
     const int S = p.nlo[w] + p.nhi[w];
-    if (w == 0) return (long long)S * ((long long)j + (long long)p.n[1] * k);
-    if (w == 1) {
+    unsigned row;
+    if (w == 0) {
+        row = (unsigned)j + (unsigned)p.n[1] * (unsigned)k;
+    } else if (w == 1) {
         const int sp = j < p.nlo[1] ? j : p.nlo[1] + (j - (p.n[1] - p.nhi[1]));
-        return (long long)p.px * ((long long)sp + (long long)S * k);
+        row = (unsigned)sp + (unsigned)S * (unsigned)k;
+    } else {
+        const int sp = k < p.nlo[2] ? k : p.nlo[2] + (k - (p.n[2] - p.nhi[2]));
+        row = (unsigned)j + (unsigned)p.n[1] * (unsigned)sp;
     }
-    const int sp = k < p.nlo[2] ? k : p.nlo[2] + (k - (p.n[2] - p.nhi[2]));
-    return (long long)p.px * ((long long)j + (long long)p.n[1] * sp);
+    return (long long)((unsigned long long)(unsigned)(w == 0 ? S : p.px) * row);
 }
 
 template <typename T>
