@@ -128,7 +128,7 @@ def run_gpu(w, precision, steps, warmup, timing_steps=12, schedule=0):
 
 def schedule_name(sched):
     if sched == 0:
-        return "separate E and H/M passes (256 x 1 tiles on grids at least 512 wide)"
+        return "separate E and H/M passes (tiles by grid width and precision)"
     if sched == 6:
         return "separate E and H/M passes on 64 x 4 tiles"
     return f"fused pass, variant {sched}"
@@ -150,9 +150,8 @@ def roofline_for(w, esz, kt, dtype_name, schedule=0, wkey="c5"):
            "algorithmic_bytes_per_launch": ab[name], "avg_launch_ms": round(ms, 5), "launches_timed": nl,
            "film_half1_ms_per_step": round(kt[2][0], 5)}
     if not fused:
-        # the H/M pass group also holds the film's second half step (on
-        # 256 x 1 tiles in the same launch, with the probes when all of them
-        # read only E or a film's mean M)
+        # the H/M pass group also holds the film's second half step (in the
+        # same launch, with the probes when none of them reads H)
         out["other_stencil_kernel"] = {"kernel": ("h_pass", "e_pass")[0 if name == "e_pass" else 1],
                                        "avg_launch_ms": round(kt[1 if name == "e_pass" else 0][0], 5)}
     return out

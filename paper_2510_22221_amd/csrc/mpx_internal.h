@@ -121,7 +121,7 @@ struct KParams {
     const T *coefv;
     const uint8_t *id;
     const uint8_t *cls; // per slot: the shared id of the 8 cells around it, or 255
-    const uint8_t *pflags; // per separate-pass tile: 1 CPML, 2 source, 4 film within reach
+    const uint8_t *pflags; // per separate-pass tile: 2 source, 4 film within reach
     // wide = 1: rows of at least two 256-slot tiles, with flags per 256 x 1
     // tile in pflags_w; -1: the single-instance passes use 64 x 4 tiles whatever
     // the grid, as batches do
