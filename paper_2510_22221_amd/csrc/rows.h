@@ -1,6 +1,6 @@
-// rows.h -- the stencil passes' view of a wavefront: 64 (or, with V slots a lane,
-// 64 V) consecutive slots of
-// one row (j, k), so that everything but the x position is uniform.
+// rows.h -- the stencil passes' view of a wavefront: 64 (or, with V slots a
+// lane, 64 V) consecutive slots of one row (j, k), so that everything but the x
+// position is uniform.
 //
 // What a pass spends beside its bytes is instructions: with per-lane rows,
 // slab tests and 64-bit psi addresses the float32 E pass of a 512 x 256 x 128
@@ -8,11 +8,11 @@
 // vector and 78 % of the (per-CU) scalar issue slots of its time.  Here rows,
 // planes and the y and z slabs are scalar, an address is a scalar base and one
 // 32-bit lane offset, and the recursion coefficients of y and z slabs come
-// through the scalar cache: 72 and 171 instructions, 34 registers instead of
-// 70, 146 -> 131 us (5.3 TB/s of the pass's own bytes; a copy reaches 5.1).
-// Smaller grids, whose fields stay in the last-level cache, gain more: a batch
-// of 32 resonators E 330 -> 239 us, H/M 279 -> 249; 211 x 109 x 77 float64 47 ->
-// 40 and 44 -> 38 us.
+// through the scalar cache: 80 and 138 instructions, 35 registers instead of
+// 70; 146 -> 131 us (5.3 TB/s of the pass's own bytes; a copy reaches 5.1), and
+// 121 with the tiles and coefficients of passes.hip.  Smaller grids, whose
+// fields stay in the last-level cache, gain more: a batch of 32 resonators E
+// 330 -> 215 us, H/M 279 -> 226; 211 x 109 x 77 float64 47 -> 34 and 44 -> 35 us.
 #pragma once
 
 #include "device_common.h"
