@@ -514,14 +514,51 @@ mpx_status upload_profiles(mpx_sim *s) {
 
 // the number of probes that ride in the H/M launch: all of them when every one
 // reads only what that launch does not write (probe_folds; energy: also a
-// film's or the grid's energy, whose partials a launch before it writes), else
-// none (the probe launch takes them)
-int folded_probes(const mpx_sim *s, bool energy = true) {
-    const int np = (int)s->probes.size();
-    for (const ProbeHost &pr : s->probes)
-        if (!probe_folds(pr.dev) || (pr.dev.kind >= MPX_PROBE_FILM_ENERGY && !energy)) return 0;
-    return np;
+// film's or the grid's energy, whose partials a launch before it writes) and
+// its probe block, which samples them one after another, costs no more than
+// the probe launch with its block a probe; else none.  The times (us a step,
+// closed boxes and resonators of 3 10^3 to 1.7 10^7 cells): a probe's in the
+// block, the launch's own, what of the block passes beside the launch's
+// film blocks and tiles (`bytes`: what those move).  All in the H/M launch :
+// in the probe launch, float32 unless said: 4 and 64 E points on 64 x 48 x 40
+// 15.7 : 16.8 and 72.4 : 17.1, 16 on 211 x 109 x 77 (float64) 79.3 : 77.4, 32 and
+// 64 on 512 x 256 x 128 240.8 : 243.4 and 275 : 244; 2, 4 and 64 means of M on
+// 64 x 48 x 40 16.6 : 19.2, 21.0 : 19.3 and 148.6 : 19.4, one of a film of 1053
+// blocks a family (400 x 128 x 40) 100.6 : 97.5; 3 and 5 film energies on
+// 32 x 32 x 32 18.6 : 19.3 and 21.1 : 19.4; 1, 4 and 8 grid energies on
+// 512 x 256 x 64 365 : 415, 682 : 681 and 1124 : 1053
+int folded_probes(const mpx_sim *s, double bytes, bool energy = true) {
+    double chain = 0.0, sums = 0.0, own = 0.0;
+    for (const ProbeHost &pr : s->probes) {
+        const ProbeDev &P = pr.dev;
+        if (!probe_folds(P) || (P.kind >= MPX_PROBE_FILM_ENERGY && !energy)) return 0;
+        const double rounds = (double)((P.npart + 255) / 256);
+        double launch;
+        if (P.kind == MPX_PROBE_FIELD) {
+            chain += 0.95;
+            launch = 2.2;
+        } else if (P.kind == MPX_PROBE_MEAN_M) {
+            const int *nb = s->films[P.film].nblk;
+            const int n = std::max(nb[0], std::max(nb[1], nb[2]));
+            chain += 1.9 + n / 95.0;
+            launch = 4.2 + 0.5 * ((n + 255) / 256);
+        } else if (P.kind == MPX_PROBE_FILM_ENERGY) {
+            chain += 0.7 + 0.6 * rounds;
+            launch = 2.4 + 0.4 * rounds;
+        } else {
+            chain += 1.3;
+            sums += 0.155 * rounds;
+            launch = 2.5 + 0.4 * rounds;
+        }
+        own = std::max(own, launch);
+    }
+    const double beside = std::max(0.0, 2.0 + bytes / 21e6 - s->nblk / 1000.0);
+    const double excess = std::max(0.0, chain - beside) + std::max(0.0, sums - bytes / 7e6);
+    return excess <= own ? (int)s->probes.size() : 0;
 }
+
+// what an H/M pass moves: six fields in, three out
+double hm_bytes(const mpx_sim *s) { return 9.0 * (double)s->nslot * (double)s->esz; }
 
 // One step of the body (not the last): the fused pass or the two separate
 // stencil passes, then the film half steps and the probes.  `par` is the
@@ -573,11 +610,11 @@ mpx_status run_body(mpx_sim *s, int &par, bool timed) {
     }
     // two-pass schedule, in place: E pass, the film's first half step (its
     // prepass reads H before the bulk pass moves it) and probes, then the
-    // film's second half step with the bulk H pass (and the probes, when all
-    // of them read only E or mean M: the H/M launch writes neither)
+    // film's second half step with the bulk H pass (and the probes, where
+    // folded_probes puts them there)
     KParams<T> p;
     fill_params<T>(s, p, MODE_INPLACE, par);
-    const int npf = folded_probes(s);
+    const int npf = folded_probes(s, hm_bytes(s));
     if ((r = rec(0, 0)) != MPX_OK) return r;
     CK(launch_epass<T>(p, st));
     if ((r = rec(0, 1)) != MPX_OK) return r;
@@ -599,7 +636,7 @@ mpx_status run_last(mpx_sim *s, int par, hipStream_t st = nullptr) {
     if (!st) st = s->stream;
     CK(launch_epass<T>(p, st));
     CK(launch_film<T>(p, s->nblk, 1, 0, st));
-    const int npf = folded_probes(s);
+    const int npf = folded_probes(s, hm_bytes(s));
     CK(launch_probes<T>(p, (int)s->probes.size(), s->probe_maxpart, st, npf > 0));
     CK(launch_hbulk_film<T>(p, 1, s->nblk, 1, st, npf));
     return MPX_OK;
@@ -839,6 +876,8 @@ mpx_status batch_tables(mpx_batch *b) {
     std::vector<int4> work, work2, workh;
     std::vector<int2> wmixed, wfilm, wext, wprobe;
     std::vector<int> tick;
+    double bytes = 0.0; // the members' H/M passes share a launch
+    for (const mpx_sim *s : b->sims) bytes += hm_bytes(s);
     for (int q = 0; q < (int)b->sims.size(); q++) {
         const mpx_sim *s = b->sims[q];
         if (b->variant == 0) {
@@ -857,7 +896,7 @@ mpx_status batch_tables(mpx_batch *b) {
         }
         for (int k = 0; k < s->nblk; k++) wfilm.push_back(make_int2(q, k));
         for (int k = 0; k < s->nblk_ext; k++) wext.push_back(make_int2(q, k));
-        b->nfold.push_back(b->variant == 0 ? folded_probes(s, false) : 0);
+        b->nfold.push_back(b->variant == 0 ? folded_probes(s, bytes, false) : 0);
         const bool folded = b->nfold.back() > 0;
         if (!folded)
             for (int k = 0; k < (int)s->probes.size(); k++) wprobe.push_back(make_int2(q, k));
@@ -1794,7 +1833,7 @@ mpx_status run_adjoint_tape(mpx_sim *s, long long N, const AdjLoss &ls, int K, c
         auto fwd = [&](int len, bool probes) -> mpx_status {
             KParams<T> p;
             fill_params<T>(s, p, MODE_INPLACE, s->parity);
-            const int np = (int)s->probes.size(), npf = probes ? folded_probes(s) : 0;
+            const int np = (int)s->probes.size(), npf = probes ? folded_probes(s, hm_bytes(s)) : 0;
             BoxTape bt;
             for (int a = 0; a < 3; a++) {
                 bt.b0[a] = eps_box[a];

@@ -65,7 +65,8 @@ struct ProbeDev {
 // 2), which a wavefront sums in at most eight rounds of 256, or the grid's
 // (kind 3), whose sum takes the longer the more tiles the launch has beside it
 // (160 x 144 x 128 in float64: 20 us in the probe launch at a step that
-// samples, 5 us for a film's mean M alone at the others)
+// samples, 5 us for a film's mean M alone at the others).  How many of them
+// it takes is the host's to say (folded_probes)
 __host__ __device__ inline bool probe_folds(const ProbeDev &P) {
     return (P.kind == 0 && P.field < 3) || P.kind == 1 || (P.kind == 2 && P.npart <= 2048) ||
            P.kind == 3;
