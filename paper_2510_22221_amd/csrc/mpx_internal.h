@@ -308,6 +308,7 @@ int pass_tiles(const int *n);
 constexpr int kPassTX = 64, kPassTY = 4; // separate-pass tile: 64 x 4 slots of one plane
 constexpr int kWideTX = 256, kWideTY = 1; // the wide tile of the single-instance passes
 constexpr int kWideMinNx = 512;           // grids this wide use it
+constexpr unsigned kMaxGridZ = 65535;     // blocks of a launch along z (the device's limit is 65536)
 
 // the bulk H/M pass with the film's part of it (nhalf 2: the second half step
 // of a merged pair; 1: the commit of a half step) and, nprobe > 0, the probes

@@ -634,8 +634,16 @@ static void launch_hm(const KParams<T> &p, int nblk, int inc, int nprobe, hipStr
         k_hbulk<T, NHALF, V, WX, WIDE, BIG><<<g, b, 0, s>>>(p, inc);
         return;
     }
-    const int per_plane = (int)(g.x * g.y);
-    const int zf = (nblk + (nprobe > 0 ? 1 : 0) + per_plane - 1) / per_plane;
+    const int per_plane = (int)(g.x * g.y), nfront = nblk + (nprobe > 0 ? 1 : 0);
+    const int zf = (nfront + per_plane - 1) / per_plane;
+    if (g.z + zf > kMaxGridZ) {
+        // a long narrow grid whose film fills most of its cross section: the
+        // film and probe blocks in a launch of their own, along x (its one
+        // "plane" holds no tile), then the tiles; the two touch disjoint data
+        k_hbulk_film<T, NHALF, V, WX, WIDE, BIG><<<dim3(nfront), b, 0, s>>>(p, inc, 1, nblk, nprobe);
+        k_hbulk<T, NHALF, V, WX, WIDE, BIG><<<g, b, 0, s>>>(p, nprobe > 0 ? 0 : inc);
+        return;
+    }
     k_hbulk_film<T, NHALF, V, WX, WIDE, BIG><<<dim3(g.x, g.y, g.z + zf), b, 0, s>>>(p, inc, zf, nblk, nprobe);
 }
 
