@@ -681,17 +681,21 @@ hipError_t launch_bhat(const KParams<T> &p, int phase, hipStream_t s) {
 
 // films of at most this many blocks (of 256 faces, over all families) run
 // their first half step and its prepass in one launch: a launch and its
-// latency chain less against five times the loads, which up to some three
-// blocks a CU hide in the chain.  Two launches : one, us of a step: 51 blocks
-// (128 x 64 x 64, float32) 24.5 : 22.7, 189 (256 x 128 x 48) 46.2 : 44.0 and in
-// float64 74.4 : 71.8, 351 (384 x 160 x 48) 66.0 : 63.2 and 114.0 : 112.3; us
-// of the kernels, 738 blocks 15.2 : 13.7 and 16.1 : 16.4, 3864 blocks 47 : 60
-constexpr int kFilmFirstMax = 1024;
+// latency chain less against more loads, which up to some three blocks a CU
+// hide in the chain (a face forms what it takes from the prepass itself: some
+// 50 loads instead of 32, and the prepass's seven a face of the grown box stay
+// beside it, for the second half step).  Two launches : one, us of a step:
+// float32 51 blocks (128 x 64 x 64) 24.5 : 22.7, 297 28.5 : 25.6, 531 31.5 : 28.6,
+// 798 37.0 : 35.5, 990 39.6 : 39.3; float64 123 blocks 25.9 : 23.7, 531 38.2 : 37.1,
+// 654 46.6 : 45.4, 711 45.6 : 46.3, 798 47.8 : 49.1, 990 49.4 : 52.0; us of the
+// kernels, 3864 blocks 47 : 60
+template <typename T>
+constexpr int kFilmFirstMax = sizeof(T) == 8 ? 680 : 1024;
 
 template <typename T>
 hipError_t launch_film(const KParams<T> &p, int nblk, int phase, int inc, hipStream_t s) {
     if (nblk == 0) return hipSuccess;
-    if (phase == 1 && !inc && nblk <= kFilmFirstMax) {
+    if (phase == 1 && !inc && nblk <= kFilmFirstMax<T>) {
         hipLaunchKernelGGL(k_film_first<T>, dim3(nblk + p.nblk_ext), dim3(256), 0, s, p, nblk);
         return hipGetLastError();
     }
@@ -749,7 +753,7 @@ template <typename T>
 hipError_t launch_film_batch(const KParams<T> *plist, const int2 *work_ext, int n_ext, const int2 *work, int n,
                              int phase, int inc, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    if (phase == 1 && !inc && n <= kFilmFirstMax) {
+    if (phase == 1 && !inc && n <= kFilmFirstMax<T>) {
         hipLaunchKernelGGL(k_film_first_batch<T>, dim3(n + n_ext), dim3(256), 0, s, plist, work_ext, work, n);
         return hipGetLastError();
     }
