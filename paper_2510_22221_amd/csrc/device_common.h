@@ -44,20 +44,17 @@ __device__ __forceinline__ T dif(T hi, T lo, T d, T invd) {
 // x / d_w in float64, correctly rounded, x a difference of two fields of type
 // T.  A float64 division is a chain of some eleven instructions, and a film
 // face without its prepass makes 18: for float fields (x is zero or at least
-// 2^-149, so nothing below underflows) the spacing's reciprocal zh + zl gives a
-// quotient within an ulp, and one residual step with zh = RN(1/d) rounds it
-// correctly (Markstein 1990); div_fixup puts the zeros' signs, infinities and
-// NaN right.  64 x 12 x 4 film: first half step 8.2 -> 6.0 us.  Float64 fields
-// may be small enough for the residual to underflow and keep the division.
+// 2^-149, so nothing below underflows) three multiply-adds with the spacing's
+// reciprocal do (spacing_quotient), and div_fixup puts the zeros' signs,
+// infinities and NaN right.  64 x 12 x 4 film: first half step 8.2 -> 6.0 us.
+// Float64 fields may be small enough for the residual to underflow and keep
+// the division.
 template <typename T>
 __device__ __forceinline__ double over_spacing(const KParams<T> &p, double x, int w) {
     if constexpr (sizeof(T) == 8) {
         return x / p.d[w];
-    } else {
-        const double q = __builtin_fma(x, p.rd[w], x * p.rdl[w]);
-        const double r = __builtin_fma(-q, p.d[w], x);
-        return __builtin_amdgcn_div_fixup(__builtin_fma(r, p.rd[w], q), p.d[w], x);
-    }
+    else
+        return __builtin_amdgcn_div_fixup(spacing_quotient(x, p.d[w], p.rd[w], p.rdl[w]), p.d[w], x);
 }
 
 // value of a field at (i, j, k), folded on periodic axes; zero outside the

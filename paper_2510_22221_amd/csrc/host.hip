@@ -291,8 +291,7 @@ void fill_params(const mpx_sim *s, KParams<T> &p, int mode = MODE_INPLACE, int p
         p.d[a] = s->d[a];
         p.dT[a] = (T)s->d[a];
         p.invd[a] = (T)(1.0 / s->d[a]);
-        p.rd[a] = 1.0 / s->d[a];
-        p.rdl[a] = std::fma(-p.rd[a], s->d[a], 1.0) / s->d[a];
+        spacing_parts(s->d[a], p.rd[a], p.rdl[a]);
         p.nlo[a] = s->nlo[a];
         p.nhi[a] = s->nhi[a];
         p.bE[a] = (const T *)s->bE[a];

@@ -11,6 +11,22 @@ constexpr int kMaxSources = 16;
 constexpr int kMaxProbes = 64;
 constexpr int kMaxFilms = 64;
 
+// the reciprocal of a spacing, to nearest, and the rest of it
+__host__ __device__ inline void spacing_parts(double d, double &rd, double &rdl) {
+    rd = 1.0 / d;
+    rdl = __builtin_fma(-rd, d, 1.0) / d;
+}
+
+// x / d correctly rounded for a finite x that is zero or whose quotient's
+// residual does not underflow (differences of float fields): the two parts give
+// a quotient within an ulp, one residual step rounds it (Markstein 1990).  A
+// zero quotient's sign is the caller's.
+__host__ __device__ inline double spacing_quotient(double x, double d, double rd, double rdl) {
+    const double q = __builtin_fma(x, rd, x * rdl);
+    const double r = __builtin_fma(-q, d, x);
+    return __builtin_fma(r, rd, q);
+}
+
 struct MatDev {
     double eps_r, sigma, Ms, alpha, gamma_abs;
     int is_pec, pad;
