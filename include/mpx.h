@@ -266,15 +266,17 @@ mpx_status mpx_film_box(const mpx_sim *sim, int32_t film, int32_t box[6], int64_
 mpx_status mpx_set_graph_steps(mpx_sim *sim, int32_t steps);
 
 /* Step schedule.  fused = 0 (default): a separate E pass and H/M pass per
- * step, each in place with one thread per slot.  fused = 1..5: one fused
+ * step, each in place (float32: one slot a thread; float64: one or two by the
+ * width).  fused = 1..5: one fused
  * stencil pass per step (the E step and the merged H/M half-step pair in one
  * z-marching sweep over ping-pong buffers, z-chunks of `kchunk` planes; 0
  * keeps the current chunk, default 16): 1 = register-blocked sweep (64 x 4
  * columns per block, each thread recomputes the neighbour edges it needs);
  * 2..5 = LDS-staged sweep over 64 x 8 tiles (2: two rows per thread, >= 2
  * waves per SIMD; 3: two rows, >= 4 waves; 4: one row, >= 2 waves; 5: one
- * row, >= 4 waves).  fused = 6: the separate passes on 64 x 4 tiles also
- * on grids at least 512 cells wide (which schedule 0 runs on 256 x 1 tiles).
+ * row, >= 4 waves).  fused = 6: the separate passes with one slot a thread on
+ * 64 x 4 tiles, whatever the width, and with the addressing that schedule 0
+ * keeps for arrays of 4 GiB and more.
  * All give bitwise identical results.  Errors: MPX_E_INVALID for fused
  * outside 0..6 or kchunk < 0. */
 mpx_status mpx_set_schedule(mpx_sim *sim, int32_t fused, int32_t kchunk);
@@ -387,7 +389,8 @@ mpx_status mpx_set_adjoint_memory(mpx_sim *sim, int64_t max_bytes);
  * nsteps time steps with one fused stencil launch per step covering all
  * members' tiles, and one launch each for their film half steps and probes,
  * so that small grids still fill the chip (with the separate-pass schedule:
- * one launch per pass).  Each member's results are
+ * one launch per pass, the films' second half step and most probes in the H/M
+ * pass's).  Each member's results are
  * bitwise identical to stepping it alone with mpx_step under the same tile
  * variant.  Sources, probes and films of each member behave exactly as for
  * a lone handle (its probe ring and step counter advance).

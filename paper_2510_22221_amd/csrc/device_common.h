@@ -51,7 +51,7 @@ __device__ __forceinline__ T dif(T hi, T lo, T d, T invd) {
 // the division.
 template <typename T>
 __device__ __forceinline__ double over_spacing(const KParams<T> &p, double x, int w) {
-    if constexpr (sizeof(T) == 8) {
+    if constexpr (sizeof(T) == 8)
         return x / p.d[w];
     else
         return __builtin_amdgcn_div_fixup(spacing_quotient(x, p.d[w], p.rd[w], p.rdl[w]), p.d[w], x);
@@ -97,10 +97,10 @@ __device__ __forceinline__ int4 block_entry(const int4 *tab, int b) {
 }
 
 // ---------------------------------------------------------------------------
-// probes at an integer time (the probe launch, and the probe block of the
-// merged H/M launch for the kinds that read neither H nor energy partials;
-// the probe launch's mean-M tree and block_order_sums3 add the same values
-// in the same grouping)
+// probes at an integer time (the probe launch, and the probe block of the H/M
+// launch for the kinds that read nothing that launch writes: E, a film's mean
+// M, energies from their partials; the probe launch's trees and the
+// block_order sums add the same values in the same grouping)
 // ---------------------------------------------------------------------------
 // whether a probe samples at the step in progress (its counter `step`), and
 // the sample's index

@@ -160,7 +160,7 @@ struct mpx_sim {
     ProbeDev *d_probes = nullptr;
     int probe_maxpart = 0; // most partial-sum blocks of an energy probe
     SrcDev *d_srcs = nullptr; // device copy of the source descriptors
-    uint8_t *d_pflags = nullptr; // per separate-pass tile: CPML / source / film bits
+    uint8_t *d_pflags = nullptr; // per separate-pass tile: source / film bits
     uint8_t *d_pflags_w = nullptr; // the same for the wide tiles (when nx >= kWideMinNx)
     int4 *d_mixed = nullptr;     // mixed-class slots without an extended triple (the general path)
     int nmixed = 0;

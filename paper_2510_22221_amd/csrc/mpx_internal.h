@@ -302,7 +302,6 @@ hipError_t launch_set_step(long long *step, long long v, hipStream_t s);
 template <typename T> hipError_t launch_bhat(const KParams<T> &p, int phase, hipStream_t s);
 hipError_t launch_adj_init_ms(const int4 *blocktab, int nblk, const FilmDev *films, const AdjFilmDev *af,
                               const double *u, hipStream_t s);
-template <typename T> hipError_t launch_hbulk(const KParams<T> &p, int nhalf, int inc, hipStream_t s);
 // tape: also write E^n and the curl input x^n of the eps box's edges to it
 struct BoxTape {
     double *dst = nullptr; // [6][region], region: the box (b0, size) grown by one slot
@@ -320,7 +319,6 @@ hipError_t launch_hbulk_batch(const KParams<T> *plist, const int4 *work, int nwo
 inline bool big_array(int px, const int *n, size_t es) {
     return (unsigned long long)px * n[1] * n[2] * es >= 1ull << 32;
 }
-int pass_tiles(const int *n);
 constexpr int kPassTX = 64, kPassTY = 4; // separate-pass tile: 64 x 4 slots of one plane
 constexpr int kWideTX = 256, kWideTY = 1; // the wide tile of the single-instance passes
 constexpr int kWideMinNx = 512;           // grids this wide use it

@@ -253,7 +253,8 @@ __device__ __forceinline__ void epass_row(const KParams<T> &p, const RowPos &r, 
 // a wide grid, else V of 64 x 4), read through the scalar cache (the aligned
 // word that holds each; the tables are whole words): a vector load here would
 // put the field loads behind its wait, since the vector memory counter
-// completes in order.  A wavefront past the row reads the row's last tile.
+// completes in order.  A row past the grid (of a partial block) reads the last
+// row's tile.
 template <typename T, int V>
 __device__ __forceinline__ int row_flags(const KParams<T> &p, const RowPos &r, bool wide) {
     typedef __attribute__((address_space(4))) const uint32_t cword;
@@ -606,8 +607,6 @@ __global__ void __launch_bounds__(PTX *PTY)
     hpass_block<T, NHALF, 1, 1, false, BIG, false>(p, wk.y, wk.z, wk.w);
 }
 
-int pass_tiles(const int *n) { return ((n[0] + PTX - 1) / PTX) * ((n[1] + PTY - 1) / PTY) * n[2]; }
-
 template <int V, int WX>
 static dim3 pass_grid(const int *n) {
     const int tx = 64 * V * WX, ty = 4 / WX;
@@ -722,11 +721,6 @@ hipError_t launch_hbulk_film(const KParams<T> &p, int nhalf, int nblk, int inc, 
 }
 
 template <typename T>
-hipError_t launch_hbulk(const KParams<T> &p, int nhalf, int inc, hipStream_t s) {
-    return launch_hbulk_film<T>(p, nhalf, 0, inc, s, 0);
-}
-
-template <typename T>
 hipError_t launch_epass_batch(const KParams<T> *plist, const int4 *work, int nwork, const int2 *mwork, int nmwork,
                               bool xcls, bool big, hipStream_t s) {
     if (nwork == 0) return hipSuccess;
@@ -754,7 +748,6 @@ hipError_t launch_hbulk_batch(const KParams<T> *plist, const int4 *work, int nwo
 
 #define MPX_PASSES(T)                                                                                      \
     template hipError_t launch_epass<T>(const KParams<T> &, hipStream_t, const BoxTape *);                \
-    template hipError_t launch_hbulk<T>(const KParams<T> &, int, int, hipStream_t);                       \
     template hipError_t launch_hbulk_film<T>(const KParams<T> &, int, int, int, hipStream_t, int);             \
     template hipError_t launch_epass_batch<T>(const KParams<T> *, const int4 *, int, const int2 *, int,   \
                                               bool, bool, hipStream_t);                                   \

@@ -1,8 +1,7 @@
 """Schedule autotuner for the fused step pass.
 
-A step runs as two separate passes (schedule 0, or 6 for 64 x 4 tiles on
-grids that schedule 0 runs on 256 x 1 tiles) or as one fused pass in one of
-five tile variants with a z-chunk length; which is fastest depends on
+A step runs as two separate passes (schedule 0, or 6 for one slot a thread
+on 64 x 4 tiles at every width) or as one fused pass in one of five tile variants with a z-chunk length; which is fastest depends on
 the grid shape, the share of CPML and film tiles, and the precision.  ``tune`` builds scratch
 simulations of the caller's workload (the caller's own handles are never
 stepped), times every candidate with captured graphs, and caches the winner
@@ -27,7 +26,7 @@ DEFAULT_CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tune_c
 
 def candidates(nz: int, single: bool = False) -> List[Tuple[int, int]]:
     """(schedule, z-chunk) pairs: the separate passes (schedule 0; for a
-    single handle also on 64 x 4 tiles on wide grids, schedule 6), and the
+    single handle also on 64 x 4 tiles at every width, schedule 6), and the
     fused variants 1-5 at each z-chunk."""
     out = [(0, 16)]  # the separate passes have no z-chunk
     if single:
