@@ -315,35 +315,49 @@ __device__ __forceinline__ void emixed_slot(const KParams<T> &p, int m) {
         emixed_apply<T, true>(p, CoefMem<T>{p.coef}, s, kMixed);
 }
 
-// the magnetic faces of a wavefront's slots: not stored (st).  Each lane looks
-// at one film (there are at most 64), so that a row out of every film's face box
-// is known after one round trip; face boxes do not overlap, and the films that
-// meet the row's slots, one or none mostly, are then taken one by one.  Face by
+// the magnetic faces of a wavefront's slots: not stored (st).  Which films' face
+// boxes meet the row's slots is scalar work, four films a round trip through the
+// scalar cache, which waits for no field load; boxes do not overlap, and the
+// films that meet it, one or none mostly, are then taken one by one.  Face by
 // face over the list, a tile near a film waited some 2 us a film with two slots
-// a lane and 1 with one: 200 x 160 x 40, 48 films, H/M launch float64 124 -> 35
-// us, float32 80 -> 23; one film 27.6 -> 27.6, 17.2 -> 17.4.
+// a lane and 1.3 with one.  H/M launch, us: 200 x 160 x 40 with 48 films float64
+// 124 -> 39, float32 80 -> 35; 160 x 144 x 128 with one 45.5 -> 44.8, 34.5 -> 27.4.
+// (A lane a film and a ballot: 35.5 and 24 with 48, but 47.8 and 27.4 with one,
+// the box loads waiting behind the fields'.)
 template <typename T, int V>
 __device__ __forceinline__ void film_faces(const KParams<T> &p, const RowPos &r, bool (&st0)[V], bool (&st1)[V],
                                            bool (&st2)[V]) {
-    bool meets = false;
-    if ((int)threadIdx.x < p.nfilm) {
-        const FilmDev &F = p.films[threadIdx.x];
-        const int y = r.j - F.b0[1], z = r.k - F.b0[2];
-        meets = y >= 0 && y < F.bn[1] && z >= 0 && z < F.bn[2] && F.b0[0] < r.w0 + 64 * V && F.b0[0] + F.bn[0] > r.w0;
-    }
-    for (unsigned long long m = __builtin_amdgcn_ballot_w64(meets); m; m &= m - 1) {
-        const FilmDev F = film_desc(p.films, __builtin_ctzll(m));
-        // (a film's faces of one family fit 32 bits)
-        const double *ms = F.prm + (unsigned)F.bn[0] * (unsigned)(r.j - F.b0[1] + F.bn[1] * (r.k - F.b0[2]));
+    constexpr int G = 4;
+    for (int g0 = 0; g0 < p.nfilm; g0 += G) {
+        int b[G][6]; // b0, bn
 #pragma unroll
-        for (int v = 0; v < V; v++) {
-            const int x = r.i + v - F.b0[0];
-            const bool in = x >= 0 && x < F.bn[0];
-            const double *q = ms + (in ? x : 0);
-            const double a = q[0], b = q[3 * F.ns], c = q[6 * F.ns];
-            st0[v] = st0[v] && !(in && a > 0.0);
-            st1[v] = st1[v] && !(in && b > 0.0);
-            st2[v] = st2[v] && !(in && c > 0.0);
+        for (int g = 0; g < G; g++) {
+            const cword_t *src = (const cword_t *)(p.films + min(g0 + g, p.nfilm - 1));
+#pragma unroll
+            for (int w = 0; w < 6; w++) b[g][w] = (int)src[w];
+        }
+        unsigned meet = 0;
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            const int y = r.j - b[g][1], z = r.k - b[g][2];
+            const bool in = g0 + g < p.nfilm && y >= 0 && y < b[g][4] && z >= 0 && z < b[g][5] &&
+                            b[g][0] < r.w0 + 64 * V && b[g][0] + b[g][3] > r.w0;
+            meet |= in ? 1u << g : 0u;
+        }
+        for (; meet; meet &= meet - 1) {
+            const FilmDev F = film_desc(p.films, g0 + __builtin_ctz(meet));
+            // (a film's faces of one family fit 32 bits)
+            const double *ms = F.prm + (unsigned)F.bn[0] * (unsigned)(r.j - F.b0[1] + F.bn[1] * (r.k - F.b0[2]));
+#pragma unroll
+            for (int v = 0; v < V; v++) {
+                const int x = r.i + v - F.b0[0];
+                const bool in = x >= 0 && x < F.bn[0];
+                const double *q = ms + (in ? x : 0);
+                const double m0 = q[0], m1 = q[3 * F.ns], m2 = q[6 * F.ns];
+                st0[v] = st0[v] && !(in && m0 > 0.0);
+                st1[v] = st1[v] && !(in && m1 > 0.0);
+                st2[v] = st2[v] && !(in && m2 > 0.0);
+            }
         }
     }
 }

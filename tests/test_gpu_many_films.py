@@ -1,5 +1,5 @@
 """Grids with as many films as a handle takes (64): the H/M pass finds the
-films that meet a wavefront's row by one lane a film.
+films that meet a wavefront's row first, then their faces.
 
 Against the fused sweep (which looks a face up in the film list by itself),
 bitwise: films that start and end at, before and after a wavefront's and a
